@@ -28,17 +28,14 @@ CFLAGS = [
     # from one build to the next.
     "-falign-loops=64",
 ]
-# MFMA results in arch VGPRs: the softmax reads S directly instead of copying
-# it out of accumulation registers every tile.  Not for the block GEMM, whose
-# 256 accumulators per lane live in the AGPRs.
+# MFMA results in arch VGPRs: the softmax and the GEMM epilogue read them
+# directly instead of copying them out of accumulation registers.
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]
-AGPR_ACC_SOURCES = {"block.hip"}
 
 
 def _compile(src: str, extra) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    form = [] if os.path.basename(src) in AGPR_ACC_SOURCES else VGPR_FORM
-    cmd = [HIPCC] + CFLAGS + form + list(extra) + ["-c", src, "-o", obj]
+    cmd = [HIPCC] + CFLAGS + VGPR_FORM + list(extra) + ["-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     msgs = "\n".join(l for l in (r.stdout + r.stderr).splitlines()
                      if "packed-fp32-ops" not in l)

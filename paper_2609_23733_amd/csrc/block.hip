@@ -105,23 +105,18 @@ __global__ __launch_bounds__(256) void k_layernorm(const bf16* __restrict__ X,
 // B2: D^T = W X^T for W [F, Kd] (weights as stored, [out, in]) and X [T, Kd]
 // (token rows), bf16 operands, fp32 accumulation: both operands are
 // Kd-contiguous, as the MFMA wants them.  Workgroup tile 256 features x 256
-// tokens, Kd in stages of 64 through two LDS buffers (144-byte rows:
-// conflict-free 16-byte reads).  Output features are the MFMA rows, so lane l
+// tokens, Kd in stages of 64.  Output features are the MFMA rows, so lane l
 // holds token l % 32 of a block and features 8 (r / 4) + 4 (l / 32) + r % 4 in
-// its register r: four consecutive features per store, and the rotary pair
-// (j, j + 16) of a 32-feature half in registers r and r + 8 of one lane.
-// Tiles are ordered with all of a token tile's feature tiles together, and
-// consecutive tiles share an XCD, so an XCD's L2 keeps a token tile for all
-// its feature tiles while the weights stream by.
-// Every output sums its Kd products in the same order (stage by stage, 16 per
-// MFMA) in both kernels below, so they produce identical bits.
+// its register r, and the rotary pair (j, j + 16) of a 32-feature half in
+// registers r and r + 8 of one lane.
 // ------------------------------------------------------------------------
-constexpr int kGM = 256, kGN = 256, kGK = 64, kGRow = 72;
-constexpr int kGemmWG = 256;   // persistent workgroups: one per CU
+constexpr int kGM = 256, kGN = 256, kGK = 64;
+constexpr int kGemmWG = 256;               // persistent workgroups: one per CU
+constexpr uint32_t kGStage = 32768;        // bytes of one operand's stage: 256 rows of 128
+constexpr uint32_t kGLdsX = 2 * kGStage;   // two W stages, then three X stages
 
-// EPI_RESID: ls (acc + bias) + res + res2, either residual may be null;
-// EPI_RESID2: the same with both residuals given.
-enum { EPI_QKV = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_RESID2 = 3 };
+// EPI_SCALE: ls (acc + bias); EPI_RESID2: ls (acc + bias) + res + res2.
+enum { EPI_QKV = 0, EPI_GELU = 1, EPI_SCALE = 2, EPI_RESID2 = 3 };
 
 struct GemmArgs {
     const bf16* W;        // [F, Kd]
@@ -129,444 +124,444 @@ struct GemmArgs {
     const float* bias;    // [F]
     int64_t T;
     int F, Kd;
-    bf16* out;            // GELU, RESID, RESID2: [T, F]
-    const bf16 *res, *res2;   // RESID: residuals [T, F] (either may be null); RESID2: both
-    const float* ls;      // RESID, RESID2: LayerScale [F]
+    bf16* out;            // GELU, SCALE, RESID2: [T, F]
+    const bf16 *res, *res2;   // RESID2: residuals [T, F]
+    const float* ls;      // SCALE, RESID2: LayerScale [F]
     bf16 *q, *k, *v;      // QKV: [T, D] each
     const int32_t* pos;   // QKV: [T, 2] (row, column)
     float log2_base;      // QKV: log2 of the rotary base
 };
 
-// Tile (L) of the grouped order, `group` feature tiles per token tile:
-// features f0.., tokens t0...
-__device__ __forceinline__ void gemm_tile(int L, int ntt, int group, int& f0, int64_t& t0) {
-    const int grp = L / (group * ntt), in = L - grp * group * ntt;
-    const int tt = in / group, ft = grp * group + in % group;
-    f0 = ft * kGM;
-    t0 = (int64_t)tt * kGN;
+// Exchange between the lane halves of a 32x32 block's registers.  In the MFMA
+// layout lane half hh holds features 8 g + 4 hh + (0..3) of group g, two
+// dwords of bf16 each; afterwards, for groups (0, 1) and (2, 3), half hh holds
+// the eight consecutive features 8 (2 p + hh) .. + 7 of pair p, one 16-byte
+// access.  The exchange is its own inverse.
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
 }
 
-// Epilogue of a wave's 128 features x (32 NTB) tokens: lane (n, hh) holds, in
-// acc[fb][tb] register r = 4 gq + i, feature f0 + 128 wm + 32 fb + 8 gq + 4 hh
-// + i of token tl + tok0 + 32 tb + n.  Tokens outside [t0, T) are not stored.
-template <int EPI, int NTB>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4][NTB], int f0,
-                                              int64_t t0, int64_t tl, int wm, int tok0, int n,
-                                              int hh, const float* sbl = nullptr) {
-    float omega[8];   // rotary frequencies of features j = 8 (r / 4) + 4 hh + r % 4, r < 8
-    if (EPI == EPI_QKV) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int j = 8 * (r >> 2) + 4 * hh + (r & 3);
-            omega[r] = exp2f(-(float)j * (1.f / 16.f) * g.log2_base);
-        }
-    }
+// Epilogue of a wave's 128 features f0 + 128 wm .. x 64 tokens t0 + 64 wn ..
+// The outputs pass through 4 KB of LDS that only this wave uses at that time
+// (32 rows of 128 bytes, row r at scratch + 8192 (r / 8) + 128 (r % 8), 16-byte
+// chunks at position chunk ^ (r / 2 % 8)), so that every store writes whole
+// 128-byte lines.  Loads and stores complete in issue order, so a load issued
+// after a store waits for it: bias and LayerScale go to LDS first (1 KB at
+// `vecs`, this wave's too) and the residuals of a block are read before the
+// previous block is stored.
+template <int EPI>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4][2], int f0,
+                                              int64_t t0, int wm, int wn, int lane0,
+                                              uint32_t scratch, uint32_t vecs) {
+    typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+    typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+    typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
+    constexpr bool kScale = EPI == EPI_SCALE || EPI == EPI_RESID2;
+    // (an opaque copy, so that nothing of the epilogue's addresses is kept in
+    // registers over the main loop)
+    int lane = lane0;
+    asm volatile("" : "+v"(lane));
+    const int n = lane & 31, hh = lane >> 5;
+    const int fw = f0 + 128 * wm;
+    const int64_t tw = t0 + 64 * wn;
+    // chunk c of row n, for the writes (c = 4 f2 + 2 p + hh: flips bits 5-6)
+    const uint32_t wr = scratch + 8192u * (n >> 3) + 128u * (n & 7) +
+                        (uint32_t)((hh ^ ((n >> 1) & 7)) << 4);
+    // chunk lane % 8 of row 8 i + lane / 8, for the reads (i: + 8192, flips bit 6)
+    const uint32_t rd = scratch + 128u * (lane >> 3) +
+                        (uint32_t)(((lane & 7) ^ (lane >> 4)) << 4);
     // All of a wave's features lie in one of Q, K, V (f0 is a multiple of
     // 256); Q and K are rotated, the first 32 features of each 64 by the row
     // coordinate and the next 32 by the column coordinate.
-    const bool rotate = EPI == EPI_QKV && (f0 + 128 * wm) / kDm < 2;
-    // The 8-wave kernel (NTB = 2) reads the wave's 64 bias values once, with
-    // one wait, for all its tokens; the persistent kernel, whose registers are
-    // full, reads the tile's bias and LayerScale from LDS (sbl: 256 bias values,
-    // then 256 LayerScale values, for features f0 ...) per 32 x 32 block.
-    constexpr bool kHoist = NTB == 2;
-    float bias[4][16];
-    if constexpr (kHoist) {
-#pragma unroll
-        for (int fb = 0; fb < 4; ++fb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                bias[fb][r] = g.bias[f0 + 128 * wm + 32 * fb + 8 * (r >> 2) + 4 * hh + (r & 3)];
-    }
-    // The wave's output tensor, chosen once with a wave-uniform index (an index
-    // in vector registers made the compiler read the pointer from the
-    // argument block per 32 x 32 block and wait for it before each store).
-    const int which = EPI == EPI_QKV ? __builtin_amdgcn_readfirstlane((f0 + 128 * wm) / kDm) : 0;
+    const int which = EPI == EPI_QKV ? __builtin_amdgcn_readfirstlane(fw / kDm) : 0;
+    const bool rotate = EPI == EPI_QKV && which < 2;
     bf16* const qkv_out = which == 0 ? g.q : (which == 1 ? g.k : g.v);
-    // Rotary positions of all the wave's tokens, read before the first is
-    // used (rows past T - 1 read row T - 1 and are not stored).
-    int2 pos[NTB];
+    bf16* const dst0 = EPI == EPI_QKV ? qkv_out + (fw - which * kDm) : g.out + fw;
+    const int64_t ldo = EPI == EPI_QKV ? kDm : g.F;
+    // Rows of the lane's tokens in the MFMA layout (past T - 1: row T - 1, not stored).
+    int64_t tn[2];
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb)
+        tn[tb] = tw + 32 * tb + n < g.T ? tw + 32 * tb + n : g.T - 1;
+    int2 pos[2];
     if (rotate) {
 #pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) {
-            const int64_t t = tl + tok0 + 32 * tb + n;
-            pos[tb] = *reinterpret_cast<const int2*>(g.pos + 2 * (t < g.T ? t : g.T - 1));
+        for (int tb = 0; tb < 2; ++tb) pos[tb] = *reinterpret_cast<const int2*>(g.pos + 2 * tn[tb]);
+    }
+    // Residuals of a 32 x 32 block in the 16-byte layout of the exchanged registers.
+    u32x4 r1[2][2], r2[2][2];
+    auto load_res = [&](int blk, int set) {
+        const int64_t at = tn[blk >> 2] * ldo + fw + 32 * (blk & 3) + 8 * hh;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            r1[set][p] = *reinterpret_cast<const u32x4*>(g.res + at + 16 * p);
+            r2[set][p] = *reinterpret_cast<const u32x4*>(g.res2 + at + 16 * p);
         }
+    };
+    {
+        const f32x2 bv = *reinterpret_cast<const f32x2*>(g.bias + fw + 2 * lane);
+        f32x2 lv = {0.f, 0.f};
+        if constexpr (kScale) lv = *reinterpret_cast<const f32x2*>(g.ls + fw + 2 * lane);
+        if constexpr (EPI == EPI_RESID2) load_res(0, 0);
+        *(lds_f32x2*)(uintptr_t)(vecs + 8u * lane) = bv;
+        if constexpr (kScale) *(lds_f32x2*)(uintptr_t)(vecs + 512u + 8u * lane) = lv;
+    }
+    float omega[8];   // rotary frequencies of features j = 8 (r / 4) + 4 hh + r % 4, r < 8
+    if (rotate) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            omega[r] = exp2f(-(float)(8 * (r >> 2) + 4 * hh + (r & 3)) * (1.f / 16.f) * g.log2_base);
     }
 #pragma unroll
-    for (int tb = 0; tb < NTB; ++tb) {
-        const int64_t t = tl + tok0 + 32 * tb + n;
-        if (t < t0 || t >= g.T) continue;
-        // An offset the compiler cannot see through, so the LDS reads of
-        // bias and LayerScale stay in each block instead of being hoisted out
-        // of the token loop (128 values per lane held across it spill).
-        int lo = -f0;
-        if (sbl) asm volatile("" : "+v"(lo));
-        // (sin, cos) of this token's angles, once per token: half 0 takes the
-        // row coordinate, half 1 the column coordinate
+    for (int tb = 0; tb < 2; ++tb) {
+        // (sin, cos) of the token's angles: half 0 takes the row coordinate,
+        // half 1 the column coordinate.
         float rs[2][8], rc[2][8];
         if (rotate) {
-            const int2 p = pos[tb];
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
-                __sincosf((float)p.x * omega[r], &rs[0][r], &rc[0][r]);
-                __sincosf((float)p.y * omega[r], &rs[1][r], &rc[1][r]);
+                __sincosf((float)pos[tb].x * omega[r], &rs[0][r], &rc[0][r]);
+                __sincosf((float)pos[tb].y * omega[r], &rs[1][r], &rc[1][r]);
             }
         }
 #pragma unroll
-        for (int fb = 0; fb < 4; ++fb) {
-            const int fbase = f0 + 128 * wm + 32 * fb;
-            float v[16];
+        for (int fp = 0; fp < 2; ++fp) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                v[r] = acc[fb][tb][r] +
-                       (kHoist ? bias[fb][r]
-                               : sbl ? sbl[fbase + lo + 8 * (r >> 2) + 4 * hh + (r & 3)]
-                                     : g.bias[fbase + 8 * (r >> 2) + 4 * hh + (r & 3)]);
-            bf16* dst;
-            if (EPI == EPI_QKV) {
-                const int fin = fbase - which * kDm;
-                if (rotate) {   // Q, K: rotate the planes (j, j + 16) of this half
-                    const int half = (fin & 32) ? 1 : 0;   // fb & 1
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        const float sn = rs[half][r], cs = rc[half][r];
-                        const float u = v[r], w = v[r + 8];
-                        v[r] = u * cs - w * sn;
-                        v[r + 8] = u * sn + w * cs;
-                    }
+            for (int f2 = 0; f2 < 2; ++f2) {
+                const int fb = 2 * fp + f2, blk = 4 * tb + fb;
+                if constexpr (EPI == EPI_RESID2) {
+                    if (blk + 1 < 8) load_res(blk + 1, (blk + 1) & 1);
                 }
-                dst = qkv_out + t * kDm + fin;
-            } else {
-                dst = g.out + t * g.F + fbase;
-                if (EPI == EPI_GELU) {
+                float v[16];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 bias = *(const lds_f32x4*)(uintptr_t)(vecs + 4u * (32 * fb + 8 * q + 4 * hh));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[4 * q + i] = acc[fb][tb][4 * q + i] + bias[i];
+                }
+                if (EPI == EPI_QKV) {
+                    if (rotate) {   // the planes (j, j + 16) of this half
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) {
+                            const float sn = rs[f2][r], cs = rc[f2][r];
+                            const float u = v[r], w = v[r + 8];
+                            v[r] = u * cs - w * sn;
+                            v[r + 8] = u * sn + w * cs;
+                        }
+                    }
+                } else if (EPI == EPI_GELU) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) v[r] = gelu(v[r]);
-                } else if (EPI == EPI_RESID2) {   // ls (acc + bias) + res + res2, in fp32
-                    // Both residuals are read with no branch around the loads,
-                    // so the reads of the four feature groups are in flight
-                    // together (a null test per read waits for each one).
+                } else {
                     float base[16];
+                    if constexpr (EPI == EPI_RESID2) {
 #pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        const int f = fbase + 8 * gq + 4 * hh;
-                        const bf16x4 r1 = *reinterpret_cast<const bf16x4*>(g.res + t * g.F + f);
-                        const bf16x4 r2 = *reinterpret_cast<const bf16x4*>(g.res2 + t * g.F + f);
+                        for (int p = 0; p < 2; ++p)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) base[4 * gq + i] = (float)r1[i] + (float)r2[i];
+                            for (int k = 0; k < 2; ++k) {
+                                uint32_t a1 = r1[blk & 1][p][k], b1 = r1[blk & 1][p][2 + k];
+                                uint32_t a2 = r2[blk & 1][p][k], b2 = r2[blk & 1][p][2 + k];
+                                swap_halves(a1, b1);
+                                swap_halves(a2, b2);
+                                const bf16x2 x1 = __builtin_bit_cast(bf16x2, a1);
+                                const bf16x2 y1 = __builtin_bit_cast(bf16x2, b1);
+                                const bf16x2 x2 = __builtin_bit_cast(bf16x2, a2);
+                                const bf16x2 y2 = __builtin_bit_cast(bf16x2, b2);
+#pragma unroll
+                                for (int i = 0; i < 2; ++i) {
+                                    base[8 * p + 2 * k + i] = (float)x1[i] + (float)x2[i];
+                                    base[8 * p + 4 + 2 * k + i] = (float)y1[i] + (float)y2[i];
+                                }
+                            }
                     }
 #pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        const int f = fbase + 8 * gq + 4 * hh;
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 ls = *(const lds_f32x4*)(uintptr_t)(vecs + 512u + 4u * (32 * fb + 8 * q + 4 * hh));
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            v[4 * gq + i] = fmaf(sbl ? sbl[kGM + f + lo + i] : g.ls[f + i],
-                                                 v[4 * gq + i], base[4 * gq + i]);
-                    }
-                } else {   // ls (acc + bias) + res + res2, summed in fp32
-#pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        const int f = fbase + 8 * gq + 4 * hh;
-                        float base[4] = {0.f, 0.f, 0.f, 0.f};
-                        if (g.res) {
-                            const bf16x4 rs = *reinterpret_cast<const bf16x4*>(g.res + t * g.F + f);
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) base[i] = (float)rs[i];
+                        for (int i = 0; i < 4; ++i) {
+                            const int r = 4 * q + i;
+                            v[r] = EPI == EPI_RESID2 ? fmaf(ls[i], v[r], base[r]) : ls[i] * v[r];
                         }
-                        if (g.res2) {
-                            const bf16x4 rs = *reinterpret_cast<const bf16x4*>(g.res2 + t * g.F + f);
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) base[i] += (float)rs[i];
-                        }
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            v[4 * gq + i] = fmaf(sbl ? sbl[kGM + f + lo + i] : g.ls[f + i],
-                                                 v[4 * gq + i], base[i]);
                     }
                 }
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    u32x4 o;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const int ra = 8 * p + 2 * k;
+                        const bf16x2 x = {(bf16)v[ra], (bf16)v[ra + 1]};
+                        const bf16x2 y = {(bf16)v[ra + 4], (bf16)v[ra + 5]};
+                        uint32_t a = __builtin_bit_cast(uint32_t, x);
+                        uint32_t b = __builtin_bit_cast(uint32_t, y);
+                        swap_halves(a, b);
+                        o[k] = a;
+                        o[2 + k] = b;
+                    }
+                    *(lds_u32x4*)(uintptr_t)(wr ^ (uint32_t)((4 * f2 + 2 * p) << 4)) = o;
+                }
             }
+            // (one wave's LDS operations execute in order: no wait between the
+            // writes and these reads, nor before the next block's writes)
+            u32x4 o[4];
 #pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                bf16x4 o;
+            for (int i = 0; i < 4; ++i)
+                o[i] = *(const lds_u32x4*)(uintptr_t)((rd ^ (uint32_t)((i & 1) << 6)) + 8192u * i);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = (bf16)v[4 * gq + i];
-                *reinterpret_cast<bf16x4*>(dst + 8 * gq + 4 * hh) = o;
+            for (int i = 0; i < 4; ++i) {
+                const int64_t t = tw + 32 * tb + 8 * i + (lane >> 3);
+                if (t < g.T)
+                    *reinterpret_cast<u32x4*>(dst0 + t * ldo + 64 * fp + 8 * (lane & 7)) = o[i];
             }
         }
     }
 }
 
-// B2a (W_O and FFN 2 projections, T >= 256): persistent, one workgroup of 4
-// waves per CU, each wave a 128 x 128 block of the tile with its 256
-// accumulators in AGPRs.  Workgroup b
-// takes tiles i G + slot(b), slot grouping the workgroups of an XCD, so the 32
-// tiles an XCD runs at once are 8 token tiles x 4 feature tiles.  A partial
-// last token tile reads rows T - 256 .. T - 1 (every read in bounds) and
-// stores only its own tokens.
-// Pipeline: stage s + 2 is loaded into registers while stage s is multiplied
-// (two register sets, so two stages are in flight), stage s + 1 goes to LDS
-// during the last k-step of stage s, and the next tile's first stages are in
-// flight during a tile's epilogue.  Per stage a wave issues 64 MFMAs
-// (4 k-steps x 16), 32 LDS fragment reads (each k-step reads the next one's),
-// 16 global loads and 16 LDS stores, interleaved one for one with the MFMAs
-// by scheduling barriers; the one barrier per stage sits between the two
-// halves of the last k-step, whose second half covers the first reads of the
-// next stage.
+// 64 lanes x 16 bytes from base + voff (per lane) to 1 KB of LDS at byte `lds`
+// (uniform).  The copy is counted in vmcnt by issue order; callers wait for it
+// with explicit counts.
+__device__ __forceinline__ void copy_to_lds(uint32_t lds, const char* base, uint32_t voff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds), "v"(voff), "s"(base)
+                 : "memory");
+}
+
+// Persistent, one workgroup of 8 waves per CU (two per SIMD), each wave a block of 128
+// features x 64 tokens.  Waves 0-3 (features 0-127) and 4-7 (features 128-255)
+// alternate, one phase apart, with one barrier per phase: while one group
+// issues a stage's 32 MFMAs per wave, the other reads its next stage's 24
+// fragments from LDS into registers.
+//   phase 2 s:     group 0 reads stage s,      group 1 multiplies stage s - 1
+//   phase 2 s + 1: group 0 multiplies stage s, group 1 reads stage s
+// Stages are copied straight from global memory to LDS (no registers), 128-byte
+// rows whose 16-byte chunks are stored at position chunk ^ (row / 2 % 8), so that
+// the fragment reads of sixteen consecutive rows hit all 64 banks once.  Group 0's
+// half of a W stage is dead after phase 2 s, the other half and the X stage after phase
+// 2 s + 1; with two W and three X buffers the copies are issued
+//   phase 2 s:     W half 1 of stage s + 1, X of stage s + 2
+//   phase 2 s + 1: W half 0 of stage s + 2
+// i.e. three to four phases before they are read, and the waits (12 and 8 copies
+// still in flight, by issue order) never drain them.  The copies run ahead over
+// tile boundaries; past the last stage they repeat the last tile's.  Token rows
+// past T - 1 read row T - 1 and are not stored.  Both groups run their epilogue
+// in the same phase.  The multiplying group runs at raised priority (2-3 %).
+//
+// What bounds it: matrix issue and power together.  At 137,400 tokens the four
+// projections take 0.28 (W_O), 0.80 (QKV), 1.11 (FFN 1) and 1.05 ms (FFN 2), 1.0-1.1 PF/s
+// over the last three (0.39, 1.14, 1.52 and 1.27 ms for the register-staged kernels
+// before it); the matrix pipe is busy 49-54 % of the cycles at 1.6-1.75 GHz, and what
+// takes idle cycles out lowers the clock.  Without any copies the FFN kernels
+// took 12-14 % fewer cycles, without the epilogue 15-25 %.
 template <int EPI>
-__global__ __launch_bounds__(256, 1) void k_gemm(GemmArgs g) {
-    // Make the AGPRs available to the register allocator (accumulators).
-    asm volatile("" ::: "a0");
+__global__ __launch_bounds__(512, 1) void k_gemm(GemmArgs g) {
     const int nft = g.F / kGM;
     const int ntt = (int)((g.T + kGN - 1) / kGN);
     const int total = nft * ntt;
     const int nk = g.Kd / kGK;
-    const int G = gridDim.x, b = blockIdx.x;
-    const int slot = (G & 7) == 0 ? (b & 7) * (G >> 3) + (b >> 3) : b;
+    const int G = gridDim.x;
+    const int slot = xcd_remap(blockIdx.x, G);
     const int ntile = slot < total ? (total - 1 - slot) / G + 1 : 0;
     if (ntile == 0) return;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 31, hh = lane >> 5;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int grp = wave >> 2, wn = wave & 3;
 
-    __shared__ __attribute__((aligned(16))) bf16 sW[2][kGM * kGRow];
-    __shared__ __attribute__((aligned(16))) bf16 sX[2][kGN * kGRow];
-    __shared__ __attribute__((aligned(16))) float sBL[2 * kGM];   // the tile's bias, LayerScale
+    __shared__ __attribute__((aligned(1024))) char smem[5 * kGStage];
+    typedef __attribute__((address_space(3))) char lds_char;
+    typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
 
-    // All of a token tile's feature tiles in one group (with FFN 1 on this
-    // kernel, 16 feature tiles, so that an XCD's 32 tiles were 2 token tiles
-    // x 16 feature tiles, were 3 % faster than groups of 4; 2.6 % on QKV in
-    // B2b).
-    auto tile_of = [&](int i, int& f0, int64_t& t0, int64_t& tl) {
-        gemm_tile(i * G + slot, ntt, nft, f0, t0);
-        tl = t0 + kGN <= g.T ? t0 : g.T - kGN;
+    // Groups of `gft` feature tiles per token tile, consecutive tiles on one
+    // XCD, whose L2 serves a token tile to all its feature tiles at once.  All
+    // feature tiles in one group, but FFN 1's 16 in two of 8: an XCD's 32
+    // tiles then are 4 x 8 instead of 2 x 16 (token x feature) tiles, 6 instead
+    // of 9 MB (output stage at 137,400 tokens 2712 -> 2682 us; QKV's 12 in
+    // groups of 4 or 6 were 1 % slower than in one).
+    const int gft = nft % 8 == 0 ? 8 : nft;
+    auto tile_of = [&](int i, int& f0, int64_t& t0) {
+        const int L = i * G + slot;
+        const int gi = L / (gft * ntt), in = L - gi * gft * ntt;
+        f0 = (gi * gft + in % gft) * kGM;
+        t0 = (int64_t)(in / gft) * kGN;
     };
 
-    // Load state: the next stage to load (tile li, stage lkt).  Past the last
-    // stage the bases keep pointing at a valid stage; those loads go unused.
-    int li = 0, lkt = 0, lf0;
-    int64_t lt0, ltl;
-    tile_of(0, lf0, lt0, ltl);
-    const char* wb;
-    const char* xb;
-    auto next_bases = [&]() {
-        wb = reinterpret_cast<const char*>(g.W + (int64_t)lf0 * g.Kd + lkt * kGK);
-        xb = reinterpret_cast<const char*>(g.X + ltl * g.Kd + lkt * kGK);
-        if (++lkt == nk) {
-            lkt = 0;
-            if (++li < ntile) tile_of(li, lf0, lt0, ltl);
+    // Copies: wave w, instruction i moves rows 64 i + 8 w + lane / 8, lane
+    // l's 16 bytes are chunk (l % 8) ^ (row / 2 % 8) of the row's 128.
+    const uint32_t rstride = (uint32_t)g.Kd * 2u;
+    const int crow = 8 * wave + (lane >> 3);
+    const uint32_t ccol = (uint32_t)((lane & 7) ^ ((crow >> 1) & 7)) * 16u;
+    const uint32_t woff = (uint32_t)crow * rstride + ccol;
+    uint32_t xoff[4];
+    const char *wb, *xb;              // stage being copied, of W and of X
+    int wi = 0, wkt = -1, xi = 0, xkt = -1;
+    uint32_t wbuf = kGStage, xbuf = 2 * kGStage;   // its LDS buffer (byte offset)
+    int tf0;
+    int64_t tt0;
+    auto x_tile = [&](int i) {
+        tile_of(i, tf0, tt0);
+        xb = reinterpret_cast<const char*>(g.X + tt0 * g.Kd);
+        const int last = (int)(g.T - 1 - tt0 < kGN - 1 ? g.T - 1 - tt0 : kGN - 1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            xoff[j] = (uint32_t)min(64 * j + crow, last) * rstride + ccol;
+    };
+    auto next_w = [&]() {
+        wbuf ^= kGStage;
+        wb += kGK * 2;
+        if (++wkt == nk) {
+            wkt = 0;
+            if (wi + 1 < ntile) ++wi;
+            tile_of(wi, tf0, tt0);
+            wb = reinterpret_cast<const char*>(g.W + (int64_t)tf0 * g.Kd);
         }
     };
-    // Thread tid moves row (tid / 8) + 32 j, bytes 16 (tid % 8) of the
-    // stage's 128, j = 0..7, of both operands.
-    const uint32_t voff = (uint32_t)(tid >> 3) * (uint32_t)g.Kd * 2u + (uint32_t)(tid & 7) * 16u;
-    const int64_t jstride = (int64_t)32 * g.Kd * 2;
-    auto gload = [&](int h, u32x4 (&rw)[8], u32x4 (&rx)[8]) {
-#pragma unroll
-        for (int j = 4 * h; j < 4 * h + 4; ++j) {
-            rw[j] = *reinterpret_cast<const u32x4*>(wb + j * jstride + voff);
-            rx[j] = *reinterpret_cast<const u32x4*>(xb + j * jstride + voff);
+    auto next_x = [&]() {
+        xbuf = xbuf == 2 * kGStage ? 0 : xbuf + kGStage;
+        xb += kGK * 2;
+        if (++xkt == nk) {
+            xkt = 0;
+            if (xi + 1 < ntile) ++xi;
+            x_tile(xi);
         }
     };
-    const int lsoff = (tid >> 3) * kGRow + (tid & 7) * 8;
-    auto lstore = [&](int buf, u32x4 (&rw)[8], u32x4 (&rx)[8]) {
+    auto copy_w = [&](int half) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            *reinterpret_cast<u32x4*>(&sW[buf][lsoff + 32 * j * kGRow]) = rw[j];
-            *reinterpret_cast<u32x4*>(&sX[buf][lsoff + 32 * j * kGRow]) = rx[j];
-        }
+        for (int j = 2 * half; j < 2 * half + 2; ++j)
+            copy_to_lds(lds0 + wbuf + (64 * j + 8 * wave) * 128, wb + (int64_t)(64 * j) * rstride,
+                        woff);
     };
-    const int aoff = (128 * wm + n) * kGRow + 8 * hh, xoff = (128 * wn + n) * kGRow + 8 * hh;
-    auto lread = [&](int buf, int ks, bf16x8 (&a)[4], bf16x8 (&x)[4]) {
+    auto copy_x = [&]() {
 #pragma unroll
-        for (int fb = 0; fb < 4; ++fb)
-            a[fb] = *reinterpret_cast<const bf16x8*>(&sW[buf][aoff + 32 * fb * kGRow + 16 * ks]);
-#pragma unroll
-        for (int tb = 0; tb < 4; ++tb)
-            x[tb] = *reinterpret_cast<const bf16x8*>(&sX[buf][xoff + 32 * tb * kGRow + 16 * ks]);
+        for (int j = 0; j < 4; ++j)
+            copy_to_lds(lds0 + kGLdsX + xbuf + (64 * j + 8 * wave) * 128, xb, xoff[j]);
+    };
+    auto issue_even = [&]() { copy_w(1); next_x(); copy_x(); };
+    auto issue_odd = [&]() { next_w(); copy_w(0); };
+    auto wait_even = [&]() { asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); };
+    auto wait_odd = [&]() { asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); };
+    auto barrier = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
     };
 
-    f32x16 acc[4][4];
-#pragma unroll
-    for (int fb = 0; fb < 4; ++fb)
-#pragma unroll
-        for (int tb = 0; tb < 4; ++tb) acc[fb][tb] = zero_f32x16();
-
-    u32x4 ra[8], xa[8], rb[8], xb8[8];   // the two register sets
-    next_bases();
-    gload(0, ra, xa);
-    gload(1, ra, xa);
-    next_bases();
-    gload(0, rb, xb8);
-    gload(1, rb, xb8);
-    lstore(0, ra, xa);
-    __syncthreads();
-    bf16x8 fa0[4], fx0[4], fa1[4], fx1[4];
-    lread(0, 0, fa0, fx0);
-    int buf = 0;
-
-#define VP_SGB(mask, cnt) __builtin_amdgcn_sched_group_barrier(mask, cnt, 0)
-#define VP_MMA(A, X, FB0, FB1)                                                          \
-    _Pragma("unroll") for (int fb = FB0; fb < FB1; ++fb)                               \
-        _Pragma("unroll") for (int tb = 0; tb < 4; ++tb) acc[fb][tb] =                  \
-            mfma_bf16(A[fb], X[tb], acc[fb][tb]);
-    // One stage: load the stage after next into (LW, LX), store the next
-    // stage from (SW, SX).  Masks: 0x008 MFMA, 0x020 global load, 0x100 LDS
-    // read, 0x200 LDS write.
-#define VP_STAGE(LW, LX, SW, SX)                                                        \
-    {                                                                                   \
-        next_bases();                                                                   \
-        lread(buf, 1, fa1, fx1);                                                        \
-        gload(0, LW, LX);                                                               \
-        VP_MMA(fa0, fx0, 0, 4);                                                         \
-        for (int q = 0; q < 8; ++q) { VP_SGB(0x008, 1); VP_SGB(0x100, 1); VP_SGB(0x020, 1); } \
-        VP_SGB(0x008, 8);                                                               \
-        lread(buf, 2, fa0, fx0);                                                        \
-        gload(1, LW, LX);                                                               \
-        VP_MMA(fa1, fx1, 0, 4);                                                         \
-        for (int q = 0; q < 8; ++q) { VP_SGB(0x008, 1); VP_SGB(0x100, 1); VP_SGB(0x020, 1); } \
-        VP_SGB(0x008, 8);                                                               \
-        lread(buf, 3, fa1, fx1);                                                        \
-        VP_MMA(fa0, fx0, 0, 4);                                                         \
-        for (int q = 0; q < 8; ++q) { VP_SGB(0x008, 1); VP_SGB(0x100, 1); }             \
-        VP_SGB(0x008, 8);                                                               \
-        VP_MMA(fa1, fx1, 0, 2);                                                         \
-        lstore(buf ^ 1, SW, SX);                                                        \
-        for (int q = 0; q < 8; ++q) { VP_SGB(0x008, 1); VP_SGB(0x200, 2); }             \
-        __syncthreads();                                                                \
-        lread(buf ^ 1, 0, fa0, fx0);                                                    \
-        VP_MMA(fa1, fx1, 2, 4);                                                         \
-        for (int q = 0; q < 8; ++q) { VP_SGB(0x008, 1); VP_SGB(0x100, 1); }             \
-        buf ^= 1;                                                                       \
+    // Prologue: X(0), W(0) half 0, then what phases -2 and -1 would issue.
+    tile_of(0, tf0, tt0);
+    wb = reinterpret_cast<const char*>(g.W + (int64_t)tf0 * g.Kd) - kGK * 2;
+    x_tile(0);
+    xb -= kGK * 2;
+    next_x();
+    copy_x();
+    issue_odd();
+    issue_even();
+    issue_odd();
+    wait_odd();
+    barrier();
+    if (grp) {   // phase 0 of group 1
+        issue_even();
+        wait_even();
+        barrier();
     }
-    for (int i = 0; i < ntile; ++i) {
-        for (int kt = 0; kt < nk; kt += 2) {   // nk is even
-            VP_STAGE(ra, xa, rb, xb8);
-            VP_STAGE(rb, xb8, ra, xa);
-        }
-        int f0;
-        int64_t t0, tl;
-        tile_of(i, f0, t0, tl);
-        // The tile's bias and LayerScale through LDS: one read and one wait per
-        // thread, then one barrier, instead of a read and a wait per 32 x 32
-        // block.  The previous tile's epilogue finished reading sBL before the
-        // barriers of this tile's stages.
-        sBL[tid] = g.bias[f0 + tid];
-        sBL[kGM + tid] = g.ls[f0 + tid];
-        __syncthreads();
-        gemm_epilogue<EPI, 4>(g, acc, f0, t0, tl, wm, 128 * wn, n, hh, sBL);
-#pragma unroll
-        for (int fb = 0; fb < 4; ++fb)
-#pragma unroll
-            for (int tb = 0; tb < 4; ++tb) acc[fb][tb] = zero_f32x16();
-    }
-#undef VP_STAGE
-#undef VP_MMA
-#undef VP_SGB
-}
-
-// B2b: one workgroup per tile, 8 waves of 128 x 64 (two per SIMD), the stage
-// copy through registers one stage ahead, token rows past T reading row T - 1
-// (their outputs are never stored).  Used for the QKV projection, whose
-// rotary epilogue (16 sincos per token) the second wave on each SIMD helps
-// to hide (3-8 % faster than B2a at S = 100), for FFN 1, whose GELU epilogue
-// it hides likewise (output stage 1 % faster), and for T < 256.
-template <int EPI>
-__global__ __launch_bounds__(512, 1) void k_gemm_w8(GemmArgs g) {
-    const int nft = g.F / kGM;
-    const int ntt = (int)((g.T + kGN - 1) / kGN);
-    const int total = nft * ntt;
-    int f0;
-    int64_t t0;
-    gemm_tile(xcd_remap(blockIdx.x, total), ntt, nft, f0, t0);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int n = lane & 31, hh = lane >> 5;
-    const int wm = wave >> 2, wn = wave & 3;
-
-    __shared__ __attribute__((aligned(16))) bf16 sW[2][kGM * kGRow];
-    __shared__ __attribute__((aligned(16))) bf16 sX[2][kGN * kGRow];
-
-    // Stage copy: 4 chunks of 16 bytes of W and 4 of X per thread; chunk
-    // c = tid + 512 i is row c / 8, bytes 16 (c % 8) of the stage's 128.
-    u32x4 rw[4], rx[4];
-    auto gload = [&](int kt) {
-        const int k0 = kt * kGK;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = tid + 512 * i, row = c >> 3, seg = (c & 7) * 8;
-            rw[i] = *reinterpret_cast<const u32x4*>(g.W + (int64_t)(f0 + row) * g.Kd + k0 + seg);
-            const int64_t tr = t0 + row < g.T ? t0 + row : g.T - 1;
-            rx[i] = *reinterpret_cast<const u32x4*>(g.X + tr * g.Kd + k0 + seg);
-        }
-    };
-    auto lstore = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = tid + 512 * i, row = c >> 3, seg = (c & 7) * 8;
-            *reinterpret_cast<u32x4*>(&sW[buf][row * kGRow + seg]) = rw[i];
-            *reinterpret_cast<u32x4*>(&sX[buf][row * kGRow + seg]) = rx[i];
-        }
-    };
 
     f32x16 acc[4][2];
+    // Fragment addresses of k-step 0 (buffer 0); k-step ks flips bits 5-6.
+    const uint32_t a0 = lds0 + (uint32_t)(128 * grp + n) * 128u + (uint32_t)((hh ^ ((n >> 1) & 7)) << 4);
+    const uint32_t x0 = lds0 + kGLdsX + (uint32_t)(64 * wn + n) * 128u +
+                        (uint32_t)((hh ^ ((n >> 1) & 7)) << 4);
+    uint32_t arb = 0, xrb = 0;
+    for (int i = 0; i < ntile; ++i) {
+        for (int kt = 0; kt < nk; ++kt) {
+            bf16x8 a[4][4], x[4][2];
 #pragma unroll
-    for (int fb = 0; fb < 4; ++fb) acc[fb][0] = acc[fb][1] = zero_f32x16();
-
-    gload(0);
-    lstore(0);
-    __syncthreads();
-    const int nk = g.Kd / kGK;
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) gload(kt + 1);
+            for (int ks = 0; ks < 4; ++ks) {
+                const uint32_t ap = (a0 + arb) ^ (uint32_t)(ks << 5);
+                const uint32_t xp = (x0 + xrb) ^ (uint32_t)(ks << 5);
 #pragma unroll
-        for (int ks = 0; ks < kGK / 16; ++ks) {
-            bf16x8 a[4], x[2];
+                for (int fb = 0; fb < 4; ++fb) a[ks][fb] = *(lds_frag*)(uintptr_t)(ap + 4096u * fb);
 #pragma unroll
-            for (int fb = 0; fb < 4; ++fb)
-                a[fb] = *reinterpret_cast<const bf16x8*>(
-                    &sW[buf][(128 * wm + 32 * fb + n) * kGRow + 16 * ks + 8 * hh]);
+                for (int tb = 0; tb < 2; ++tb) x[ks][tb] = *(lds_frag*)(uintptr_t)(xp + 4096u * tb);
+            }
+            arb ^= kGStage;
+            xrb = xrb == 2 * kGStage ? 0 : xrb + kGStage;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (grp)
+                issue_odd();
+            else
+                issue_even();
+            if (grp)
+                wait_odd();
+            else
+                wait_even();
+            barrier();
+            __builtin_amdgcn_s_setprio(1);
+            // The phase's copies go behind the first MFMAs, which keep the
+            // matrix pipe busy meanwhile.
+            if (kt == 0) {
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-                x[tb] = *reinterpret_cast<const bf16x8*>(
-                    &sX[buf][(64 * wn + 32 * tb + n) * kGRow + 16 * ks + 8 * hh]);
+                for (int fb = 0; fb < 4; ++fb)
 #pragma unroll
-            for (int fb = 0; fb < 4; ++fb)
+                    for (int tb = 0; tb < 2; ++tb)
+                        acc[fb][tb] = mfma_bf16(a[0][fb], x[0][tb], zero_f32x16());
+            } else {
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb) acc[fb][tb] = mfma_bf16(a[fb], x[tb], acc[fb][tb]);
+                for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+                    for (int tb = 0; tb < 2; ++tb)
+                        acc[fb][tb] = mfma_bf16(a[0][fb], x[0][tb], acc[fb][tb]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (grp == 0)
+                issue_odd();
+            else if (kt + 1 < nk)
+                issue_even();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 1; ks < 4; ++ks)
+#pragma unroll
+                for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+                    for (int tb = 0; tb < 2; ++tb)
+                        acc[fb][tb] = mfma_bf16(a[ks][fb], x[ks][tb], acc[fb][tb]);
+            __builtin_amdgcn_s_setprio(0);
+            if (grp == 0) {
+                wait_odd();
+                barrier();
+            } else if (kt + 1 < nk) {
+                wait_even();
+                barrier();
+            }
         }
-        if (kt + 1 < nk) lstore(buf ^ 1);
-        __syncthreads();
+        int f0;
+        int64_t t0;
+        tile_of(i, f0, t0);
+        // The wave's scratch is those parts of the next X stage's and of the
+        // next W half's buffer that its own copies fill, which it issues only
+        // afterwards.
+        const uint32_t xnext = xbuf == 2 * kGStage ? 0 : xbuf + kGStage;
+        gemm_epilogue<EPI>(g, acc, f0, t0, grp, wn, lane, lds0 + kGLdsX + xnext + 1024u * wave,
+                           lds0 + wbuf + kGStage / 2 + 1024u * wave);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (grp) {
+            issue_even();
+            wait_even();
+            barrier();
+        }
     }
-    gemm_epilogue<EPI, 2>(g, acc, f0, t0, t0, wm, 64 * wn, n, hh);
+    if (grp == 0) barrier();
+    // (no copy may land after the workgroup's LDS is given back)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // ------------------------------------------------------------------ launchers
 
+// F a multiple of 256, Kd of 64 and at least 128.
 template <int EPI>
-static void gemm_launch(const GemmArgs& a, hipStream_t st) {
+static void gemm(const GemmArgs& a, hipStream_t st) {
     const int total = (a.F / kGM) * (int)((a.T + kGN - 1) / kGN);
-    if constexpr (EPI == EPI_RESID || EPI == EPI_RESID2) {
-        if (a.T >= kGN) {
-            hipLaunchKernelGGL(k_gemm<EPI>, dim3(total < kGemmWG ? total : kGemmWG), dim3(256), 0,
-                               st, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL(k_gemm_w8<EPI>, dim3(total), dim3(512), 0, st, a);
-}
-
-// F a multiple of 256, Kd of 128 (the persistent kernel takes stages in
-// pairs); the block's shapes are 1024 x
-// {3, 1, 4} by 1024 and 1024 by 4096.
-static void gemm(int epi, const GemmArgs& a, hipStream_t st) {
-    if (epi == EPI_QKV)
-        gemm_launch<EPI_QKV>(a, st);
-    else if (epi == EPI_GELU)
-        gemm_launch<EPI_GELU>(a, st);
-    else if (epi == EPI_RESID2 && a.res && a.res2)
-        gemm_launch<EPI_RESID2>(a, st);
-    else
-        gemm_launch<EPI_RESID>(a, st);
+    hipLaunchKernelGGL(k_gemm<EPI>, dim3(total < kGemmWG ? total : kGemmWG), dim3(512), 0, st, a);
 }
 
 static void layernorm(const bf16* X, const bf16* X2, int64_t T, const float* g, const float* b,
@@ -583,7 +578,7 @@ void launch_block_qkv(const BlockArgs& a, hipStream_t st) {
     GemmArgs g = {};
     g.W = a.w_qkv; g.X = a.ln; g.bias = a.b_qkv; g.T = a.T; g.F = 3 * kDm; g.Kd = kDm;
     g.q = a.Q; g.k = a.K; g.v = a.V; g.pos = a.pos; g.log2_base = log2f(a.rope_base);
-    gemm(EPI_QKV, g, st);
+    gemm<EPI_QKV>(g, st);
 }
 
 void launch_block_out(const BlockArgs& a, hipStream_t st) {
@@ -591,16 +586,16 @@ void launch_block_out(const BlockArgs& a, hipStream_t st) {
     g.T = a.T;
     // A = LS_1 (Y W_O^T + b_O), the attention update (X_attn = X + A)
     g.W = a.w_o; g.X = a.Y; g.bias = a.b_o; g.F = kDm; g.Kd = kDm;
-    g.res = nullptr; g.res2 = nullptr; g.ls = a.ls1; g.out = a.xa;
-    gemm(EPI_RESID, g, st);
+    g.ls = a.ls1; g.out = a.xa;
+    gemm<EPI_SCALE>(g, st);
     layernorm(a.X, a.xa, a.T, a.ln2_w, a.ln2_b, a.eps, a.ln, st);
     // H = GELU(LN_2(X + A) W_fc1^T + b_fc1)
     g.W = a.w_fc1; g.X = a.ln; g.bias = a.b_fc1; g.F = 4 * kDm; g.Kd = kDm; g.out = a.hid;
-    gemm(EPI_GELU, g, st);
+    gemm<EPI_GELU>(g, st);
     // X_out = X + A + LS_2 (H W_fc2^T + b_fc2)
     g.W = a.w_fc2; g.X = a.hid; g.bias = a.b_fc2; g.F = kDm; g.Kd = 4 * kDm;
     g.res = a.X; g.res2 = a.xa; g.ls = a.ls2; g.out = a.Xout;
-    gemm(EPI_RESID2, g, st);
+    gemm<EPI_RESID2>(g, st);
 }
 
 }  // namespace vp

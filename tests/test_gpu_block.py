@@ -118,6 +118,33 @@ def test_block_full_size_sampled():
     check_update(out[rt], Xr, ref, "S=100 out")
 
 
+@pytest.mark.parametrize("N", [5376, 5377, 5632])
+def test_block_more_tiles_than_workgroups(N):
+    """21 and 22 token tiles of 256: QKV has 252 (one round of the 256
+    persistent workgroups) or 264 feature x token tiles (a second round), the
+    last token tile whole or one token; rows on both sides of tile edges."""
+    from paper_2609_23733_amd import vp
+    log("block tiles N=%d" % N)
+    wt = synth.make_block_weights((26, N))
+    wd = {k: v.cuda() for k, v in wt.items()}
+    X = synth.make_block_input(1, N, key=(26, N))
+    pos = synth.token_positions(1, N)
+    Y = synth.stored(synth.normal((N, D), synth.derive_seed(26, N, 99), 0.1), "bf16")
+    ws = torch.empty(vp.block_workspace_bytes(1, N), dtype=torch.uint8, device="cuda")
+    Q, K, V = vp.block_qkv(X.cuda(), torch.from_numpy(pos).cuda(), wd, 1, N, ws)
+    out = vp.block_out(X.cuda(), Y.cuda(), wd, 1, N, ws)
+    torch.cuda.synchronize()
+    edges = np.arange(0, N, 512)
+    rows = np.unique(np.concatenate([edges, edges[1:] - 1, edges + 31, edges + 32, [N - 2, N - 1]]))
+    rows = rows[rows < N].astype(np.int64)
+    rt = torch.from_numpy(rows)
+    rq, rk, rv = oracle.block_qkv(X[rt], pos[rows], wt)
+    for nm, g, r in (("Q", Q, rq), ("K", K, rk), ("V", V, rv)):
+        check_y(g[rt.cuda()].double().cpu().numpy(), r, "bf16", True, label="N=%d %s" % (N, nm))
+    ref, _ = oracle.block_out(X[rt], Y[rt], wt)
+    check_update(out[rt.cuda()], X[rt], ref, "N=%d out" % N)
+
+
 def test_block_element_offsets_past_2_32():
     """N = 3053 x 1374 = 4,194,822 tokens: the FFN's 4096-wide hidden rows
     pass 2^32 elements from token 2^20 on, the 1024-wide rows of X, Q, K, V
