@@ -11,148 +11,11 @@
 //       kernels, which compute Delta^T's attention in the same pass;
 //   D2  per key, max over queries of x_qk - o_q, exponentiated once at the
 //       end (exp2 is monotone, so the maximum can be taken before it), on the
-//       bf16 MFMA (bf16 products are exact in fp32).
+//       bf16 MFMA (bf16 products are exact in fp32): colmax.hip.
 #include "vp_device.hpp"
 #include "vp_internal.hpp"
 
 namespace vp {
-
-constexpr int kDL = 72;   // bf16 LDS row stride (144 B)
-
-// ------------------------------------------------------------------------
-// D2: one workgroup = kCmWaves waves x (32 kCmKB) keys of one head; each wave
-// keeps its key rows as the MFMA's A operand in registers.  Query tiles of
-// 32 kCmQB (Q rows and -o_q / c) are staged through LDS, double-buffered, and
-// shared by the waves.  The accumulator starts at -o_q / c, so the MFMA
-// returns (x_qk - o_q) / c and a score costs half of a three-way max (two
-// query blocks at once); c > 0 carries the maximum over to x - o.  Queries
-// past N carry -inf; keys past N read row 0 and are not written.
-// ------------------------------------------------------------------------
-constexpr int kCmWaves = 8;
-constexpr int kCmKB = 2;                            // 32-key blocks per wave
-constexpr int kCmQB = 2;                            // 32-query blocks per tile (even)
-constexpr int kCmKeys = 32 * kCmKB * kCmWaves;      // keys per workgroup
-constexpr int kCmQ = 32 * kCmQB;                    // queries per LDS tile
-
-__global__ __launch_bounds__(64 * kCmWaves) void k_colmax(const bf16* __restrict__ Q,
-                                                          const bf16* __restrict__ K,
-                                                          const float* __restrict__ off,
-                                                          int64_t N, int H, float c,
-                                                          float* __restrict__ colmax) {
-    constexpr int kThreads = 64 * kCmWaves;
-    constexpr int kSegs = kCmQ * 8 / kThreads;   // 16-byte tile segments per thread
-    static_assert(kSegs * kThreads == kCmQ * 8 && kCmQ <= kThreads && kCmQB % 2 == 0, "tile");
-    const int h = blockIdx.y;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
-    const int64_t k0 = (int64_t)blockIdx.x * kCmKeys + wave * 32 * kCmKB;
-    bf16x8 Ka[kCmKB][4];
-#pragma unroll
-    for (int kb = 0; kb < kCmKB; ++kb) {
-        const int64_t key = k0 + 32 * kb + n;
-        const bf16* kp = K + ((key < N ? key : 0) * H + h) * kD + 8 * hh;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) Ka[kb][ks] = load_bf16x8(kp + 16 * ks);
-    }
-    __shared__ __attribute__((aligned(16))) bf16 sQ[2][kCmQ * kDL];
-    __shared__ float sO[2][kCmQ];
-    const float* oh = off + (int64_t)h * N;
-    const float ninv = -1.f / c;
-    bf16x8 gq[kSegs];
-    float go = 0.f;
-    // (Token indices fit int32: N is at most 2^28.)
-    const int Ni = (int)N;
-    const int64_t qstride = (int64_t)H * kD;
-    const bf16* qh = Q + (int64_t)h * kD;
-    auto gload = [&](int t) {
-#pragma unroll
-        for (int i = 0; i < kSegs; ++i) {
-            const int sg = threadIdx.x + i * kThreads;
-            const int q = min(t * kCmQ + (sg >> 3), Ni - 1);
-            gq[i] = load_bf16x8(qh + (int64_t)q * qstride + (sg & 7) * 8);
-        }
-        // (scaled at the store, so that nothing waits for the load here)
-        if (threadIdx.x < kCmQ) go = oh[min(t * kCmQ + (int)threadIdx.x, Ni - 1)];
-    };
-    auto lstore = [&](int t, int b) {
-#pragma unroll
-        for (int i = 0; i < kSegs; ++i) {
-            const int sg = threadIdx.x + i * kThreads;
-            *reinterpret_cast<bf16x8*>(&sQ[b][(sg >> 3) * kDL + (sg & 7) * 8]) = gq[i];
-        }
-        if (threadIdx.x < kCmQ)
-            sO[b][threadIdx.x] = t * kCmQ + (int)threadIdx.x < Ni ? go * ninv : -INFINITY;
-    };
-    float acc[kCmKB][16];
-#pragma unroll
-    for (int kb = 0; kb < kCmKB; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[kb][r] = -INFINITY;
-    const int nt = (Ni + kCmQ - 1) / kCmQ;
-    gload(0);
-    lstore(0, 0);
-    __syncthreads();
-    for (int t = 0; t < nt; ++t) {
-        const int b = (int)(t & 1);
-        if (t + 1 < nt) gload(t + 1);
-#pragma unroll
-        for (int qp = 0; qp < kCmQB; qp += 2) {
-            // lanes: query (qp + u) * 32 + n of the tile, features 16 ks + 8 hh ..
-            bf16x8 qv[2][4];
-            f32x16 ci[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int row = (qp + u) * 32 + n;
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
-                    qv[u][ks] = *reinterpret_cast<const bf16x8*>(&sQ[b][row * kDL + 16 * ks + 8 * hh]);
-                // ci = 16 copies of o: one copy into a register pair, then
-                // 64-bit moves (8 instructions instead of 16).
-                const float o = sO[b][row];
-                const uint32_t ob = __builtin_bit_cast(uint32_t, o);
-                const uint64_t pr = ((uint64_t)ob << 32) | ob;
-                uint64_t c8[8];
-                c8[0] = pr;
-#pragma unroll
-                for (int r = 1; r < 8; ++r) asm volatile("v_mov_b64 %0, %1" : "=v"(c8[r]) : "v"(pr));
-                ci[u] = __builtin_bit_cast(f32x16, c8);
-            }
-#pragma unroll
-            for (int kb = 0; kb < kCmKB; ++kb) {
-                f32x16 Sa = mfma_bf16(Ka[kb][0], qv[0][0], ci[0]);
-                f32x16 Sb = mfma_bf16(Ka[kb][0], qv[1][0], ci[1]);
-#pragma unroll
-                for (int ks = 1; ks < 4; ++ks) {
-                    Sa = mfma_bf16(Ka[kb][ks], qv[0][ks], Sa);
-                    Sb = mfma_bf16(Ka[kb][ks], qv[1][ks], Sb);
-                }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[kb][r] = fmaxf(acc[kb][r], fmaxf(Sa[r], Sb[r]));
-            }
-        }
-        if (t + 1 < nt) lstore(t + 1, b ^ 1);
-        __syncthreads();
-    }
-    // Maximum over the 32 query lanes of each half (same key rows), then
-    // 2^(c max).
-#pragma unroll
-    for (int kb = 0; kb < kCmKB; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float v = acc[kb][r];
-#pragma unroll
-            for (int o = 1; o < 32; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
-            acc[kb][r] = v;
-        }
-    if (n == 0) {
-#pragma unroll
-        for (int kb = 0; kb < kCmKB; ++kb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t key = k0 + 32 * kb + 8 * (r >> 2) + 4 * hh + (r & 3);
-                if (key < N) colmax[(int64_t)h * N + key] = exp2f(c * acc[kb][r]);
-            }
-    }
-}
 
 // s^attn_h = max_k colmax[h][k]; one workgroup per head.
 __global__ __launch_bounds__(256) void k_colmax_max(const float* __restrict__ colmax, int64_t N,
@@ -168,15 +31,17 @@ __global__ __launch_bounds__(256) void k_colmax_max(const float* __restrict__ co
 }
 
 // Bucket array with every head FULL (the teacher): counts (0, 0, H), ids
-// 0 .. H-1, no flags.
-__global__ void k_all_full(int H, int32_t* __restrict__ buckets) {
-    const int i = threadIdx.x;
+// 0 .. H-1, no flags; and colmax [n] = 0 for k_colmax's maxima.
+__global__ __launch_bounds__(256) void k_teacher_init(int H, int32_t* __restrict__ buckets,
+                                                      float* __restrict__ colmax, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < kBucketsLen) {
         int v = 0;
         if (i == 2) v = H;
-        else if (i >= 3 && i < 3 + kMaxHeads) v = (i - 3 < H) ? i - 3 : 0;
+        else if (i >= 3 && i < 3 + kMaxHeads) v = ((int)i - 3 < H) ? (int)i - 3 : 0;
         buckets[i] = v;
     }
+    for (int64_t k = i; k < n; k += (int64_t)gridDim.x * 256) colmax[k] = 0.f;
 }
 
 // delta = Y - V (Y fp32, V bf16), rounded once to the output type.
@@ -344,13 +209,13 @@ void launch_teacher_targets(const TeacherArgs& a, hipStream_t st) {
     const bf16 *Q = (const bf16*)a.attn.Q, *K = (const bf16*)a.attn.K;
     // D1 with Delta^T's attention: every head FULL into fp32 Y, offsets into
     // attn.off.
-    hipLaunchKernelGGL(k_all_full, dim3(1), dim3(64), 0, st, a.attn.H,
-                       const_cast<int32_t*>(a.attn.buckets));
+    const int64_t nc = a.attn.N * a.attn.H;
+    hipLaunchKernelGGL(k_teacher_init, dim3((unsigned)(nc < 262144 ? (nc + 255) / 256 : 1024)),
+                       dim3(256), 0, st, a.attn.H, const_cast<int32_t*>(a.attn.buckets), a.colmax,
+                       nc);
     launch_gather(a.attn, st);
     launch_flash(a.attn, st);
-    hipLaunchKernelGGL(k_colmax, dim3((unsigned)((a.attn.N + kCmKeys - 1) / kCmKeys), a.attn.H),
-                       dim3(64 * kCmWaves), 0, st, Q, K, (const float*)a.attn.off, a.attn.N,
-                       a.attn.H, c, a.colmax);
+    launch_colmax(Q, K, a.attn.off, a.attn.N, a.attn.H, c, a.colmax, st);
     hipLaunchKernelGGL(k_colmax_max, dim3(a.attn.H), dim3(256), 0, st, (const float*)a.colmax,
                        a.attn.N, a.smax);
     // Delta^T = Y - V.

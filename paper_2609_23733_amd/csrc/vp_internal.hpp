@@ -89,6 +89,8 @@ struct LossArgs {
     float* part;          // partial sums (distill_part_bytes)
     float* loss;          // [H]
 };
+void launch_colmax(const __bf16* Q, const __bf16* K, const float* off, int64_t N, int H, float c,
+                   float* colmax, hipStream_t st);
 void launch_teacher_targets(const TeacherArgs& a, hipStream_t st);
 void launch_router_loss(const LossArgs& a, hipStream_t st);
 void launch_latent_loss(const LossArgs& a, hipStream_t st);

@@ -65,6 +65,22 @@ def test_teacher_targets(P, sharp):
         check_delta(dl[:, h, :], d_ref, av, "P=%d h=%d" % (P, h))
 
 
+@pytest.mark.parametrize("P,H", [(64, 2), (1023, 16), (1025, 5), (2500, 16)])
+def test_colmax_split(P, H):
+    """Column maxima where the sequence of (head, 1024 keys, 64-query tile)
+    steps is shorter than, about, and longer than one per workgroup, with keys
+    just below and above one block: every key of the first and last head."""
+    from paper_2609_23733_amd import vp
+    log("column maxima P=%d H=%d" % (P, H))
+    x = synth.make_layer(1, P, dtype="bf16", key=(35, P), H=H, n_full=1, sharp=True)
+    colmax, smax, _ = vp.teacher_targets(x.Q.cuda(), x.K.cuda(), x.V.cuda(), 1, P)
+    torch.cuda.synchronize()
+    for h in (0, H - 1):
+        ref = oracle.attention_colmax(x.Q, x.K, h)
+        check_colmax(colmax[h].cpu().numpy(), ref, "P=%d h=%d" % (P, h))
+        check_colmax(smax[h:h + 1].cpu().numpy(), ref.max(keepdims=True), "smax")
+
+
 def test_teacher_targets_few_heads():
     """H = 3 heads (the teacher takes any head count up to 16)."""
     from paper_2609_23733_amd import vp
