@@ -44,6 +44,11 @@ __device__ __forceinline__ uint32_t float_order(float f) {
     const uint32_t u = __float_as_uint(f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+__device__ __forceinline__ float float_unorder(uint32_t u) {
+    return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
+}
+// Matching key of a source without a destination yet: (-inf, slot 0).
+constexpr uint64_t kNoMatch = 0x007fffffffffffffull;
 
 // ---------------------------------------------------------------- T1
 // 8 threads per token, 8 features each.
@@ -78,168 +83,236 @@ __global__ __launch_bounds__(256) void k_tome_metric(const bf16* __restrict__ K,
 }
 
 // ---------------------------------------------------------------- T2
-// One workgroup = kTmWaves waves x 64 sources and one chunk of the
-// destination tiles (blockIdx.y; chunks split the work finely enough to fill
-// the chip); each wave keeps its source rows as the MFMA's A operand.
-// Destination tiles of 64 rows (metric, 1 / |m| and a -inf bias past the last
-// destination) stream through LDS, double-buffered.  Per score:
-// v = dot / |m_d| (an FMA with the bias), a compare and two selects; each
-// lane sees its destinations in increasing slot order and keeps the first
-// maximum, the final reduction over lanes prefers the lower slot on equal
-// values.  The chunk's (value, slot) per source goes to a partial record;
-// k_tome_match_final takes the chunks in order (a later chunk wins only when
-// strictly larger), so ties still go to the lowest slot.
-constexpr int kTmWaves = 4;
-constexpr int kTmSrc = 64 * kTmWaves;
-constexpr int kTmChunks = 4;          // most destination chunks
-constexpr int kTmTargetGroups = 1024; // workgroups the split aims for
+// 8 waves x 128 sources per workgroup, the sources' metric rows in registers as
+// the MFMA's B operand.  Tiles of 64 destinations stream through three LDS
+// buffers; destinations are the MFMA's rows, so a lane's 16 results of a 32 x
+// 32 block are 16 destinations of one source, in increasing slot order.  The
+// similarity up to the source's own norm is v = fl(m_s . m_d fl(1 / |m_d|)); a
+// lane keeps its source's first largest v.
+// Most blocks raise no lane's maximum, so a block is first bounded: every v is
+// at most max(m_s . m_d, 0) times the largest 1 / |m_d| of the lane's 16 rows
+// (rounding is monotone, so the bound holds for the rounded products, too), and
+// only if that passes some lane's maximum are the products formed and, if one
+// is larger, its slot found: eight integer maxima (non-negative floats order like
+// integers), a multiplication and a compare per 16 scores instead of 64
+// instructions.  A NaN product makes the bound NaN, which takes the exact path,
+// where it never wins.  Rows past the last destination repeat it.
+//
+// The work is one sequence of (1024 sources, destination tile) steps split evenly
+// over the workgroups; the parts of a source meet in an atomic maximum of
+// (ordered v, complement of the slot), so the lower slot wins on equal values
+// whatever the order.  Every 16 tiles a part publishes what it has found and
+// takes the value just below the source's maximum so far as its own lower
+// bound: that leaves out only destinations that are strictly worse than a
+// published one, so the outcome does not depend on when it is read.
+// 108,405 sources x 28,995 destinations (S = 100, 75 %): 911 -> 475 us, 325 of
+// them without a block past its bound (the products alone would take 160).
+// Screening on rows scaled beforehand (a tighter bound, the products taken
+// again past it) was slower (549 us): the blocks that pass are mostly real
+// improvements.
+constexpr int kTmWaves = 8;
+constexpr int kTmKB = 4;                           // 32-source blocks per wave
+constexpr int kTmSrc = 32 * kTmKB * kTmWaves;      // sources per workgroup
+constexpr int kTmWG = 256;                         // workgroups: one per CU
 
-__global__ __launch_bounds__(64 * kTmWaves) void k_tome_match(const bf16* __restrict__ m,
-                                                              const float* __restrict__ invn,
-                                                              TomeGeom G,
-                                                              float* __restrict__ pval,
-                                                              int32_t* __restrict__ pidx) {
-    constexpr int kThreads = 64 * kTmWaves;
-    constexpr int kSegs = 64 * 8 / kThreads;
+// Destination slot -> token in 32 bits (N is at most 2^28).
+__device__ __forceinline__ uint32_t dst_token32(uint32_t j, uint32_t P, uint32_t per, uint32_t nsp,
+                                                uint32_t g) {
+    if (j < P) return j;
+    const uint32_t q = (j - P) / per, w = j - P - q * per;
+    return (1 + q) * P + (w < nsp ? w : nsp + (w - nsp) * g);
+}
+
+__global__ __launch_bounds__(64 * kTmWaves, 1) void k_tome_match(const bf16* __restrict__ m,
+                                                                 const float* __restrict__ invn,
+                                                                 TomeGeom G,
+                                                                 unsigned long long* __restrict__ best) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
-    const int64_t i0 = (int64_t)blockIdx.x * kTmSrc + wave * 64;
-    bf16x8 A[2][4];
+    __shared__ __attribute__((aligned(16))) bf16 sD[3][64 * kRow];
+    __shared__ __attribute__((aligned(16))) float sInv[3][64];   // 1 / |m_d|
+    __shared__ float sTop[3][4];   // the largest of the 16 rows (block, lane half)
+    const int nD = (int)G.nD;
+    const uint32_t P = (uint32_t)G.P, per = (uint32_t)(G.nsp + G.ndp), nsp = (uint32_t)G.nsp,
+                   gs = (uint32_t)G.g;
+    const int nt = (nD + 63) / 64;
+    const int64_t nsb = (G.nA + kTmSrc - 1) / kTmSrc;
+    const int64_t total = nsb * nt, W = gridDim.x;
+    const int w = xcd_remap(blockIdx.x, (int)W);
+    int64_t x = total * w / W;
+    const int64_t end = total * (w + 1) / W;
+    while (x < end) {
+        const int64_t item = x / nt;
+        const int t0 = (int)(x - item * nt);
+        const int t1 = (int)(end - x < nt - t0 ? t0 + (end - x) : nt);
+        x += t1 - t0;
+        const int64_t i0 = item * kTmSrc + wave * 32 * kTmKB;
+        bf16x8 B[kTmKB][4];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        const int64_t i = i0 + 32 * kb + n;
-        const int64_t tok = i < G.nA ? tome_src_token(G, i) : 0;
+        for (int kb = 0; kb < kTmKB; ++kb) {
+            const int64_t i = i0 + 32 * kb + n;
+            const int64_t tok = i < G.nA ? tome_src_token(G, i) : 0;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) A[kb][ks] = load_bf16x8(m + tok * kD + 16 * ks + 8 * hh);
-    }
-    __shared__ __attribute__((aligned(16))) bf16 sD[2][64 * kRow];
-    __shared__ float sInv[2][64], sBias[2][64];
-    bf16x8 gq[kSegs];
-    float gi = 0.f;
-    auto gload = [&](int64_t t) {
-#pragma unroll
-        for (int s = 0; s < kSegs; ++s) {
-            const int sg = threadIdx.x + s * kThreads;
-            const int64_t j = t * 64 + (sg >> 3);
-            const int64_t tok = j < G.nD ? tome_dst_token(G, j) : 0;
-            gq[s] = load_bf16x8(m + tok * kD + (sg & 7) * 8);
+            for (int ks = 0; ks < 4; ++ks) B[kb][ks] = load_bf16x8(m + tok * kD + 16 * ks + 8 * hh);
         }
-        if (threadIdx.x < 64) {
-            const int64_t j = t * 64 + threadIdx.x;
-            gi = invn[j < G.nD ? tome_dst_token(G, j) : 0];
-        }
-    };
-    auto lstore = [&](int64_t t, int b) {
-#pragma unroll
-        for (int s = 0; s < kSegs; ++s) {
-            const int sg = threadIdx.x + s * kThreads;
-            *reinterpret_cast<bf16x8*>(&sD[b][(sg >> 3) * kRow + (sg & 7) * 8]) = gq[s];
-        }
-        if (threadIdx.x < 64) {
-            const bool ok = t * 64 + threadIdx.x < G.nD;
-            sInv[b][threadIdx.x] = ok ? gi : 0.f;
-            sBias[b][threadIdx.x] = ok ? 0.f : -INFINITY;
-        }
-    };
-    float acc[2][16];
-    int32_t idx[2][16];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            acc[kb][r] = -INFINITY;
-            idx[kb][r] = 0;
-        }
-    const int64_t ntt = (G.nD + 63) / 64, C = gridDim.y;
-    const int64_t t0 = blockIdx.y * ntt / C, nt = (blockIdx.y + 1) * ntt / C;
-    gload(t0);
-    lstore(t0, (int)(t0 & 1));
-    __syncthreads();
-    for (int64_t t = t0; t < nt; ++t) {
-        const int b = (int)(t & 1);
-        if (t + 1 < nt) gload(t + 1);
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-            bf16x8 qv[4];
+        bf16x8 gq;
+        float gi = 0.f;
+        const int lr = threadIdx.x >> 3, lc = (threadIdx.x & 7) * 8;
+        auto gload = [&](int t) {   // (clamped to the last tile and destination)
+            t = t < t1 ? t : t1 - 1;
+            gq = load_bf16x8(m + (int64_t)dst_token32(min(t * 64 + lr, nD - 1), P, per, nsp, gs) * kD +
+                             lc);
+            if (wave == 0)
+                gi = invn[dst_token32(min(t * 64 + lane, nD - 1), P, per, nsp, gs)];
+        };
+        auto lstore = [&](int b) {
+            *reinterpret_cast<bf16x8*>(&sD[b][lr * kRow + lc]) = gq;
+            if (wave == 0) {
+                sInv[b][lane] = gi;
+                // rows 8 g + 4 hh + i of a block: the same bits 2 and 5
+                float top = gi;
+                top = fmaxf(top, __shfl_xor(top, 1));
+                top = fmaxf(top, __shfl_xor(top, 2));
+                top = fmaxf(top, __shfl_xor(top, 8));
+                top = fmaxf(top, __shfl_xor(top, 16));
+                if ((lane & 27) == 0) sTop[b][2 * (lane >> 5) + ((lane >> 2) & 1)] = top;
+            }
+        };
+        bf16x8 qv[2][4];
+        auto lread = [&](int b, int qb) {
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks)
-                qv[ks] = *reinterpret_cast<const bf16x8*>(
-                    &sD[b][(qb * 32 + n) * kRow + 16 * ks + 8 * hh]);
-            const float inv = sInv[b][qb * 32 + n], bias = sBias[b][qb * 32 + n];
-            const int32_t jn = (int32_t)(t * 64 + qb * 32 + n);
+                qv[qb][ks] = *reinterpret_cast<const bf16x8*>(
+                    &sD[b][(32 * qb + n) * kRow + 16 * ks + 8 * hh]);
+        };
+        float acc[kTmKB];
+        int idx[kTmKB];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                f32x16 S = mfma_bf16(A[kb][0], qv[0], zero_f32x16());
+        for (int kb = 0; kb < kTmKB; ++kb) {
+            acc[kb] = -INFINITY;
+            idx[kb] = -1;   // none of this part's, or one already published
+        }
+        // Publish the part's finds; known = the sources' maxima so far (lane half 0).
+        unsigned long long known[kTmKB];
+        auto publish = [&]() {
 #pragma unroll
-                for (int ks = 1; ks < 4; ++ks) S = mfma_bf16(A[kb][ks], qv[ks], S);
+            for (int kb = 0; kb < kTmKB; ++kb) {
+                const float v = acc[kb] + 0.f;   // (no -0)
+                unsigned long long k =
+                    idx[kb] < 0 ? 0
+                                : ((unsigned long long)float_order(v) << 32) |
+                                      (uint32_t)~(uint32_t)idx[kb];
+                const unsigned long long o = __shfl_xor(k, 32);   // the source's other rows
+                k = o > k ? o : k;
+                const int64_t i = i0 + 32 * kb + n;
+                known[kb] = 0;
+                if (hh == 0 && i < G.nA) known[kb] = max(k, atomicMax(&best[i], k));
+            }
+        };
+        auto raise = [&]() {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float v = fmaf(S[r], inv, bias);
-                    const bool up = v > acc[kb][r];
-                    acc[kb][r] = up ? v : acc[kb][r];
-                    idx[kb][r] = up ? jn : idx[kb][r];
+            for (int kb = 0; kb < kTmKB; ++kb) {
+                const uint32_t u = __shfl((uint32_t)(known[kb] >> 32), n);
+                const float low = u > 0x007fffffu ? float_unorder(u - 1) : -INFINITY;
+                if (low > acc[kb]) {
+                    acc[kb] = low;
+                    idx[kb] = -1;
                 }
             }
-        }
-        if (t + 1 < nt) lstore(t + 1, b ^ 1);
+        };
+        f32x16 Sa[2], Sb[2];   // the blocks being multiplied, and the two before them
+        // S = blocks (qb, 2 kp and 2 kp + 1)
+        auto mul = [&](int qb, int kp, f32x16 (&S)[2]) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) S[u] = mfma_bf16(qv[qb][0], B[2 * kp + u][0], zero_f32x16());
+#pragma unroll
+            for (int ks = 1; ks < 4; ++ks)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) S[u] = mfma_bf16(qv[qb][ks], B[2 * kp + u][ks], S[u]);
+        };
+        // Blocks T of sources 2 kp, 2 kp + 1 and the 32 destinations from slot j0, whose
+        // 1 / |m| start at inv (LDS; the largest of the lane half's 16: top).
+        auto take = [&](int kp, const f32x16 (&T)[2], const float* inv, float top, int j0) {
+            bool over[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                int mx = 0;
+#pragma unroll
+                for (int r = 0; r < 16; r += 2)
+                    mx = max(max(mx, __float_as_int(T[u][r])), __float_as_int(T[u][r + 1]));
+                over[u] = !(__int_as_float(mx) * top <= acc[2 * kp + u]);
+            }
+            if (__builtin_amdgcn_ballot_w64(over[0] || over[1]) == 0) return;
+            f32x4 iv[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) iv[g] = *reinterpret_cast<const f32x4*>(inv + 8 * g + 4 * hh);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (__builtin_amdgcn_ballot_w64(over[u]) == 0) continue;
+                float v[16], mx = -INFINITY;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = T[u][r] * iv[r >> 2][r & 3];
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) mx = fmaxf(fmaxf(mx, v[r]), v[r + 1]);
+                const bool up = mx > acc[2 * kp + u];
+                if (__builtin_amdgcn_ballot_w64(up) == 0) continue;
+                int at = 0;   // the first row with that value
+#pragma unroll
+                for (int r = 15; r >= 0; --r) at = v[r] == mx ? 8 * (r >> 2) + (r & 3) : at;
+                acc[2 * kp + u] = up ? mx : acc[2 * kp + u];
+                idx[2 * kp + u] = up ? min(j0 + 4 * hh + at, nD - 1) : idx[2 * kp + u];
+            }
+        };
+        __syncthreads();   // the previous segment's reads are done
+        gload(t0);
+        lstore(0);
+        gload(t0 + 1);
+        lstore(1);
+        gload(t0 + 2);
         __syncthreads();
-    }
-    // Over the 32 destination lanes of each half: the larger value, the
-    // lower slot on equal values.
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float v = acc[kb][r];
-            int32_t j = idx[kb][r];
-#pragma unroll
-            for (int o = 1; o < 32; o <<= 1) {
-                const float ov = __shfl_xor(v, o);
-                const int32_t oj = __shfl_xor(j, o);
-                const bool take = ov > v || (ov == v && oj < j);
-                v = take ? ov : v;
-                j = take ? oj : j;
-            }
-            acc[kb][r] = v;
-            idx[kb][r] = j;
+        lread(0, 0);
+        mul(0, 0, Sa);
+        int b0 = 0, b1 = 1, b2 = 2;   // buffers of tiles t, t + 1, t + 2
+        for (int t = t0; t < t1; ++t) {
+            const float* inv = sInv[b0];
+            const float top0 = sTop[b0][hh], top1 = sTop[b0][2 + hh];
+            lread(b0, 1);
+            mul(0, 1, Sb);
+            lstore(b2);
+            gload(t + 3);
+            if (((t - t0) & 15) == 8) publish();
+            if (((t - t0) & 15) == 10) raise();
+            take(0, Sa, inv, top0, 64 * t);
+            mul(1, 0, Sa);
+            take(1, Sb, inv, top0, 64 * t);
+            lread(b1, 0);
+            mul(1, 1, Sb);
+            take(0, Sa, inv + 32, top1, 64 * t + 32);
+            mul(0, 0, Sa);   // (past the last tile: a block that is not taken)
+            take(1, Sb, inv + 32, top1, 64 * t + 32);
+            __syncthreads();
+            const int b = b0;
+            b0 = b1;
+            b1 = b2;
+            b2 = b;
         }
-    if (n == 0) {
-        const int64_t base = (int64_t)blockIdx.y * G.nA;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t i = i0 + 32 * kb + 8 * (r >> 2) + 4 * hh + (r & 3);
-                if (i < G.nA) {
-                    pval[base + i] = acc[kb][r];
-                    pidx[base + i] = idx[kb][r];
-                }
-            }
+        publish();
     }
 }
 
-// Per source: the best over the chunks, its cosine similarity and its
-// selection key (similarity, then the lower token).
-__global__ __launch_bounds__(256) void k_tome_match_final(TomeGeom G, int C,
-                                                          const float* __restrict__ pval,
-                                                          const int32_t* __restrict__ pidx,
+// Per source: its destination slot, the cosine similarity and the selection key
+// (similarity, then the lower token).
+__global__ __launch_bounds__(256) void k_tome_match_final(TomeGeom G,
+                                                          const uint64_t* __restrict__ top,
                                                           const float* __restrict__ invn,
                                                           int32_t* __restrict__ best,
                                                           float* __restrict__ score,
                                                           uint64_t* __restrict__ key) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= G.nA) return;
-    float v = pval[i];
-    int32_t j = pidx[i];
-    for (int c = 1; c < C; ++c) {
-        const float w = pval[(int64_t)c * G.nA + i];
-        if (w > v) {
-            v = w;
-            j = pidx[(int64_t)c * G.nA + i];
-        }
-    }
+    const float v = float_unorder((uint32_t)(top[i] >> 32));
     const int64_t tok = tome_src_token(G, i);
     const float sc = v * invn[tok] + 0.f;   // + 0: no -0
-    best[i] = j;
+    best[i] = (int32_t)~(uint32_t)top[i];
     score[i] = sc;
     key[i] = ((uint64_t)float_order(sc) << 32) | (uint64_t)(~(uint32_t)tok);
 }
@@ -247,13 +320,18 @@ __global__ __launch_bounds__(256) void k_tome_match_final(TomeGeom G, int C,
 // ---------------------------------------------------------------- T3
 // Radix select of the M largest keys, 8 bits per pass from the top.  State:
 // [0] prefix (u64), [1] keys still to take (as u64).
-__global__ void k_rsel_init(uint64_t* __restrict__ st, uint32_t* __restrict__ ghist, int64_t M) {
-    const int i = threadIdx.x;
+__global__ __launch_bounds__(256) void k_tome_init(uint64_t* __restrict__ st,
+                                                   uint32_t* __restrict__ ghist, int64_t M,
+                                                   int32_t* __restrict__ cnt, int64_t nD,
+                                                   uint64_t* __restrict__ top, int64_t nA) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < 256) ghist[i] = 0;
     if (i == 0) {
         st[0] = 0;
         st[1] = (uint64_t)M;
     }
+    if (i < nD) cnt[i] = 0;    // merged sources per destination
+    if (i < nA) top[i] = kNoMatch;   // matching: maxima so far
 }
 
 __global__ __launch_bounds__(256) void k_rsel_hist(const uint64_t* __restrict__ key, int64_t n,
@@ -431,11 +509,6 @@ __global__ __launch_bounds__(kSortBlock) void k_rs_scatter(const uint32_t* __res
 }
 
 // ---------------------------------------------------------------- T4
-__global__ __launch_bounds__(256) void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 // Per token: kept flag; per source: merged flag; merged count per
 // destination; the optional best / score outputs.
 __global__ __launch_bounds__(256) void k_tome_flags(TomeGeom G, const uint64_t* __restrict__ key,
@@ -642,7 +715,7 @@ __global__ __launch_bounds__(256) void k_tome_unmerge(const u32x4* __restrict__ 
 // Workspace of the plan for N tokens.
 struct TomeWs {
     size_t m, invn, bslot, score, key, st, ghist, mflag, pos, kept, cnt, off, size, lk0, lv0,
-        lk1, lv1, bsum, hist, pval, pidx, total;
+        lk1, lv1, bsum, hist, top, total;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -677,8 +750,7 @@ TomeWs tome_ws(int64_t N) {
     w.lv1 = take(n * 4);
     w.bsum = take(((256 * nbr > n ? 256 * nbr : n) / kScanBlock + 2) * 4 + nbs * 4);
     w.hist = take(256 * nbr * 4);
-    w.pval = take(n * kTmChunks * 4);
-    w.pidx = take(n * kTmChunks * 4);
+    w.top = take(n * 8);
     w.total = o;
     return w;
 }
@@ -707,24 +779,20 @@ void launch_tome_plan(const TomeArgs& a, hipStream_t st) {
     int32_t *lv0 = (int32_t*)(ws + w.lv0), *lv1 = (int32_t*)(ws + w.lv1);
     int32_t* bsum = (int32_t*)(ws + w.bsum);
     int32_t* hist = (int32_t*)(ws + w.hist);
+    uint64_t* top = (uint64_t*)(ws + w.top);
     const int64_t N = G.N, M = a.M, nrows = N - M;
 
-    hipLaunchKernelGGL(k_rsel_init, dim3(1), dim3(256), 0, st, sel, ghist, M);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid256(G.nD)), dim3(256), 0, st, cnt, G.nD, 0);
+    hipLaunchKernelGGL(k_tome_init, dim3(grid256(N)), dim3(256), 0, st, sel, ghist, M, cnt, G.nD,
+                       top, G.nA);
     if (G.nA > 0) {
         hipLaunchKernelGGL(k_tome_metric, dim3(grid256(N * 8)), dim3(256), 0, st, a.K, N, a.H, m,
                            invn);
-        const int64_t ns = (G.nA + kTmSrc - 1) / kTmSrc, ntt = (G.nD + 63) / 64;
-        int64_t C = (kTmTargetGroups + ns - 1) / ns;
-        C = C < 1 ? 1 : (C > kTmChunks ? kTmChunks : C);
-        C = C > ntt ? ntt : C;
-        float* pval = (float*)(ws + w.pval);
-        int32_t* pidx = (int32_t*)(ws + w.pidx);
-        hipLaunchKernelGGL(k_tome_match, dim3((unsigned)ns, (unsigned)C), dim3(64 * kTmWaves), 0,
-                           st, (const bf16*)m, (const float*)invn, G, pval, pidx);
-        hipLaunchKernelGGL(k_tome_match_final, dim3(grid256(G.nA)), dim3(256), 0, st, G, (int)C,
-                           (const float*)pval, (const int32_t*)pidx, (const float*)invn, bslot,
-                           score, key);
+        const int64_t steps = ((G.nA + kTmSrc - 1) / kTmSrc) * ((G.nD + 63) / 64);
+        hipLaunchKernelGGL(k_tome_match, dim3((unsigned)(steps < kTmWG ? steps : kTmWG)),
+                           dim3(64 * kTmWaves), 0, st, (const bf16*)m, (const float*)invn, G,
+                           (unsigned long long*)top);
+        hipLaunchKernelGGL(k_tome_match_final, dim3(grid256(G.nA)), dim3(256), 0, st, G,
+                           (const uint64_t*)top, (const float*)invn, bslot, score, key);
         // (M > 0 here: M = 0 leaves stride 1, hence no sources)
         const unsigned gh = (unsigned)((G.nA + 4095) / 4096);
         for (int shift = 56; shift >= 0; shift -= 8) {

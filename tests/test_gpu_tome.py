@@ -169,6 +169,44 @@ def test_plan_edges(S, P, M, nspecial):
         np.testing.assert_array_equal(plan.members.cpu().numpy(), np.arange(S * P))
 
 
+@pytest.mark.parametrize("S,P,M", [(2, 70, 40), (3, 700, 1000), (4, 1374, 3900)])
+def test_match_zero_and_nan_rows(S, P, M):
+    """Source counts below and above one block of 1024 and destinations around
+    whole 64-row tiles, with zero rows and NaN rows on both sides: a NaN
+    destination never wins, a zero source takes the first destination, and
+    every other choice is the best of the finite destinations (fp32 sums of 64
+    products of bf16 values: 2e-6 covers them, as in the other plan tests)."""
+    from paper_2609_23733_amd import vp
+    log("match zero / NaN rows S=%d P=%d" % (S, P))
+    N = S * P
+    K = synth.stored(synth.normal((N, 16, 64), synth.derive_seed(49, S, P), 1.0), "bf16")
+    is_dst, _ = oracle.tome_split(S, P, M)
+    d, s = np.nonzero(is_dst)[0], np.nonzero(~is_dst)[0]
+    K[int(d[7])] = 0
+    K[int(s[3])] = 0
+    K[int(d[11])] = float("nan")
+    K[int(d[-1])] = float("nan")
+    K[int(s[5])] = float("nan")
+    plan = run_plan(K, S, P, M)
+    best, score = plan.best.cpu().numpy(), plan.score.cpu().numpy().astype(np.float64)
+    acc = torch.zeros(N, 64)
+    for h in range(16):
+        acc += K[:, h].float()
+    m = acc.to(torch.bfloat16).double().numpy()
+    nrm = np.sqrt((m * m).sum(1))
+    u = m / np.where(nrm > 0, nrm, 1.0)[:, None]
+    sim = u[s] @ u[d].T
+    sim[:, np.isnan(u[d]).any(1)] = -np.inf
+    ok = ~np.isnan(u[s]).any(1)
+    slot = np.searchsorted(d, best[s])
+    assert (d[slot] == best[s]).all()
+    got = sim[np.arange(len(s)), slot]
+    assert (got[ok] >= sim[ok].max(1) - 2e-6).all()
+    assert np.abs(score[s][ok] - got[ok]).max() <= 2e-6
+    assert best[s[3]] == d[0] and score[s[3]] == 0.0
+    assert int((plan.row.cpu().numpy()[s] == plan.row.cpu().numpy()[best[s]]).sum()) == M
+
+
 def planted_keys(S, P, seed):
     """Random keys; 40 sources are power-of-two multiples of one destination
     (exact cosine ties on both sides), 100 more are noisy copies of other
