@@ -319,16 +319,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4
     }
 }
 
-// 64 lanes x 16 bytes from base + voff (per lane) to 1 KB of LDS at byte `lds`
-// (uniform).  The copy is counted in vmcnt by issue order; callers wait for it
-// with explicit counts.
-__device__ __forceinline__ void copy_to_lds(uint32_t lds, const char* base, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds), "v"(voff), "s"(base)
-                 : "memory");
-}
-
 // Persistent, one workgroup of 8 waves per CU (two per SIMD), each wave a block of 128
 // features x 64 tokens.  Waves 0-3 (features 0-127) and 4-7 (features 128-255)
 // alternate, one phase apart, with one barrier per phase: while one group

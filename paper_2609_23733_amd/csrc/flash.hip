@@ -333,10 +333,9 @@ constexpr int kPartFloats = kBQf * kD + 2 * kBQf;   // partial slot: O[512][64],
 constexpr int kMinPartTiles = 8;    // fewest key tiles per workgroup in the tail
 constexpr int64_t kRotateTiles = 4096;   // 64 MB of K and V^T tiles (16 KB each)
 
-// Workgroups used for T tail steps (at most G, at least kMinPartTiles steps
-// each), the first step of workgroup w, and the workgroup holding step x.
-__device__ __forceinline__ int tail_groups(int64_t T, int G) {
-    const int64_t g = T / kMinPartTiles;
+// Workgroups used for T tail steps (at most G, at least `least` steps each), the first step of workgroup w, and the workgroup holding step x.
+__host__ __device__ inline int tail_groups(int64_t T, int G, int least = kMinPartTiles) {
+    const int64_t g = T / least;
     return g < 1 ? 1 : (g < G ? (int)g : G);
 }
 __device__ __forceinline__ int64_t tail_start(int w, int64_t T, int G) {
@@ -1228,24 +1227,27 @@ __global__ __launch_bounds__(256, 2) void k_flash_bf16_wide(const bf16* __restri
 // matching V row from LDS.  Small layers (few work items for the chip) split
 // each item's key tiles into two halves run by separate workgroups; each
 // half writes O (unnormalized, relative to its reference point m), l and m
-// per query, and K6d combines the two halves in order.
+// per query, and K6d combines the two halves in order.  With `only`, runs the
+// items flagged there (those that K6e left).
 // ------------------------------------------------------------------------
 constexpr int kBQ32 = 128;
 constexpr int kKRow32 = 65;   // odd stride: column reads are bank-conflict free
-constexpr int kRec32 = kD + 4;   // split record: O[64], l, m, 2 pad (16-byte aligned)
+constexpr int kRec32 = kD + 4;   // part record: O[64], l, m, 2 pad (16-byte aligned)
 
 __global__ __launch_bounds__(256, 2) void k_flash_f32(const float* __restrict__ Q,
                                                       const float* __restrict__ K,
                                                       const float* __restrict__ V,
                                                       const int32_t* __restrict__ buckets,
                                                       int64_t N, int H, int nqt, int nkt, float c,
-                                                      int splits, float* __restrict__ part,
+                                                      int splits, const int32_t* __restrict__ only,
+                                                      float* __restrict__ part,
                                                       void* __restrict__ Y, int ydt) {
     const int nfull = full_count(buckets, H);
     const int active = nfull * nqt;
     if ((int)blockIdx.x >= active * splits) return;
     const int Lx = xcd_remap(blockIdx.x, active * splits);
     const int L = Lx / splits, half = Lx - L * splits;
+    if (only && !only[L]) return;
     const int slot = L / nqt, qt = L - slot * nqt;
     // key tiles [t0, t1) of the item (all of them unless split)
     const int t0 = (int)((int64_t)half * nkt / splits);
@@ -1441,6 +1443,470 @@ __global__ __launch_bounds__(256) void k_flash_f32_combine(const int32_t* __rest
     }
 }
 
+// ------------------------------------------------------------------------
+// K6e (fp32, longer layers).  Every operand is a sum of two fp16 values times a power of two, x
+// 2^-e = hi + lo (both rounded to nearest: the remainder is at most 2^-24 |x|,
+// like fp32's own rounding, and 2^-39 of the largest value of its group where lo is
+// subnormal), and a product takes three 32x32x16 fp16 MFMAs, lo hi + hi lo + hi hi
+// (lo lo is at most 2^-24 of it), 96 cycles per 16 values against 512 for the
+// 32x32x2 fp32 MFMA; all sums stay fp32.  Measured against float64 the
+// error is smaller than with fp32 MFMAs, whose 64 products per sum are added
+// one by one (of the output norm, 2,748 tokens: 1.3e-7 against 1.9e-7; sharp
+// heads 2.1e-7 against 3.5e-7, Q x 3 4.2e-7 against 9.4e-7).
+// K is scaled per head, V per head and feature (undone at the end, so that
+// every feature keeps its own precision), Q per query.  Heads and items with a
+// value that is not finite or whose largest magnitude lies outside [2^-60, 2^60]
+// (zero aside) are flagged and left to K6.
+//   k_absmax_f32: per group of token rows, largest |k| and per feature |v|, as
+//   integer bits (a NaN is larger than any number);
+//   k_pack_f32: scales, and per 64-key tile K hi, K lo (rows in swap23 order),
+//   V^T hi, V^T lo: 4 x 8 KB, 128-byte rows with 16-byte chunks at position
+//   chunk ^ (row / 2 % 8), copied to LDS as they are.
+// ------------------------------------------------------------------------
+constexpr int kWG32 = 512;       // workgroups: two per CU
+constexpr int kMinTiles32 = 4;   // fewest key tiles per workgroup in the tail
+constexpr uint32_t kTile32 = 32768;    // bytes of a packed key tile
+constexpr int kMax32 = kD + 1;         // |v| per feature, |k|
+constexpr int kScale32 = kD + 4;       // per slot: 2^e_d of V, 2^e of K, exact flag, 2 pad
+constexpr int kMaxGroups32 = 64;
+
+__host__ __device__ inline int64_t f32_group_rows(int64_t N) {   // rows per maximum group
+    const int64_t r = (N + kMaxGroups32 - 1) / kMaxGroups32;
+    return r < 128 ? 128 : (r + 31) / 32 * 32;
+}
+
+__global__ __launch_bounds__(256) void k_absmax_f32(const float* __restrict__ K,
+                                                    const float* __restrict__ V,
+                                                    const int32_t* __restrict__ buckets, int64_t N,
+                                                    int H, uint32_t* __restrict__ part) {
+    const int slot = blockIdx.y;
+    if (slot >= full_count(buckets, H)) return;
+    const int h = full_head(buckets, H, slot);
+    if (h < 0) return;
+    __shared__ uint32_t s[kMax32];
+    if (threadIdx.x < kMax32) s[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t rows = f32_group_rows(N), r0 = (int64_t)blockIdx.x * rows;
+    const int64_t r1 = r0 + rows < N ? r0 + rows : N;
+    const int seg = (threadIdx.x & 15) * 4;
+    uint32_t mk = 0, mv[4] = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int64_t row = r0 + (threadIdx.x >> 4); row < r1; row += 16) {
+        const int64_t o = (row * H + h) * kD + seg;
+        const u32x4 k = *reinterpret_cast<const u32x4*>(K + o);
+        const u32x4 v = *reinterpret_cast<const u32x4*>(V + o);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            mk = max(mk, k[j] & 0x7fffffffu);
+            mv[j] = max(mv[j], v[j] & 0x7fffffffu);
+        }
+    }
+    atomicMax(&s[kD], mk);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) atomicMax(&s[seg + j], mv[j]);
+    __syncthreads();
+    if (threadIdx.x < kMax32)
+        part[((int64_t)slot * gridDim.x + blockIdx.x) * kMax32 + threadIdx.x] = s[threadIdx.x];
+}
+
+// Exponent e with |x| 2^-e < 2^14 for all |x| up to the one with bits m, and
+// whether it is in the split's range.
+__device__ __forceinline__ int f32_exponent(uint32_t m) {
+    return m == 0 ? 0 : (int)(m >> 23) - 127 - 13;
+}
+__device__ __forceinline__ bool f32_in_range(uint32_t m) {
+    return m == 0 || (m >= (uint32_t)(127 - 60) << 23 && m < (uint32_t)(127 + 60) << 23);
+}
+__device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
+
+// x = hi + lo (x already scaled).
+__device__ __forceinline__ void split16(float x, f16& hi, f16& lo) {
+    hi = (f16)x;
+    lo = (f16)(x - (float)hi);
+}
+
+__global__ __launch_bounds__(256) void k_pack_f32(const float* __restrict__ K,
+                                                  const float* __restrict__ V,
+                                                  const int32_t* __restrict__ buckets, int64_t N,
+                                                  int H, int nkt, const uint32_t* __restrict__ part,
+                                                  int ng, float* __restrict__ scales,
+                                                  char* __restrict__ tiles) {
+    const int slot = blockIdx.y, tile = blockIdx.x;
+    if (slot >= full_count(buckets, H)) return;
+    const int h = full_head(buckets, H, slot);
+    if (h < 0) return;
+    __shared__ uint32_t smax[kMax32];
+    __shared__ __attribute__((aligned(16))) f16 sT[2][kD * kLdsRow];
+    const int t = threadIdx.x;
+    const int key = t >> 2, dseg = (t & 3) * 16;
+    const int64_t row = (int64_t)tile * kBK + key;
+    const bool ok = row < N;
+    const int64_t o = ((ok ? row : 0) * H + h) * kD + dseg;
+    f32x4 kv[4], vv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        kv[i] = *reinterpret_cast<const f32x4*>(K + o + 4 * i);
+        vv[i] = *reinterpret_cast<const f32x4*>(V + o + 4 * i);
+    }
+    if (t < kMax32) {
+        uint32_t m = 0;
+        for (int g = 0; g < ng; ++g) m = max(m, part[((int64_t)slot * ng + g) * kMax32 + t]);
+        smax[t] = m;
+    }
+    __syncthreads();
+    const int ek = f32_exponent(smax[kD]);
+    if (tile == 0) {
+        const bool bad = t < kMax32 && !f32_in_range(smax[t]);
+        const bool any = __syncthreads_or(bad) != 0;
+        if (t < kD) scales[slot * kScale32 + t] = f32_in_range(smax[t]) ? pow2(f32_exponent(smax[t])) : 1.f;
+        if (t == kD) scales[slot * kScale32 + kD] = f32_in_range(smax[kD]) ? pow2(ek) : 1.f;
+        if (t == kD + 1) scales[slot * kScale32 + kD + 1] = any ? 1.f : 0.f;
+    }
+    // (out of range: any scale, the tiles are not used)
+    const float dk = f32_in_range(smax[kD]) ? pow2(-ek) : 1.f;
+    char* out = tiles + ((int64_t)slot * nkt + tile) * kTile32;
+    const int kr = swap23(key);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        f16x8 hi, lo;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            f16 a, b;
+            split16(ok ? kv[2 * c + (j >> 2)][j & 3] * dk : 0.f, a, b);
+            hi[j] = a;
+            lo[j] = b;
+        }
+        char* p = out + kr * 128 + ((((t & 3) * 2 + c) ^ ((kr >> 1) & 7)) << 4);
+        *reinterpret_cast<f16x8*>(p) = hi;
+        *reinterpret_cast<f16x8*>(p + 8192) = lo;
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const uint32_t m = smax[dseg + j];
+        const float dv = f32_in_range(m) ? pow2(-f32_exponent(m)) : 1.f;
+        f16 a, b;
+        split16(ok ? vv[j >> 2][j & 3] * dv : 0.f, a, b);
+        sT[0][(dseg + j) * kLdsRow + key] = a;
+        sT[1][(dseg + j) * kLdsRow + key] = b;
+    }
+    __syncthreads();
+    const int d = t >> 2;
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int ch = (t & 3) * 2 + c;
+            *reinterpret_cast<f16x8*>(out + (2 + p) * 8192 + d * 128 + ((ch ^ ((d >> 1) & 7)) << 4)) =
+                *reinterpret_cast<const f16x8*>(&sT[p][d * kLdsRow + ch * 8]);
+        }
+}
+
+// Work items (128 queries of a FULL head) go to the workgroups as in K6a:
+// whole rounds, and the last, partial round cut into one sequence of item-tile
+// steps.  One workgroup = 4 waves x 32 queries; two workgroups per CU, so that one
+// wave's softmax runs beside another's MFMAs.
+__global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__ Q,
+                                                       const int32_t* __restrict__ buckets,
+                                                       int64_t N, int H, int nqt, int nkt, float c,
+                                                       const float* __restrict__ scales,
+                                                       const char* __restrict__ tiles,
+                                                       int32_t* __restrict__ left,
+                                                       float* __restrict__ part, int G,
+                                                       void* __restrict__ Y, int ydt) {
+    const int nfull = full_count(buckets, H);
+    const int active = nfull * nqt;
+    if (active == 0) return;
+    const int w = xcd_remap(blockIdx.x, G);
+    const int full = active / G * G, R = active - full;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n = lane & 31, hh = lane >> 5;
+    __shared__ __attribute__((aligned(1024))) char smem[2 * kTile32];
+    typedef __attribute__((address_space(3))) char lds_char;
+    typedef __attribute__((address_space(3))) const f16x8 lds_frag;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+
+    auto segment = [&](int L, int t0, int t1, int pslot) __attribute__((always_inline)) {
+        const int slot = L / nqt, qt = L - slot * nqt;
+        const int h = full_head(buckets, H, slot);
+        if (h < 0) return;
+        const int64_t qi = (int64_t)qt * kBQ32 + wave * 32 + n;
+        const bool qok = qi < N;
+        const float* sc = scales + slot * kScale32;
+        f32x16 O[2] = {zero_f32x16(), zero_f32x16()};
+        float m = -INFINITY, l = 0.f;
+
+        // Q: features 16 ks + 8 hh .. + 7 of the lane's query, and its scale.
+        f32x4 q[8];
+        {
+            const float* qp = Q + ((qok ? qi : 0) * H + h) * kD + 8 * hh;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                q[i] = *reinterpret_cast<const f32x4*>(qp + 16 * (i >> 1) + 4 * (i & 1));
+                if (!qok) q[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+        uint32_t mq = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mq = max(mq, __float_as_uint(q[i][j]) & 0x7fffffffu);
+        mq = max(mq, (uint32_t)__shfl_xor(mq, 32));
+        // (also the barrier between one segment's LDS reads and the next's writes)
+        const bool exact = __syncthreads_or(!f32_in_range(mq) || sc[kD + 1] != 0.f) != 0;
+        if (t0 == 0 && threadIdx.x == 0) left[L] = exact;
+        if (exact) return;   // uniform over the workgroup
+        const int eq = f32_exponent(mq);
+        const float dq = pow2(-eq), cs = c * sc[kD] * pow2(eq);
+        f16x8 qh[4], ql[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                f16 a, b;
+                split16(q[2 * ks + (j >> 2)][j & 3] * dq, a, b);
+                qh[ks][j] = a;
+                ql[ks][j] = b;
+            }
+        const char* tb = tiles + (int64_t)slot * nkt * kTile32;
+        auto copy = [&](int t, int buf) {   // 8 KB per wave, as it lies
+            const char* src = tb + (int64_t)t * kTile32 + wave * 8192;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                copy_to_lds(lds0 + buf * kTile32 + wave * 8192 + i * 1024, src + i * 1024,
+                            (uint32_t)lane * 16u);
+        };
+        const uint32_t f0 = lds0 + (uint32_t)n * 128u + (uint32_t)((hh ^ ((n >> 1) & 7)) << 4);
+        // chunk 2 k + hh of row 32 blk + n of matrix `mat` (K hi, K lo, V hi, V lo)
+        auto frag = [&](int buf, int mat, int blk, int k) {
+            return *(lds_frag*)(uintptr_t)((f0 ^ (uint32_t)(k << 5)) + buf * kTile32 +
+                                           8192u * mat + 4096u * blk);
+        };
+        copy(t0, 0);
+        for (int t = t0; t < t1; ++t) {
+            const int buf = (t - t0) & 1;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();   // tile t is there; the other buffer's reads are done
+            if (t + 1 < t1) copy(t + 1, buf ^ 1);
+            f32x16 S[2] = {zero_f32x16(), zero_f32x16()};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    S[kb] = mfma_f16(frag(buf, 1, kb, ks), qh[ks], S[kb]);
+            f16x8 kh[4][2];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    kh[ks][kb] = frag(buf, 0, kb, ks);
+                    S[kb] = mfma_f16(kh[ks][kb], ql[ks], S[kb]);
+                }
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) S[kb] = mfma_f16(kh[ks][kb], qh[ks], S[kb]);
+            if ((int64_t)(t + 1) * kBK > N) {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int64_t key =
+                            (int64_t)t * kBK + kb * 32 + 16 * (i >> 3) + 8 * hh + (i & 7);
+                        if (key >= N) S[kb][i] = -INFINITY;
+                    }
+            }
+            float mx = -INFINITY;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[kb][i]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float mn = fmaxf(m, mx * cs);
+            const float al = exp2f_fast(m - mn);
+            m = mn;
+            // The weights are split times 2^14 (the low halves of all but the
+            // smallest are then normal), a factor that O keeps until the
+            // end.  (Added to the exponent it would cost the precision
+            // of an argument near 14.)
+            float ls = 0.f;
+            f16x8 ph[2][2], pl[2][2];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    u32x4 h4, l4;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const f32x2 e = {exp2f_fast(fmaf(S[kb][8 * b + 2 * j], cs, -mn)),
+                                         exp2f_fast(fmaf(S[kb][8 * b + 2 * j + 1], cs, -mn))};
+                        ls += e[0];
+                        ls += e[1];
+                        const f32x2 es = {e[0] * 16384.f, e[1] * 16384.f};
+                        const f16x2 eh = __builtin_convertvector(es, f16x2);
+                        const f32x2 er = {es[0] - (float)eh[0], es[1] - (float)eh[1]};
+                        h4[j] = __builtin_bit_cast(uint32_t, eh);
+                        l4[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(er, f16x2));
+                    }
+                    ph[kb][b] = __builtin_bit_cast(f16x8, h4);
+                    pl[kb][b] = __builtin_bit_cast(f16x8, l4);
+                }
+            l = fmaf(l, al, ls);
+            // Two-level sums: the tile's product is summed from zero,
+            // then added to the running O, so that rounding grows with the
+            // tile count rather than the key count.
+            f32x16 Ot[2] = {zero_f32x16(), zero_f32x16()};
+#pragma unroll
+            for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+                for (int db = 0; db < 2; ++db)
+                    Ot[db] = mfma_f16(frag(buf, 3, db, kc), ph[kc >> 1][kc & 1], Ot[db]);
+            f16x8 vh[4][2];
+#pragma unroll
+            for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+                for (int db = 0; db < 2; ++db) {
+                    vh[kc][db] = frag(buf, 2, db, kc);
+                    Ot[db] = mfma_f16(vh[kc][db], pl[kc >> 1][kc & 1], Ot[db]);
+                }
+#pragma unroll
+            for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+                for (int db = 0; db < 2; ++db)
+                    Ot[db] = mfma_f16(vh[kc][db], ph[kc >> 1][kc & 1], Ot[db]);
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) O[db][r] = fmaf(O[db][r], al, Ot[db][r]);
+        }
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 up = *reinterpret_cast<const f32x4*>(sc + db * 32 + 8 * g + 4 * hh);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) O[db][4 * g + i] *= up[i] * 0x1p-14f;
+            }
+
+        const float lt = l + __shfl_xor(l, 32);
+        if (t0 != 0 || t1 != nkt) {
+            float* pr = part + ((int64_t)(w * 2 + pslot) * kBQ32 + wave * 32 + n) * kRec32;
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<float4*>(pr + db * 32 + 8 * g + 4 * hh) =
+                        make_float4(O[db][4 * g], O[db][4 * g + 1], O[db][4 * g + 2],
+                                    O[db][4 * g + 3]);
+            if (hh == 0) {
+                pr[kD] = lt;
+                pr[kD + 1] = m;
+            }
+            return;
+        }
+        const float inv = 1.f / lt;
+        if (qok) {
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int64_t off = (qi * H + h) * kD + db * 32 + 8 * g + 4 * hh;
+                    const float y0 = O[db][4 * g] * inv, y1 = O[db][4 * g + 1] * inv;
+                    const float y2 = O[db][4 * g + 2] * inv, y3 = O[db][4 * g + 3] * inv;
+                    if (ydt == DT_BF16) {
+                        bf16x4 v;
+                        v[0] = (bf16)y0; v[1] = (bf16)y1; v[2] = (bf16)y2; v[3] = (bf16)y3;
+                        *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(Y) + off) = v;
+                    } else {
+                        *reinterpret_cast<float4*>(reinterpret_cast<float*>(Y) + off) =
+                            make_float4(y0, y1, y2, y3);
+                    }
+                }
+        }
+    };
+
+    for (int L = w; L < full; L += G) segment(L, 0, nkt, 0);
+    if (R > 0) {
+        const int64_t T = (int64_t)R * nkt;
+        const int Gt = tail_groups(T, G, kMinTiles32);
+        if (w < Gt) {
+            const int64_t start = tail_start(w, T, Gt), end = tail_start(w + 1, T, Gt);
+            for (int64_t x = start; x < end;) {
+                const int i = (int)(x / nkt);
+                const int t0 = (int)(x - (int64_t)i * nkt);
+                const int64_t left = end - x;
+                const int t1 = (int64_t)(nkt - t0) < left ? nkt : (int)(t0 + left);
+                segment(full + i, t0, t1, x == start ? 0 : 1);
+                x += t1 - t0;
+            }
+        }
+    }
+}
+
+// K6f: Y of the items that K6e split over workgroups: the parts' O and l scaled to the
+// largest reference point and added in workgroup order (deterministic), then O
+// / l.  Two workgroups of 256 threads per tail item, 4 threads per query and 16 of
+// its values each.
+__global__ __launch_bounds__(256) void k_flash_f32s_combine(const int32_t* __restrict__ buckets,
+                                                            int64_t N, int H, int nqt, int nkt,
+                                                            const int32_t* __restrict__ left,
+                                                            const float* __restrict__ part, int G,
+                                                            void* __restrict__ Y, int ydt) {
+    const int nfull = full_count(buckets, H);
+    const int active = nfull * nqt, full = active / G * G, R = active - full;
+    const int i = blockIdx.x >> 1;
+    if (i >= R) return;
+    const int64_t T = (int64_t)R * nkt;
+    const int Gt = tail_groups(T, G, kMinTiles32);
+    const int wf = tail_owner((int64_t)i * nkt, T, Gt);
+    const int wl = tail_owner((int64_t)(i + 1) * nkt - 1, T, Gt);
+    if (wf == wl || left[full + i]) return;
+    const int L = full + i, slot = L / nqt, qt = L - slot * nqt;
+    const int h = full_head(buckets, H, slot);
+    if (h < 0) return;
+    const int qr = (blockIdx.x & 1) * 64 + (threadIdx.x >> 2), d0 = (threadIdx.x & 3) * 16;
+    const int64_t qi = (int64_t)qt * kBQ32 + qr;
+    if (qi >= N) return;
+    auto rec = [&](int v) {
+        const int k = i == (int)(tail_start(v, T, Gt) / nkt) ? 0 : 1;
+        return part + ((int64_t)(v * 2 + k) * kBQ32 + qr) * kRec32;
+    };
+    float mt = -INFINITY;
+    for (int v = wf; v <= wl; ++v) mt = fmaxf(mt, rec(v)[kD + 1]);
+    float y[16], lt = 0.f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) y[k] = 0.f;
+    for (int v = wf; v <= wl; ++v) {
+        const float* r = rec(v);
+        const float wt = exp2f_fast(r[kD + 1] - mt);
+        lt = fmaf(r[kD], wt, lt);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const f32x4 a = *reinterpret_cast<const f32x4*>(r + d0 + 4 * k);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) y[4 * k + j] = fmaf(a[j], wt, y[4 * k + j]);
+        }
+    }
+    const float inv = 1.f / lt;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) y[k] *= inv;
+    const int64_t yo = (qi * H + h) * kD + d0;
+    if (ydt == DT_BF16) {
+#pragma unroll
+        for (int k8 = 0; k8 < 2; ++k8) {
+            bf16x8 o;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) o[k] = (bf16)y[8 * k8 + k];
+            *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(Y) + yo + 8 * k8) = o;
+        }
+    } else {
+        float* yp = reinterpret_cast<float*>(Y) + yo;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            *reinterpret_cast<float4*>(yp + 4 * k) =
+                make_float4(y[4 * k], y[4 * k + 1], y[4 * k + 2], y[4 * k + 3]);
+    }
+}
+
 // ------------------------------------------------------------------ launchers
 
 int flash_q_tile(int dtype) { return dtype == DT_BF16 ? kBQ16 : kBQ32; }
@@ -1455,17 +1921,36 @@ size_t flash_part_bytes(int64_t N, int H) {
     return (size_t)2 * flash_stream_groups(N, H) * kPartFloats * sizeof(float);
 }
 
-// fp32 layers: two key halves per work item while the items alone would
-// leave the chip short of waves (at most 2 workgroups per CU of them), and
-// the workspace for the halves' records.
-int flash_f32_splits(int64_t N, int H) {
+// fp32 layers.  Up to kSplit32 tokens: K6, with two key halves per work item while
+// the items alone would leave the chip short of waves (at most 2 workgroups
+// per CU of them).  Longer ones: K6e, whose packing and combine launches cost
+// more than it gains on short ones (FULL stage, 8 heads: 768 tokens 38.7 us with K6
+// and 42.0 with K6e; 1,024 tokens 48.9 and 44.8; 1,374 tokens 65 and 50; 2,748
+// tokens 205 and 86; 4,096 tokens 290 and 139).
+constexpr int64_t kSplit32 = 1024;
+static bool f32_split(int64_t N) { return N > kSplit32; }
+static int flash_f32_halves(int64_t N, int H) {
     const int64_t nqt = (N + kBQ32 - 1) / kBQ32, nkt = (N + kBK - 1) / kBK;
     return nqt * H <= 2 * kStreamWG && nkt >= 2 ? 2 : 1;
 }
+// Bytes of the partial results (K6's halves, or two part slots per workgroup
+// that K6e's tail can use), of K6e's flags, maxima and scales, and of its tiles.
 size_t flash_f32_part_bytes(int64_t N, int H) {
-    if (flash_f32_splits(N, H) == 1) return 0;
-    const int64_t nqt = (N + kBQ32 - 1) / kBQ32;
-    return (size_t)H * nqt * 2 * kBQ32 * kRec32 * sizeof(float);
+    const int64_t nqt = (N + kBQ32 - 1) / kBQ32, nkt = (N + kBK - 1) / kBK;
+    if (!f32_split(N))
+        return flash_f32_halves(N, H) == 1
+                   ? 0 : (size_t)H * nqt * 2 * kBQ32 * kRec32 * sizeof(float);
+    const int64_t most = nqt * H < kWG32 ? nqt * H : kWG32 - 1;   // tail items
+    return (size_t)2 * tail_groups(most * nkt, kWG32, kMinTiles32) * kBQ32 * kRec32 * sizeof(float);
+}
+static int flash_f32_groups(int64_t N) { return (int)((N + f32_group_rows(N) - 1) / f32_group_rows(N)); }
+size_t flash_f32_max_bytes(int64_t N, int H) {
+    if (!f32_split(N)) return 0;
+    return (size_t)H * (flash_f32_groups(N) * kMax32 + kScale32 + (N + kBQ32 - 1) / kBQ32) * 4;
+}
+size_t flash_f32_tile_bytes(int64_t N, int H) {
+    if (!f32_split(N)) return 0;
+    return (size_t)H * ((N + kBK - 1) / kBK) * kTile32;
 }
 
 int64_t flash_vmax_parts(int64_t N) {
@@ -1503,14 +1988,34 @@ void launch_flash(const AttnArgs& a, hipStream_t st) {
                            dim3(nqt * a.H), dim3(256), 0, st, (const bf16*)a.Q, (const bf16*)a.K,
                            (const f16*)a.vt, (const float*)a.kmax, (const float*)a.vsc, a.buckets,
                            a.N, a.H, nqt, nkt, c, a.qflag, nqf, a.Y, a.ydt, a.off);
-    } else {
-        const int splits = flash_f32_splits(a.N, a.H);
+    } else if (!f32_split(a.N)) {
+        const int splits = flash_f32_halves(a.N, a.H);
         hipLaunchKernelGGL(k_flash_f32, dim3(nqt * a.H * splits), dim3(256), 0, st,
                            (const float*)a.Q, (const float*)a.K, (const float*)a.V, a.buckets,
-                           a.N, a.H, nqt, nkt, c, splits, a.part, a.Y, a.ydt);
+                           a.N, a.H, nqt, nkt, c, splits, (const int32_t*)nullptr, a.part, a.Y,
+                           a.ydt);
         if (splits > 1)
             hipLaunchKernelGGL(k_flash_f32_combine, dim3(nqt * a.H * 2), dim3(256), 0, st,
                                a.buckets, a.N, a.H, nqt, (const float*)a.part, a.Y, a.ydt);
+    } else {
+        const int ng = flash_f32_groups(a.N);
+        uint32_t* mx = (uint32_t*)a.fmax;
+        float* scales = a.fmax + (size_t)a.H * ng * kMax32;
+        int32_t* left = (int32_t*)(scales + (size_t)a.H * kScale32);
+        hipLaunchKernelGGL(k_absmax_f32, dim3(ng, a.H), dim3(256), 0, st, (const float*)a.K,
+                           (const float*)a.V, a.buckets, a.N, a.H, mx);
+        hipLaunchKernelGGL(k_pack_f32, dim3(nkt, a.H), dim3(256), 0, st, (const float*)a.K,
+                           (const float*)a.V, a.buckets, a.N, a.H, nkt, (const uint32_t*)mx, ng,
+                           scales, (char*)a.ftiles);
+        hipLaunchKernelGGL(k_flash_f32s, dim3(kWG32), dim3(256), 0, st, (const float*)a.Q,
+                           a.buckets, a.N, a.H, nqt, nkt, c, (const float*)scales,
+                           (const char*)a.ftiles, left, a.part, kWG32, a.Y, a.ydt);
+        hipLaunchKernelGGL(k_flash_f32s_combine, dim3(2 * (nqt * a.H < kWG32 ? nqt * a.H : kWG32)),
+                           dim3(256), 0, st, a.buckets, a.N, a.H, nqt, nkt, (const int32_t*)left,
+                           (const float*)a.part, kWG32, a.Y, a.ydt);
+        hipLaunchKernelGGL(k_flash_f32, dim3(nqt * a.H), dim3(256), 0, st, (const float*)a.Q,
+                           (const float*)a.K, (const float*)a.V, a.buckets, a.N, a.H, nqt, nkt, c,
+                           1, (const int32_t*)left, (float*)nullptr, a.Y, a.ydt);
     }
 }
 

@@ -27,7 +27,7 @@ struct Layout {
     int64_t N;
     int64_t n1, chunk1, n2, chunk2, nkt, n3, chunk3;
     size_t off_part1, off_part2, off_vt, off_kh, off_kmax, off_vpart, off_vsc, off_qflag,
-        off_fpart, off_lpart, off_lsum, total;
+        off_fpart, off_fmax, off_ftiles, off_lpart, off_lsum, total;
 };
 
 // Chunking of the router reductions and the workspace carve-up; a pure
@@ -74,6 +74,10 @@ bool make_layout(const vp_shape* s, Layout* L) {
     L->off_fpart = off;
     off = align_up(off + (s->dtype == VP_BF16 ? vp::flash_part_bytes(N, (int)s->H)
                                               : vp::flash_f32_part_bytes(N, (int)s->H)));
+    L->off_fmax = off;
+    if (s->dtype == VP_F32) off = align_up(off + vp::flash_f32_max_bytes(N, (int)s->H));
+    L->off_ftiles = off;
+    if (s->dtype == VP_F32) off = align_up(off + vp::flash_f32_tile_bytes(N, (int)s->H));
     L->off_lpart = off;
     off = align_up(off + (size_t)L->n3 * s->H * vp::kLinSums * sizeof(float));
     L->off_lsum = off;
@@ -352,6 +356,8 @@ vp::AttnArgs attn_args(const vp_shape* shape, const Layout& L, const void* Q, co
     a.vsc = ws ? (float*)((char*)ws + L.off_vsc) : nullptr;
     a.qflag = ws ? (int32_t*)((char*)ws + L.off_qflag) : nullptr;
     a.part = ws ? (float*)((char*)ws + L.off_fpart) : nullptr;
+    a.fmax = ws ? (float*)((char*)ws + L.off_fmax) : nullptr;
+    a.ftiles = ws ? (char*)ws + L.off_ftiles : nullptr;
     a.n3 = L.n3;
     a.chunk3 = L.chunk3;
     a.lpart = ws ? (float*)((char*)ws + L.off_lpart) : nullptr;

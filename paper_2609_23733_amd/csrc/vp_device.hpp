@@ -133,6 +133,16 @@ __device__ __forceinline__ bf16x8 pack_bf16x8(float a0, float a1, float a2, floa
     return r;
 }
 
+// 64 lanes x 16 bytes from base + voff (per lane) to 1 KB of LDS at byte `lds`
+// (uniform).  The copy is counted in vmcnt by issue order; callers wait for it
+// with explicit counts.
+__device__ __forceinline__ void copy_to_lds(uint32_t lds, const char* base, uint32_t voff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds), "v"(voff), "s"(base)
+                 : "memory");
+}
+
 // Remap a linear work index so that consecutive work items land on the same
 // XCD.  The dispatcher assigns workgroup i to XCD i % 8; item k of XCD x then
 // receives work index x * q + min(x, r) + k over `active` items (q = active / 8,

@@ -34,7 +34,9 @@ struct AttnArgs {
     void* kh;      // packed K tiles of FULL heads, fp16 (bf16 only)
     float* kmax;   // per (FULL slot, 64-key tile): max key norm (bf16 only)
     int32_t* qflag;  // per FULL-head work item: needs the running reference point (bf16 only)
-    float* part;     // stream-K partial results of the FULL-head kernel (bf16 only)
+    float* part;     // stream-K partial results of the FULL-head kernel
+    float* fmax;     // maxima and scales of the FULL heads' K and V (fp32 only)
+    void* ftiles;    // their packed tiles (fp32 only)
     void* Y;
     const float *ctx, *vmean;
     const void *g_w1, *g_w2, *d_w1, *d_w2;
@@ -162,8 +164,9 @@ void launch_linear_heads(const AttnArgs& a, hipStream_t st);
 int flash_q_tile(int dtype);
 int flash_stream_groups(int64_t N, int H);
 size_t flash_part_bytes(int64_t N, int H);
-int flash_f32_splits(int64_t N, int H);
 size_t flash_f32_part_bytes(int64_t N, int H);
+size_t flash_f32_max_bytes(int64_t N, int H);
+size_t flash_f32_tile_bytes(int64_t N, int H);
 int64_t flash_vmax_parts(int64_t N);
 
 }  // namespace vp

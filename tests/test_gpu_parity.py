@@ -179,6 +179,43 @@ def test_pooling_weight_scale(dtype, wscale):
             label="pool w x%g %s" % (wscale, dtype))
 
 
+@pytest.mark.parametrize("case,P", [("plain", 1025), ("plain", 1088), ("plain", 1151),
+                                    ("columns", 1100), ("huge", 1100), ("one inf", 1100)])
+def test_fp32_split_full_heads(case, P):
+    """fp32 FULL heads past 1,024 tokens (operands as sums of two fp16 values)
+    against the oracle, every row: token counts on both sides of whole 64-key tiles
+    and 128-query items; V's features over 15 decades (each keeps its own
+    precision); K and V past the split's range, and one infinite value of V, whose
+    heads run on fp32 MFMAs.  Per feature, 2-norm error <= 1e-6 of its norm
+    plus 2e-7 of sqrt(1 / N) |v| (a feature's near-uniform average cancels to
+    that size): exp2 to 1 ulp and sums of N weights, each rounded to 2^-24, leave
+    a few 1e-7 (3e-7 observed with fp32 MFMAs)."""
+    from paper_2609_23733_amd import vp
+    log("fp32 split %s P=%d" % (case, P))
+    x = synth.make_layer(1, P, dtype="f32", n_full=5, n_surr=0, key=(61, P), sharp=True)
+    heads = np.nonzero(x.modes == 2)[0]
+    if case == "columns":
+        x.V *= torch.logspace(-12, 3, 64)
+    elif case == "huge":
+        x.K *= 2.0 ** 70
+        x.Q *= 2.0 ** -70
+        x.V *= 2.0 ** 80
+    elif case == "one inf":
+        x.V[17, int(heads[1]), 5] = float("inf")
+    layer = run_gpu(x, y_dtype=torch.float32)
+    Y = layer.Y.double().cpu().numpy()
+    for h in heads:
+        ref = oracle.full_rows(x.Q, x.K, x.V, int(h))
+        g = Y[:, h, :]
+        if case == "one inf" and h == heads[1]:
+            assert not np.isfinite(g[:, 5]).any()
+            g, ref = np.delete(g, 5, 1), np.delete(ref, 5, 1)
+        scale = np.abs(x.V[:, int(h)].double().numpy()).max(0) if case != "one inf" else 1.0
+        err = np.linalg.norm(g - ref, axis=0)
+        bound = 1e-6 * np.linalg.norm(ref, axis=0) + (2e-7 * scale if case != "one inf" else 2e-7)
+        assert (err <= bound).all(), (case, int(h), float((err / bound).max()))
+
+
 def test_single_token():
     """N = 1: FULL returns v, MEAN returns v, s = 1 (every head FULL under Eq.4)."""
     log("N=1")
