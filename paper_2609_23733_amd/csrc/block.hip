@@ -132,17 +132,6 @@ struct GemmArgs {
     float log2_base;      // QKV: log2 of the rotary base
 };
 
-// Exchange between the lane halves of a 32x32 block's registers.  In the MFMA
-// layout lane half hh holds features 8 g + 4 hh + (0..3) of group g, two
-// dwords of bf16 each; afterwards, for groups (0, 1) and (2, 3), half hh holds
-// the eight consecutive features 8 (2 p + hh) .. + 7 of pair p, one 16-byte
-// access.  The exchange is its own inverse.
-__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
-
 // Epilogue of a wave's 128 features f0 + 128 wm .. x 64 tokens t0 + 64 wn ..
 // The outputs pass through 4 KB of LDS that only this wave uses at that time
 // (32 rows of 128 bytes, row r at scratch + 8192 (r / 8) + 128 (r % 8), 16-byte

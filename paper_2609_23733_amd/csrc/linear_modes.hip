@@ -373,59 +373,86 @@ __global__ __launch_bounds__(256) void k_broadcast_heads(const uint8_t* __restri
 // Table 6; Katharopoulos et al.), non-causal over all N tokens with
 // phi(x) = elu(x) + 1:  y_i = phi(q_i)^T S / phi(q_i) . z with
 // S = sum_j phi(k_j) v_j^T (64 x 64) and z = sum_j phi(k_j).
-// Both contractions run on the fp32 MFMA (32x32x2: exact fp32 products,
-// operands taken straight from the row-major [N, H, 64] rows), sums in fp32:
+// Sums in fp32.  fp32 layers: both contractions on the fp32 MFMA (32x32x2: exact
+// fp32 products, operands taken straight from the row-major [N, H, 64] rows).
+// bf16 layers: fp32 values as exact sums of three bf16 values (split3) on the
+// bf16 MFMA, which takes a sixteenth of the time per product: v is bf16, so phi(k)
+// v^T is three products, every one exact; phi(q)^T S takes the six products of
+// at least 2^-16 of the largest (the others are below 2^-24).
 //   K10a  per (token chunk, head): partial S and z of the chunk;
-//   K10b  per head: S and z summed over the chunks in chunk order;
+//   K10b  per head: S and z summed over the chunks;
 //   K10c  per (32-query block, head): y_i.
+// bf16, 137,400 tokens, 6 heads, us: K10a 138 -> 79, K10b 34 -> 5.6 (more loads in flight),
+// K10c 121 -> 67 (fp32 MFMAs before); 42 each would be the HBM rate.
 // ------------------------------------------------------------------------
 __device__ __forceinline__ float elu1(float x) {
     return x > 0.f ? x + 1.f : exp2f_fast(x * kLog2e);
 }
 
-// Elements 2c and 2c + 1 of the 64-value row starting at element `off`.
-template <int DT>
-__device__ __forceinline__ float2 load_pair(const void* __restrict__ X, int64_t off, int c) {
-    if (DT == DT_BF16) {
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(
-            reinterpret_cast<const bf16*>(X) + off + 2 * c);
-        const bf16x2 v = __builtin_bit_cast(bf16x2, w);
-        return make_float2(bf16_to_f32(v[0]), bf16_to_f32(v[1]));
-    }
-    return *reinterpret_cast<const float2*>(reinterpret_cast<const float*>(X) + off + 2 * c);
-}
-
-// 32 consecutive values of a row, as fp32.
-template <int DT>
-__device__ __forceinline__ void load32(const void* __restrict__ X, int64_t off, float* o) {
-    if (DT == DT_BF16) {
-        const bf16* p = reinterpret_cast<const bf16*>(X) + off;
+// x = b[0] + b[1] + b[2] exactly (24 significant bits; x finite and not so small
+// that the last part is subnormal), for eight values.
+__device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&b)[3]) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bf16x8 v = load_bf16x8(p + 8 * k);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) o[8 * k + j] = bf16_to_f32(v[j]);
-        }
-    } else {
-        const float4* p = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(X) + off);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float4 v = p[k];
-            o[4 * k] = v.x; o[4 * k + 1] = v.y; o[4 * k + 2] = v.z; o[4 * k + 3] = v.w;
-        }
+    for (int j = 0; j < 8; ++j) {
+        const bf16 b0 = (bf16)x[j];
+        const float r1 = x[j] - (float)b0;
+        const bf16 b1 = (bf16)r1;
+        b[0][j] = b0;
+        b[1][j] = b1;
+        b[2][j] = (bf16)(r1 - (float)b1);
     }
 }
 
-// K10a.  S^T blocks on MFMA with the token pair as the reduction index:
+// 32 consecutive values of a row.
+__device__ __forceinline__ void load32(const float* __restrict__ X, float* o) {
+    const float4* p = reinterpret_cast<const float4*>(X);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const float4 v = p[k];
+        o[4 * k] = v.x; o[4 * k + 1] = v.y; o[4 * k + 2] = v.z; o[4 * k + 3] = v.w;
+    }
+}
+
+// The four waves' blocks and z sums, added in wave order, to o (S then z).
+__device__ __forceinline__ void lin_reduce(const f32x16 (&acc)[2][2], const float (&zacc)[2], int wave,
+                                           int n, int hh, float* __restrict__ o) {
+    __shared__ float sP[kD * kD + kD];   // S then z
+#pragma unroll 1
+    for (int wv = 0; wv < 4; ++wv) {
+        if (wave == wv) {
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int m = 8 * (r >> 2) + 4 * hh + (r & 3);
+                        float* d = &sP[(2 * m + mb) * kD + 2 * n + nb];
+                        *d = wv == 0 ? acc[mb][nb][r] : *d + acc[mb][nb][r];
+                    }
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                const float zt = zacc[mb] + __shfl_xor(zacc[mb], 32);
+                if (hh == 0) {
+                    float* d = &sP[kD * kD + 2 * n + mb];
+                    *d = wv == 0 ? zt : *d + zt;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < kLinSums; e += 256) o[e] = sP[e];
+}
+
+// K10a (fp32 layers).  S^T blocks on MFMA with the token pair as the reduction index:
 // A[m][k] = phi(k_{t+k})[2m + mb], B[k][n] = v_{t+k}[2n + nb], so that a lane
 // reads one 4-byte pair per row and 32 lanes one whole 128-byte row.  Block
 // (mb, nb) register r of lane l then holds S[2m + mb][2n + nb] with
 // n = l % 32, m = 8 (r / 4) + 4 (l / 32) + r % 4.  Wave w takes token pairs
 // w, w + 4, ..., four per step with the next step's rows already loading; the
 // four waves' sums meet in one 16 KB LDS buffer, added in wave order.
-template <int DT>
-__global__ __launch_bounds__(256) void k_linattn_partial(const void* __restrict__ K,
-                                                         const void* __restrict__ V,
+__global__ __launch_bounds__(256) void k_linattn_partial(const float* __restrict__ K,
+                                                         const float* __restrict__ V,
                                                          const uint8_t* __restrict__ modes,
                                                          int64_t N, int H, int64_t chunk,
                                                          float* __restrict__ part) {
@@ -450,8 +477,8 @@ __global__ __launch_bounds__(256) void k_linattn_partial(const void* __restrict_
             ka[u] = vb[u] = make_float2(0.f, 0.f);
             if (tok < t1) {
                 const int64_t off = (tok * H + h) * kD;
-                ka[u] = load_pair<DT>(K, off, n);
-                vb[u] = load_pair<DT>(V, off, n);
+                ka[u] = *reinterpret_cast<const float2*>(K + off + 2 * n);
+                vb[u] = *reinterpret_cast<const float2*>(V + off + 2 * n);
             }
         }
     };
@@ -478,50 +505,153 @@ __global__ __launch_bounds__(256) void k_linattn_partial(const void* __restrict_
             acc[1][1] = mfma_f32(a[u].y, b[u].y, acc[1][1]);
         }
     }
-    __shared__ float sP[kD * kD + kD];   // S then z
-#pragma unroll 1
-    for (int wv = 0; wv < 4; ++wv) {
-        if (wave == wv) {
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int m = 8 * (r >> 2) + 4 * hh + (r & 3);
-                        float* d = &sP[(2 * m + mb) * kD + 2 * n + nb];
-                        *d = wv == 0 ? acc[mb][nb][r] : *d + acc[mb][nb][r];
-                    }
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb) {
-                const float zt = zacc[mb] + __shfl_xor(zacc[mb], 32);
-                if (hh == 0) {
-                    float* d = &sP[kD * kD + 2 * n + mb];
-                    *d = wv == 0 ? zt : *d + zt;
-                }
-            }
-        }
-        __syncthreads();
-    }
-    float* o = part + ((int64_t)h * gridDim.x + c) * kLinSums;
-    for (int e = threadIdx.x; e < kLinSums; e += 256) o[e] = sP[e];
+    lin_reduce(acc, zacc, wave, n, hh, part + ((int64_t)h * gridDim.x + c) * kLinSums);
 }
 
-// K10b.  Grid (cdiv(kLinSums, 256), H): one sum per thread, chunks in order.
+// K10a for bf16 layers: the same blocks on 32x32x16 bf16 MFMAs, 16 tokens per
+// step: lane l holds features 2n and 2n + 1 of tokens 8 (l / 32) .. + 7, each token's
+// 128-byte row read whole by 32 lanes.  Wave w takes the chunk's 16-token steps w,
+// w + 4, ..., the next step's rows loading meanwhile.  The low parts have sums
+// of their own, so that the main ones round once per 16 tokens (in one sum the
+// layer's error at 137,400 tokens was 1.95e-7 of the output norm; so it is 1.16e-7, with
+// the fp32 MFMA 1.5e-7).  (An infinity does not split: a
+// chunk whose sums are not all finite is summed again on fp32 MFMAs, whose
+// infinities and NaNs are those of the plain sum.)
+__global__ __launch_bounds__(256) void k_linattn_partial_bf16(const bf16* __restrict__ K,
+                                                              const bf16* __restrict__ V,
+                                                              const uint8_t* __restrict__ modes,
+                                                              int64_t N, int H, int64_t chunk,
+                                                              float* __restrict__ part) {
+    const int h = blockIdx.y, c = blockIdx.x;
+    if (modes[h] != MODE_SURR) return;
+    const int64_t t0 = (int64_t)c * chunk;
+    const int64_t t1 = (t0 + chunk < N) ? t0 + chunk : N;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n = lane & 31, hh = lane >> 5;
+    f32x16 acc[2][2], lo[2][2];
+    float zacc[2] = {0.f, 0.f};
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) acc[mb][0] = acc[mb][1] = lo[mb][0] = lo[mb][1] = zero_f32x16();
+    uint32_t kw[8], vw[8], kn[8], vn[8];
+    const int64_t rstride = (int64_t)H * kD;
+    auto load = [&](int64_t tg, uint32_t (&k)[8], uint32_t (&v)[8]) {   // rows past t1: row t1 - 1
+        const int64_t last = t1 - 1;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t tok = tg + 8 * hh + j;
+            const int64_t o = (tok < t1 ? tok : last) * rstride + h * kD + 2 * n;
+            k[j] = *reinterpret_cast<const uint32_t*>(K + o);
+            v[j] = *reinterpret_cast<const uint32_t*>(V + o);
+        }
+    };
+    int64_t tg = t0 + 16 * wave;
+    if (tg < t1) load(tg, kn, vn);
+    for (; tg < t1; tg += 64) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            kw[j] = kn[j];
+            vw[j] = vn[j];
+        }
+        if (tg + 64 < t1) load(tg + 64, kn, vn);
+        float f[2][8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            f[0][j] = elu1(__uint_as_float(kw[j] << 16));
+            f[1][j] = elu1(__uint_as_float(kw[j] & 0xffff0000u));
+        }
+        if (tg + 16 > t1) {   // tokens past the chunk: phi = 0, v = 0
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (tg + 8 * hh + j >= t1) {
+                    f[0][j] = f[1][j] = 0.f;
+                    vw[j] = 0;
+                }
+        }
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) zacc[mb] += f[mb][j];
+        u32x4 b[2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            b[0][j] = (vw[2 * j] & 0xffffu) | (vw[2 * j + 1] << 16);
+            b[1][j] = (vw[2 * j] >> 16) | (vw[2 * j + 1] & 0xffff0000u);
+        }
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+            bf16x8 a[3];
+            split3(f[mb], a);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                const bf16x8 v = __builtin_bit_cast(bf16x8, b[nb]);
+                lo[mb][nb] = mfma_bf16(a[2], v, lo[mb][nb]);
+                lo[mb][nb] = mfma_bf16(a[1], v, lo[mb][nb]);
+                acc[mb][nb] = mfma_bf16(a[0], v, acc[mb][nb]);
+            }
+        }
+    }
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mb][nb][r] += lo[mb][nb][r];
+    bool bad = !(fabsf(zacc[0]) < INFINITY) || !(fabsf(zacc[1]) < INFINITY);
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[mb][nb][r]) < INFINITY);
+    if (__syncthreads_or(bad)) {
+        zacc[0] = zacc[1] = 0.f;
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) acc[mb][0] = acc[mb][1] = zero_f32x16();
+#pragma unroll 1
+        for (int64_t t = t0 + 2 * wave; t < t1; t += 8) {
+            float f[2] = {0.f, 0.f}, v[2] = {0.f, 0.f};
+            if (t + hh < t1) {
+                const int64_t o = (t + hh) * rstride + h * kD + 2 * n;
+                const uint32_t k = *reinterpret_cast<const uint32_t*>(K + o);
+                const uint32_t w = *reinterpret_cast<const uint32_t*>(V + o);
+                f[0] = elu1(__uint_as_float(k << 16));
+                f[1] = elu1(__uint_as_float(k & 0xffff0000u));
+                v[0] = __uint_as_float(w << 16);
+                v[1] = __uint_as_float(w & 0xffff0000u);
+            }
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                zacc[mb] += f[mb];
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma_f32(f[mb], v[nb], acc[mb][nb]);
+            }
+        }
+    }
+    lin_reduce(acc, zacc, wave, n, hh, part + ((int64_t)h * gridDim.x + c) * kLinSums);
+}
+
+// K10b.  Grid (cdiv(kLinSums, 64), H): one sum per 64 threads' lane, four groups of
+// chunks (each in order, then the groups in order).
 __global__ __launch_bounds__(256) void k_linattn_combine(const uint8_t* __restrict__ modes,
                                                          const float* __restrict__ part,
                                                          int nchunks, float* __restrict__ sums) {
     const int h = blockIdx.y;
     if (modes[h] != MODE_SURR) return;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= kLinSums) return;
-    const float* p = part + (int64_t)h * nchunks * kLinSums + i;
+    const int g = threadIdx.x >> 6, l = threadIdx.x & 63, i = blockIdx.x * 64 + l;
+    __shared__ float s[4][64];
     float acc = 0.f;
-    for (int c = 0; c < nchunks; ++c) acc += p[(int64_t)c * kLinSums];
-    sums[h * kLinSums + i] = acc;
+    if (i < kLinSums) {
+        const float* p = part + (int64_t)h * nchunks * kLinSums + i;
+        const int q = (nchunks + 3) / 4, c1 = (g + 1) * q < nchunks ? (g + 1) * q : nchunks;
+#pragma unroll 8
+        for (int c = g * q; c < c1; ++c) acc += p[(int64_t)c * kLinSums];
+    }
+    s[g][l] = acc;
+    __syncthreads();
+    if (g == 0 && i < kLinSums) sums[h * kLinSums + i] = (s[0][l] + s[1][l]) + (s[2][l] + s[3][l]);
 }
 
-// K10c.  Y^T = S^T phi(Q)^T per 32-query block on MFMA: reduction step s
+// K10c (fp32 layers).  Y^T = S^T phi(Q)^T per 32-query block on MFMA: reduction step s
 // covers features s and s + 32 (k = l / 32 picks one), so lane l needs the
 // contiguous half-row [32 (l / 32), 32 (l / 32) + 32) of its query l % 32,
 // and A[m][k] = S[s + 32 k][32 db + m] stays in registers for every block.
@@ -530,8 +660,7 @@ __global__ __launch_bounds__(256) void k_linattn_combine(const uint8_t* __restri
 // queries.
 constexpr int kLinQBlocks = 4;
 
-template <int DT>
-__global__ __launch_bounds__(256) void k_linattn_apply(const void* __restrict__ Q,
+__global__ __launch_bounds__(256) void k_linattn_apply(const float* __restrict__ Q,
                                                        const uint8_t* __restrict__ modes,
                                                        const float* __restrict__ sums, int64_t N,
                                                        int H, void* __restrict__ Y, int ydt) {
@@ -558,7 +687,7 @@ __global__ __launch_bounds__(256) void k_linattn_apply(const void* __restrict__ 
         return ((qi < N ? qi : q0) * H + h) * kD + 32 * hh;
     };
     float fn[32];
-    if (first * 32 < N) load32<DT>(Q, qrow(0), fn);
+    if (first * 32 < N) load32(Q + qrow(0), fn);
     for (int qb = 0; qb < kLinQBlocks; ++qb) {
         const int64_t q0 = (first + qb) * 32;
         if (q0 >= N) break;
@@ -567,7 +696,7 @@ __global__ __launch_bounds__(256) void k_linattn_apply(const void* __restrict__ 
         float fq[32];
 #pragma unroll
         for (int s = 0; s < 32; ++s) fq[s] = fn[s];
-        if (qb + 1 < kLinQBlocks && q0 + 32 < N) load32<DT>(Q, qrow(qb + 1), fn);
+        if (qb + 1 < kLinQBlocks && q0 + 32 < N) load32(Q + qrow(qb + 1), fn);
         float den = 0.f;
 #pragma unroll
         for (int s = 0; s < 32; ++s) {
@@ -599,6 +728,138 @@ __global__ __launch_bounds__(256) void k_linattn_apply(const void* __restrict__ 
                             make_float4(y0, y1, y2, y3);
                     }
                 }
+        }
+    }
+}
+
+// K10c for bf16 layers, on 32x32x16 bf16 MFMAs: S^T split once per workgroup into LDS
+// (three 64 x 64 matrices, rows dv), phi(Q) split per block in registers: lane l holds
+// features 16 ks + 8 (l / 32) .. + 7 of query l % 32.  (Sums that are not all finite
+// stay on fp32 MFMAs.)
+__global__ __launch_bounds__(256, 4) void k_linattn_apply_bf16(const bf16* __restrict__ Q,
+                                                            const uint8_t* __restrict__ modes,
+                                                            const float* __restrict__ sums, int64_t N,
+                                                            int H, void* __restrict__ Y, int ydt) {
+    const int h = blockIdx.y;
+    if (modes[h] != MODE_SURR) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int n = lane & 31, hh = lane >> 5;
+    __shared__ __attribute__((aligned(16))) bf16 sS[3][kD * kW];
+    __shared__ __attribute__((aligned(16))) float sz[kD];
+    const float* sh = sums + h * kLinSums;
+    bool bad = false;
+    {
+        const int dv = threadIdx.x & 63, dk0 = (threadIdx.x >> 6) * 16;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            float x[8];
+            bf16x8 b[3];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                x[j] = sh[(dk0 + 8 * c + j) * kD + dv];
+                bad |= !(fabsf(x[j]) < INFINITY);
+            }
+            split3(x, b);
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                *reinterpret_cast<bf16x8*>(&sS[p][dv * kW + dk0 + 8 * c]) = b[p];
+        }
+        if (threadIdx.x < kD) sz[threadIdx.x] = sh[kD * kD + threadIdx.x];
+    }
+    bad = __syncthreads_or(bad) != 0;
+    const int64_t first = (int64_t)blockIdx.x * 4 * kLinQBlocks + wave * kLinQBlocks;
+    bf16x8 qn[4];
+    auto load = [&](int qb) {   // (rows past N - 1: row N - 1)
+        const int64_t qi = (first + qb) * 32 + n;
+        const bf16* p = Q + ((qi < N ? qi : N - 1) * H + h) * kD + 8 * hh;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) qn[ks] = load_bf16x8(p + 16 * ks);
+    };
+    if (first * 32 < N) load(0);
+#pragma unroll 1
+    for (int qb = 0; qb < kLinQBlocks; ++qb) {
+        const int64_t q0 = (first + qb) * 32;
+        if (q0 >= N) break;
+        const int64_t qi = q0 + n;
+        bf16x8 qc[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) qc[ks] = qn[ks];
+        if (qb + 1 < kLinQBlocks && q0 + 32 < N) load(qb + 1);
+        float den = 0.f;
+        f32x16 y[2] = {zero_f32x16(), zero_f32x16()};
+        if (bad) {   // fp32 MFMA step (ks, j): features 16 ks + j and 16 ks + 8 + j
+#pragma unroll 1
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll 1
+                for (int j = 0; j < 8; ++j) {
+                    const int dk = 16 * ks + 8 * hh + j;
+                    const float f = elu1(bf16_to_f32(Q[((qi < N ? qi : N - 1) * H + h) * kD + dk]));
+                    den = fmaf(f, sz[dk], den);
+#pragma unroll
+                    for (int db = 0; db < 2; ++db)
+                        y[db] = mfma_f32(sh[dk * kD + 32 * db + n], f, y[db]);
+                }
+        } else
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            float f[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = elu1(bf16_to_f32(qc[ks][j]));
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const f32x4 z = *reinterpret_cast<const f32x4*>(&sz[16 * ks + 8 * hh + 4 * c]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) den = fmaf(f[4 * c + j], z[j], den);
+            }
+            bf16x8 b[3];
+            split3(f, b);
+#pragma unroll
+            for (int db = 0; db < 2; ++db) {
+                bf16x8 a[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    a[p] = *reinterpret_cast<const bf16x8*>(
+                        &sS[p][(32 * db + n) * kW + 16 * ks + 8 * hh]);
+                y[db] = mfma_bf16(a[2], b[0], y[db]);
+                y[db] = mfma_bf16(a[0], b[2], y[db]);
+                y[db] = mfma_bf16(a[1], b[1], y[db]);
+                y[db] = mfma_bf16(a[1], b[0], y[db]);
+                y[db] = mfma_bf16(a[0], b[1], y[db]);
+                y[db] = mfma_bf16(a[0], b[0], y[db]);
+            }
+        }
+        den += __shfl_xor(den, 32);
+        const float inv = 1.f / den;
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+            const int64_t off = (qi * H + h) * kD + 32 * db;
+            if (ydt == DT_BF16) {
+                // 16-byte stores: the lane halves exchange registers first
+                // (all lanes take part).
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    u32x4 o;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const int r = 8 * p + 2 * k;
+                        const bf16x2 u = {(bf16)(y[db][r] * inv), (bf16)(y[db][r + 1] * inv)};
+                        const bf16x2 v = {(bf16)(y[db][r + 4] * inv), (bf16)(y[db][r + 5] * inv)};
+                        uint32_t x0 = __builtin_bit_cast(uint32_t, u);
+                        uint32_t x1 = __builtin_bit_cast(uint32_t, v);
+                        swap_halves(x0, x1);
+                        o[k] = x0;
+                        o[2 + k] = x1;
+                    }
+                    if (qi < N)
+                        *reinterpret_cast<u32x4*>(reinterpret_cast<bf16*>(Y) + off + 16 * p + 8 * hh) = o;
+                }
+            } else if (qi < N) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<float4*>(reinterpret_cast<float*>(Y) + off + 8 * g + 4 * hh) =
+                        make_float4(y[db][4 * g] * inv, y[db][4 * g + 1] * inv,
+                                    y[db][4 * g + 2] * inv, y[db][4 * g + 3] * inv);
+            }
         }
     }
 }
@@ -635,21 +896,21 @@ void launch_linear_heads(const AttnArgs& a, hipStream_t st) {
         hipLaunchKernelGGL(k_broadcast_heads, dim3(nb, a.H), dim3(256), 0, st, a.modes,
                            (int)MODE_SURR, a.ctx, a.N, a.H, a.Y, a.ydt);
     } else {   // SURR_LINEAR_ATTN
-        const dim3 gp((unsigned)a.n3, a.H), gc((kLinSums + 255) / 256, a.H),
+        const dim3 gp((unsigned)a.n3, a.H), gc((kLinSums + 63) / 64, a.H),
             ga((unsigned)((a.N + 32 * 4 * kLinQBlocks - 1) / (32 * 4 * kLinQBlocks)), a.H);
         if (a.dtype == DT_BF16) {
-            hipLaunchKernelGGL(k_linattn_partial<DT_BF16>, gp, dim3(256), 0, st, a.K, a.V,
-                               a.modes, a.N, a.H, a.chunk3, a.lpart);
+            hipLaunchKernelGGL(k_linattn_partial_bf16, gp, dim3(256), 0, st, (const bf16*)a.K,
+                               (const bf16*)a.V, a.modes, a.N, a.H, a.chunk3, a.lpart);
             hipLaunchKernelGGL(k_linattn_combine, gc, dim3(256), 0, st, a.modes, a.lpart,
                                (int)a.n3, a.lsum);
-            hipLaunchKernelGGL(k_linattn_apply<DT_BF16>, ga, dim3(256), 0, st, a.Q, a.modes,
+            hipLaunchKernelGGL(k_linattn_apply_bf16, ga, dim3(256), 0, st, (const bf16*)a.Q, a.modes,
                                a.lsum, a.N, a.H, a.Y, a.ydt);
         } else {
-            hipLaunchKernelGGL(k_linattn_partial<DT_F32>, gp, dim3(256), 0, st, a.K, a.V,
-                               a.modes, a.N, a.H, a.chunk3, a.lpart);
+            hipLaunchKernelGGL(k_linattn_partial, gp, dim3(256), 0, st, (const float*)a.K,
+                               (const float*)a.V, a.modes, a.N, a.H, a.chunk3, a.lpart);
             hipLaunchKernelGGL(k_linattn_combine, gc, dim3(256), 0, st, a.modes, a.lpart,
                                (int)a.n3, a.lsum);
-            hipLaunchKernelGGL(k_linattn_apply<DT_F32>, ga, dim3(256), 0, st, a.Q, a.modes,
+            hipLaunchKernelGGL(k_linattn_apply, ga, dim3(256), 0, st, (const float*)a.Q, a.modes,
                                a.lsum, a.N, a.H, a.Y, a.ydt);
         }
     }

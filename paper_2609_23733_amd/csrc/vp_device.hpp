@@ -133,6 +133,17 @@ __device__ __forceinline__ bf16x8 pack_bf16x8(float a0, float a1, float a2, floa
     return r;
 }
 
+// Exchange between the lane halves of a 32x32 block's registers.  In the MFMA
+// layout lane half hh holds features 8 g + 4 hh + (0..3) of group g, two
+// dwords of bf16 each; afterwards, for groups (0, 1) and (2, 3), half hh holds
+// the eight consecutive features 8 (2 p + hh) .. + 7 of pair p, one 16-byte
+// access.  The exchange is its own inverse.
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
 // 64 lanes x 16 bytes from base + voff (per lane) to 1 KB of LDS at byte `lds`
 // (uniform).  The copy is counted in vmcnt by issue order; callers wait for it
 // with explicit counts.

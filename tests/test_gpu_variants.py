@@ -219,3 +219,34 @@ def test_variants_full_size_sampled(variant, pool):
         if ref["modes"][h] == 2:
             ref["Y"][:, h, :] = ref["Y_full_rows"][h]
     check_y(Yg, ref["Y"], "bf16", True, label="s100 variant %d pool %d" % (variant, pool))
+
+
+@pytest.mark.parametrize("P,bad", [(15, None), (17, None), (255, None), (273, None), (4500, None),
+                                   (700, "v"), (700, "k")])
+def test_linear_attention_split(P, bad):
+    """bf16 linear attention with fp32 output, every row, at token counts around
+    whole 16-token steps and chunks: 2-norm error <= 5e-7 (products exact to
+    2^-24, fp32 sums: 1.2e-7 observed).  An infinite value of V or K reaches the
+    outputs it reaches in the plain sum (one feature as an infinity, or the whole
+    head as NaN) and nothing else."""
+    from paper_2609_23733_amd import vp
+    log("linear attention split P=%d %s" % (P, bad))
+    modes = np.ones(16, np.uint8)
+    x = synth.make_layer(1, P, dtype="bf16", key=(71, P), modes=modes, sharp=True)
+    if bad == "v":
+        x.V[9, 3, 11] = float("inf")
+    elif bad == "k":
+        x.K[9, 3, 11] = float("inf")
+    layer = vp.RoutedLayer(x, y_dtype=torch.float32, surr_variant=vp.SURR_LINEAR_ATTN)
+    layer.step()
+    torch.cuda.synchronize()
+    Y = layer.Y.double().cpu().numpy()
+    for h in (0, 3, 15):
+        g, ref = Y[:, h, :], oracle.linattn_rows(x.Q, x.K, x.V, h)
+        if h == 3 and bad == "k":
+            assert np.isnan(g).all()
+            continue
+        if h == 3 and bad == "v":
+            assert np.isposinf(g[:, 11]).all()
+            g, ref = np.delete(g, 11, 1), np.delete(ref, 11, 1)
+        assert np.linalg.norm(g - ref) <= 5e-7 * np.linalg.norm(ref), (P, h)
