@@ -926,12 +926,101 @@ __global__ __launch_bounds__(512, 1) void k_flash_bf16(const bf16* __restrict__ 
 
 // K6c: Y of the tail items that K6a split over workgroups: the parts' O and
 // l, each relative to its part's reference point m, scaled to the largest m
-// and added in workgroup order (fixed, so results are deterministic), then
-// O 2^e_h / l.  One workgroup of 256 threads per (tail item, 64-query
-// block): 4 threads per query, 16 consecutive values each, so a query's
-// 256-byte row of a part is read whole.  Items that K6a finished whole or
-// left to K6b exit at once.
-constexpr int kCombRows = 64;
+// and added in a fixed order (so results are deterministic), then O 2^e_h / l.
+// Items that K6a finished whole or left to K6b are passed over.
+//
+// Bound by reading the parts, 131 KB each, at most two per workgroup of K6a,
+// and by the latency of a unit's loads.  The number of tail items R is known
+// only on the device (0 .. G - 1), with Gt / R parts or one more each.  With
+// few parts an item has 8 units of 64 queries (4 threads per query, one group).
+// With 8 parts or more it has 64 units of 8 queries (16 threads per query, two
+// groups of threads share the parts, 8 parts in flight): few items then still
+// give enough workgroups, and no thread adds up more than half of the parts.
+// 3 heads of 43,968 tokens (2 items of 128 parts) 87 us with 8 units an item,
+// 14 us with 64; 4 heads of 34,350 tokens (16 items of 16 parts) 20 -> 10 us;
+// 8 heads of 10,992 tokens (176 items of 2 parts) 14 us with 8 units, 30 us
+// with 64 in a persistent loop.  Lines at 8 and 16 parts measured the same.
+constexpr int kCombUnits = 8;   // workgroups per workgroup of K6a
+constexpr int kCombFew = 8;     // fewer than this many parts per item
+
+// One unit: the parts wf .. wl of ROWS queries of an item, dealt to GROUPS
+// groups of threads whose sums are added in order.
+template <int ROWS, int GROUPS>
+__device__ __forceinline__ void combine_parts(const float* __restrict__ part, int wf, int wl,
+                                              int vbase, int qr0, int qt, int64_t N, int H, int h,
+                                              const float* __restrict__ vsc, int slot,
+                                              void* __restrict__ Y, int ydt,
+                                              float* __restrict__ off, float4* s_acc) {
+    constexpr int TPR = 256 / (ROWS * GROUPS), NV = kD / TPR / 4;   // threads, float4s per query
+    const int grp = threadIdx.x / (ROWS * TPR), rl = threadIdx.x % (ROWS * TPR);
+    const int lr = rl % TPR, qr = qr0 + rl / TPR, d0 = lr * 4 * NV;
+    const int64_t qi = (int64_t)qt * kBQf + qr;
+    // Workgroup v's partial slot for this item: its first, unless v began
+    // with an earlier item (only the item's first workgroup can).
+    auto pslot = [&](int v) {
+        return part + (int64_t)(v * 2 + (v == wf ? vbase : 0)) * kPartFloats;
+    };
+    // largest reference point and the sum of l, over the lanes of a query
+    float mt = -INFINITY;
+    for (int v = wf + lr; v <= wl; v += TPR) mt = fmaxf(mt, pslot(v)[kBQf * kD + kBQf + qr]);
+#pragma unroll
+    for (int o = TPR / 2; o >= 1; o >>= 1) mt = fmaxf(mt, __shfl_xor(mt, o));
+    // 2^(m_v - max m): exactly 1 for parts at the largest reference point
+    // (every part of a FAST item has m = 0).
+    float lt = 0.f;
+    for (int v = wf + lr; v <= wl; v += TPR) {
+        const float* ps = pslot(v) + kBQf * kD + qr;
+        lt = fmaf(ps[0], exp2f_fast(ps[kBQf] - mt), lt);
+    }
+#pragma unroll
+    for (int o = TPR / 2; o >= 1; o >>= 1) lt += __shfl_xor(lt, o);
+    float4 acc[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    constexpr int kInFlight = NV == 1 ? 8 : 1;
+#pragma unroll kInFlight
+    for (int v = wf + grp; v <= wl; v += GROUPS) {
+        const float* ps = pslot(v);
+        const float sc = exp2f_fast(ps[kBQf * kD + kBQf + qr] - mt);
+        const float4* src = reinterpret_cast<const float4*>(ps + qr * kD + d0);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const float4 a = src[k];
+            acc[k].x = fmaf(a.x, sc, acc[k].x);
+            acc[k].y = fmaf(a.y, sc, acc[k].y);
+            acc[k].z = fmaf(a.z, sc, acc[k].z);
+            acc[k].w = fmaf(a.w, sc, acc[k].w);
+        }
+    }
+    if (GROUPS > 1) {
+        static_assert(GROUPS == 1 || NV == 1, "one float4 per thread goes through s_acc");
+        if (grp) s_acc[(grp - 1) * ROWS * TPR + rl] = acc[0];
+        __syncthreads();
+        if (grp) return;
+#pragma unroll
+        for (int g = 0; g < GROUPS - 1; ++g) {
+            const float4 b = s_acc[g * ROWS * TPR + rl];
+            acc[0].x += b.x; acc[0].y += b.y; acc[0].z += b.z; acc[0].w += b.w;
+        }
+    }
+    if (qi >= N) return;
+    if (off && lr == 0) off[(int64_t)h * N + qi] = mt + __log2f(lt);
+    const float inv = vsc[2 * slot + 1] / lt;
+    const int64_t yo = (qi * H + h) * kD + d0;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const float4 a = make_float4(acc[k].x * inv, acc[k].y * inv, acc[k].z * inv,
+                                     acc[k].w * inv);
+        if (ydt == DT_BF16) {
+            bf16x4 o;
+            o[0] = (bf16)a.x; o[1] = (bf16)a.y; o[2] = (bf16)a.z; o[3] = (bf16)a.w;
+            *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(Y) + yo + 4 * k) = o;
+        } else {
+            *reinterpret_cast<float4*>(reinterpret_cast<float*>(Y) + yo + 4 * k) = a;
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void k_flash_combine(const int32_t* __restrict__ buckets,
                                                        int64_t N, int H, int nqt, int nkt,
                                                        const int32_t* __restrict__ exact_items,
@@ -939,69 +1028,35 @@ __global__ __launch_bounds__(256) void k_flash_combine(const int32_t* __restrict
                                                        const float* __restrict__ vsc, int G,
                                                        void* __restrict__ Y, int ydt,
                                                        float* __restrict__ off) {
+    __shared__ float4 s_acc[128];
     const int nfull = full_count(buckets, H);
     const int active = nfull * nqt;
     const int full = active / G * G, R = active - full;
-    const int i = blockIdx.x / (kBQf / kCombRows), rb = blockIdx.x % (kBQf / kCombRows);
-    if (i >= R) return;
+    if (R == 0) return;
     const int64_t T = (int64_t)R * nkt;
     const int Gt = tail_groups(T, G);
+    // Few parts per item: 8 units of 64 queries.  Many: 64 units of 8 queries,
+    // at most kCombUnits * G in all, since R <= Gt / kCombFew <= G / 8.
+    const bool few = Gt < kCombFew * R;
+    const int units = few ? 8 : 64;
+    const int i = blockIdx.x / units, rb = blockIdx.x % units;
+    if (i >= R) return;
+    const int L = full + i;
     const int wf = tail_owner((int64_t)i * nkt, T, Gt);
     const int wl = tail_owner((int64_t)(i + 1) * nkt - 1, T, Gt);
-    const int L = full + i;
     if (wf == wl || exact_items[L]) return;
     const int slot = L / nqt, qt = L - slot * nqt;
     const int h = full_head(buckets, H, slot);
     if (h < 0) return;
-    // partial slot of workgroup v for this item
-    auto pslot = [&](int v) {
-        const int k = i == (int)(tail_start(v, T, Gt) / nkt) ? 0 : 1;
-        return part + (int64_t)(v * 2 + k) * kPartFloats;
-    };
-    const int qr = rb * kCombRows + (threadIdx.x >> 2), d0 = (threadIdx.x & 3) * 16;
-    const int64_t qi = (int64_t)qt * kBQf + qr;
-    if (qi >= N) return;
-    float mt = -INFINITY;
-    for (int v = wf; v <= wl; ++v) mt = fmaxf(mt, pslot(v)[kBQf * kD + kBQf + qr]);
-    float lt = 0.f;
-    float acc[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) acc[k] = 0.f;
-    for (int v = wf; v <= wl; ++v) {
-        const float* ps = pslot(v);
-        // 2^(m_v - max m): exactly 1 for parts at the largest reference point
-        // (every part of a FAST item has m = 0).
-        const float sc = exp2f_fast(ps[kBQf * kD + kBQf + qr] - mt);
-        lt = fmaf(ps[kBQf * kD + qr], sc, lt);
-        const float4* src = reinterpret_cast<const float4*>(ps + qr * kD + d0);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float4 a = src[k];
-            acc[4 * k] = fmaf(a.x, sc, acc[4 * k]);
-            acc[4 * k + 1] = fmaf(a.y, sc, acc[4 * k + 1]);
-            acc[4 * k + 2] = fmaf(a.z, sc, acc[4 * k + 2]);
-            acc[4 * k + 3] = fmaf(a.w, sc, acc[4 * k + 3]);
-        }
-    }
-    if (off && d0 == 0) off[(int64_t)h * N + qi] = mt + __log2f(lt);
-    const float inv = vsc[2 * slot + 1] / lt;
-    const int64_t yo = (qi * H + h) * kD + d0;
-    if (ydt == DT_BF16) {
-#pragma unroll
-        for (int k8 = 0; k8 < 2; ++k8) {
-            bf16x8 o;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) o[k] = (bf16)(acc[8 * k8 + k] * inv);
-            *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(Y) + yo + 8 * k8) = o;
-        }
-    } else {
-        float* y = reinterpret_cast<float*>(Y) + yo;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            *reinterpret_cast<float4*>(y + 4 * k) = make_float4(
-                acc[4 * k] * inv, acc[4 * k + 1] * inv, acc[4 * k + 2] * inv, acc[4 * k + 3] * inv);
-    }
+    const int vbase = tail_start(wf, T, Gt) == (int64_t)i * nkt ? 0 : 1;
+    if (few)
+        combine_parts<64, 1>(part, wf, wl, vbase, rb * 64, qt, N, H, h, vsc, slot, Y, ydt, off,
+                             s_acc);
+    else
+        combine_parts<8, 2>(part, wf, wl, vbase, rb * 8, qt, N, H, h, vsc, slot, Y, ydt, off,
+                            s_acc);
 }
+static_assert(kBQf == 512 && kCombUnits * kCombFew == 64, "units of k_flash_combine");
 
 // ------------------------------------------------------------------------
 // K6b (bf16, wide logit range): one workgroup = 4 waves x 64 queries of one
@@ -1980,7 +2035,7 @@ void launch_flash(const AttnArgs& a, hipStream_t st) {
                            0, st, (const bf16*)a.Q, (const f16*)a.kh, (const f16*)a.vt,
                            (const float*)a.kmax, (const float*)a.vsc, a.buckets, a.N, a.H, nqf,
                            nkt, c, a.qflag, a.part, G, a.Y, a.ydt, a.off);
-        hipLaunchKernelGGL(k_flash_combine, dim3(G * (kBQf / kCombRows)), dim3(256), 0, st,
+        hipLaunchKernelGGL(k_flash_combine, dim3(G * kCombUnits), dim3(256), 0, st,
                            a.buckets, a.N, a.H, nqf,
                            nkt, (const int32_t*)a.qflag, (const float*)a.part,
                            (const float*)a.vsc, G, a.Y, a.ydt, a.off);

@@ -136,6 +136,21 @@ def test_ragged_token_counts(dtype, P):
     check_y(layer.Y.double().cpu().numpy(), ref["Y"], dtype, False, label="P=%d" % P)
 
 
+@pytest.mark.parametrize("P", [64, 4096, 4097, 16384, 32769])
+def test_router_chunk_counts(P):
+    """The combine of the routing and pooling partials: 1, 64, 65, 256 and 505 routing
+    chunks and 1, 16, 17, 64 and 52 pooling chunks (64 groups of threads, up to 8 chunks
+    each)."""
+    log("router chunks P=%d" % P)
+    x = synth.make_layer(1, P, dtype="bf16", key=(14, P), sharp=True,
+                         modes=np.zeros(16, np.uint8), qkv_device="cuda")
+    layer = run_gpu(x, y_dtype=torch.float32)
+    rows = np.arange(4)
+    ref = oracle_layer(x, rows=rows)
+    check_router(layer, ref, oracle.RULE_ARGMAX)
+    check_y(layer.Y[:4].double().cpu().numpy(), ref["Y"], "bf16", False, label="P=%d" % P)
+
+
 @pytest.mark.parametrize("H", [1, 3, 5, 8])
 def test_fewer_heads(H):
     log("H=%d" % H)
@@ -577,6 +592,42 @@ def test_zero_reference_low_first_tile():
     ref = oracle_layer(x)
     check_router(layer, ref, oracle.RULE_ARGMAX)
     check_y(layer.Y.double().cpu().numpy(), ref["Y"], "bf16", False, label="low first tile")
+
+
+@pytest.mark.parametrize("P,n_full,few", [(2500, 16, True), (9001, 1, False), (4700, 2, False)])
+def test_combined_parts(P, n_full, few):
+    """Items of FULL heads split over workgroups, on both sides of the combine's rule (units
+    of 64 queries below 8 parts an item, of 8 queries and two groups of parts from there):
+    every query of the first, a middle and the (ragged) last item.  One key per head planted
+    as in test_zero_reference_overflow_moves: some parts of one query have their own
+    reference point, the others 0."""
+    log("combined parts P=%d full=%d" % (P, n_full))
+    modes = np.zeros(16, np.uint8)
+    modes[16 - n_full:] = 2
+    x = synth.make_layer(1, P, dtype="bf16", key=(13, P), sharp=True, modes=modes,
+                         qkv_device="cuda")
+    x.K = (x.K.float() * 0.7).to(torch.bfloat16)
+    nkt, items = -(-P // 64), -(-P // 512) * n_full
+    tail = items % 256
+    parts = min(256, tail * nkt // 8)
+    assert tail and (parts < 8 * tail) == few
+    heads = np.nonzero(modes == 2)[0]
+    rows = [np.arange(512), 512 * (P // 1024) + np.arange(512), np.arange(P // 512 * 512, P)]
+    for h in heads:
+        q = x.Q[:, h].float()
+        i0 = int(torch.linalg.vector_norm(q, dim=1).argmax())
+        qn = float(torch.linalg.vector_norm(q[i0]))
+        x.K[21 * 64 + 7, h] = (q[i0] / qn * (20.0 / (C_LOG2 * qn))).to(torch.bfloat16)
+        rows.append(np.array([i0]))
+    b = item_bounds(x)
+    assert ((b > FAST_BOUND) & (b <= EXT_BOUND)).all(), b
+    rows = np.unique(np.concatenate(rows))
+    layer = run_gpu(x, y_dtype=torch.float32)
+    Y = layer.Y[torch.from_numpy(rows).to(layer.Y.device)].double().cpu().numpy()
+    ref = np.zeros_like(Y)
+    for h in heads:
+        ref[:, h] = oracle.full_rows(x.Q, x.K, x.V, int(h), rows=rows)
+    check_y(Y, ref, "bf16", False, heads=heads, label="parts P=%d full=%d" % (P, n_full))
 
 
 def test_reference_point_mixed_launch():
