@@ -352,77 +352,93 @@ __global__ __launch_bounds__(256) void k_pool_partial_f32(const float* __restric
     }
 }
 
-// Combine of per-chunk online-softmax partials (m_c, l_c, a_c[...]) of one
-// head: M = max_c m_c, w_c = 2^(m_c - M), L = sum_c w_c l_c,
-// A = sum_c w_c a_c (and, when `plain` is set, an unweighted sum of a second
-// vector).  256 threads: thread (d, g) sums the g-th quarter of the chunks in
-// order for feature d; quarters and the L partials are then added in a fixed
-// order, so the result does not depend on scheduling.
+// Combine of per-chunk online-softmax partials (m_c, l_c, a_c[64], and with
+// NV = 2 a second vector b_c[64]) of one head: M = max_c m_c,
+// w_c = 2^(m_c - M), L = sum_c w_c l_c, A = sum_c w_c a_c, B = sum_c b_c.
+//
+// Bound by latency: a few MB at most, read once.  A workgroup of 1,024 threads
+// takes 16 of the 64 features (four workgroups a head, so all heads keep 64
+// compute units busy): thread (g, d) loads its values of chunks g, g + 64, ...
+// before the maximum is known, so every load of the kernel is in flight at
+// once.  The sums run in a fixed order and do not depend on scheduling.
+// At 137,400 tokens: 16 heads, one workgroup each, 17.2 us (routing, 512
+// chunks) and 8.4 us (pooling, 64 chunks); this split 6.0 and 5.0 us.
+constexpr int kCombFeat = 16, kCombGroups = 64, kCombThreads = kCombFeat * kCombGroups;
 struct Combined {
     float M, L;
 };
 
-// NG groups of 64 threads (the workgroup is 64 NG threads); group g sums a
-// contiguous run of chunks, and the groups' sums are added in group order.
-template <int NV, int NG>
-__device__ Combined combine_chunks(const float* __restrict__ part, int nchunks, int stride,
+// At most kCombGroups * CH chunks; acc[v] is the sum of feature
+// d0 + threadIdx.x % 16 (valid in the first 16 threads).
+template <int NV, int CH>
+__device__ Combined combine_chunks(const float* __restrict__ part, int nchunks, int d0,
                                    float (&acc)[NV]) {
-    __shared__ float s_w[1024];
-    __shared__ float s_red[NG][kD * NV];
-    __shared__ float s_ml[2 * NG];
-    const int t = threadIdx.x, d = t & 63, g = t >> 6;
-    float M = -INFINITY;
-    for (int c = t; c < nchunks; c += 64 * NG) M = fmaxf(M, part[(int64_t)c * stride]);
-    M = wave_max(M);
-    if ((t & 63) == 0) s_ml[g] = M;
-    __syncthreads();
-    M = s_ml[0];
-#pragma unroll
-    for (int i = 1; i < NG; ++i) M = fmaxf(M, s_ml[i]);
-    for (int c = t; c < nchunks; c += 64 * NG) {
-        const float mc = part[(int64_t)c * stride];
-        s_w[c] = (mc == -INFINITY) ? 0.f : exp2f_fast(mc - M);
-    }
-    __syncthreads();
-    const int q = (nchunks + NG - 1) / NG;
-    const int c0 = g * q, c1 = (c0 + q < nchunks) ? c0 + q : nchunks;
-    float a[NV], lsum = 0.f;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) a[v] = 0.f;
-#pragma unroll 4
-    for (int c = c0; c < c1; ++c) {
-        const float* p = part + (int64_t)c * stride;
-        const float w = s_w[c];
-        if (d == 0) lsum = fmaf(p[1], w, lsum);
-        a[0] = fmaf(p[2 + d], w, a[0]);
-        if (NV > 1) a[NV - 1] += p[2 + kD + d];
+    constexpr int stride = 2 + NV * kD;
+    __shared__ float s_w[kCombGroups * CH];
+    __shared__ float s_red[NV][kCombGroups][kCombFeat + 1];
+    __shared__ float s_m[kCombThreads / 64], s_l[kCombThreads / 64];
+    const int t = threadIdx.x, d = t % kCombFeat, g = t / kCombFeat;
+    float mc = -INFINITY, lc = 0.f, v[NV][CH];
+    if (t < nchunks) {
+        mc = part[(int64_t)t * stride];
+        lc = part[(int64_t)t * stride + 1];
     }
 #pragma unroll
-    for (int v = 0; v < NV; ++v) s_red[g][v * kD + d] = a[v];
-    if (d == 0) s_ml[NG + g] = lsum;
+    for (int k = 0; k < CH; ++k) {
+        const int c = g + kCombGroups * k;
+#pragma unroll
+        for (int n = 0; n < NV; ++n)
+            v[n][k] = c < nchunks ? part[(int64_t)c * stride + 2 + n * kD + d0 + d] : 0.f;
+    }
+    const float wm = wave_max(mc);
+    if ((t & 63) == 0) s_m[t >> 6] = wm;
     __syncthreads();
     Combined r;
-    r.M = M;
-    r.L = s_ml[NG];
+    r.M = s_m[0];
 #pragma unroll
-    for (int i = 1; i < NG; ++i) r.L += s_ml[NG + i];
+    for (int i = 1; i < kCombThreads / 64; ++i) r.M = fmaxf(r.M, s_m[i]);
+    const float w = (mc == -INFINITY) ? 0.f : exp2f_fast(mc - r.M);
+    if (t < kCombGroups * CH) s_w[t] = w;
+    const float wl = wave_sum(lc * w);
+    if ((t & 63) == 0) s_l[t >> 6] = wl;
+    __syncthreads();
+    float a[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        acc[v] = s_red[0][v * kD + d];
+    for (int n = 0; n < NV; ++n) a[n] = 0.f;
 #pragma unroll
-        for (int i = 1; i < NG; ++i) acc[v] += s_red[i][v * kD + d];
+    for (int k = 0; k < CH; ++k) {
+        a[0] = fmaf(v[0][k], s_w[g + kCombGroups * k], a[0]);
+        if (NV > 1) a[NV - 1] += v[NV - 1][k];
+    }
+#pragma unroll
+    for (int n = 0; n < NV; ++n) s_red[n][g][d] = a[n];
+    __syncthreads();
+    r.L = s_l[0];
+#pragma unroll
+    for (int i = 1; i < kCombThreads / 64; ++i) r.L += s_l[i];
+    // 64 groups: four runs of 16 per feature, then the four in order.
+    if (t < 4 * kCombFeat) {
+#pragma unroll
+        for (int n = 0; n < NV; ++n) {
+            float x = 0.f;
+#pragma unroll
+            for (int i = 0; i < kCombGroups / 4; ++i) x += s_red[n][g * (kCombGroups / 4) + i][d];
+            const float y = x + __shfl(x, (t + 16) & 63);
+            acc[n] = y + __shfl(y, (t + 32) & 63);
+        }
     }
     return r;
 }
 
-// K9a: q_pool_h = (sum_c w_c acc_c) / (sum_c w_c l_c).
-__global__ __launch_bounds__(256) void k_pool_combine(const float* __restrict__ part, int nchunks,
-                                                      float* __restrict__ q_pool) {
-    const int h = blockIdx.x;
+// K9a: q_pool_h = (sum_c w_c acc_c) / (sum_c w_c l_c); at most 64 chunks.
+__global__ __launch_bounds__(kCombThreads) void k_pool_combine(const float* __restrict__ part,
+                                                               int nchunks,
+                                                               float* __restrict__ q_pool) {
+    const int h = blockIdx.x / (kD / kCombFeat), d0 = blockIdx.x % (kD / kCombFeat) * kCombFeat;
     float acc[1];
     const Combined r =
-        combine_chunks<1, 4>(part + (int64_t)h * nchunks * (2 + kD), nchunks, 2 + kD, acc);
-    if (threadIdx.x < kD) q_pool[h * kD + threadIdx.x] = acc[0] / r.L;
+        combine_chunks<1, 1>(part + (int64_t)h * nchunks * (2 + kD), nchunks, d0, acc);
+    if (threadIdx.x < kCombFeat) q_pool[h * kD + d0 + threadIdx.x] = acc[0] / r.L;
 }
 
 // ------------------------------------------------------------------------
@@ -536,23 +552,24 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_partial(const void* __r
     }
 }
 
-// K9b: per head, combine the routing partials (up to 512 chunks, 16 groups of
-// 64 threads); write stats, score, ctx, vmean.
-constexpr int kRouteCombineGroups = 16;
-__global__ __launch_bounds__(64 * kRouteCombineGroups) void k_route_combine(const float* __restrict__ part, int nchunks,
-                                                       int64_t N, float* __restrict__ stats,
-                                                       float* __restrict__ score,
-                                                       float* __restrict__ ctx,
-                                                       float* __restrict__ vmean) {
-    const int h = blockIdx.x, d = threadIdx.x;
+// K9b: per head, combine the routing partials (at most 512 chunks); write
+// stats, score, ctx, vmean.
+__global__ __launch_bounds__(kCombThreads) void k_route_combine(const float* __restrict__ part,
+                                                                int nchunks, int64_t N,
+                                                                float* __restrict__ stats,
+                                                                float* __restrict__ score,
+                                                                float* __restrict__ ctx,
+                                                                float* __restrict__ vmean) {
+    const int h = blockIdx.x / (kD / kCombFeat), d0 = blockIdx.x % (kD / kCombFeat) * kCombFeat;
+    const int t = threadIdx.x;
     float acc[2];
-    const Combined r = combine_chunks<2, kRouteCombineGroups>(
-        part + (int64_t)h * nchunks * (2 + 2 * kD), nchunks, 2 + 2 * kD, acc);
-    if (d < kD) {
-        ctx[h * kD + d] = acc[0] / r.L;
-        vmean[h * kD + d] = acc[1] / (float)N;
+    const Combined r = combine_chunks<2, 8>(part + (int64_t)h * nchunks * (2 + 2 * kD), nchunks,
+                                            d0, acc);
+    if (t < kCombFeat) {
+        ctx[h * kD + d0 + t] = acc[0] / r.L;
+        vmean[h * kD + d0 + t] = acc[1] / (float)N;
     }
-    if (d == 0) {
+    if (t == 0 && d0 == 0) {
         stats[2 * h] = r.M * kLn2;
         stats[2 * h + 1] = r.L;
         score[h] = 1.f / r.L;
@@ -585,17 +602,17 @@ __global__ __launch_bounds__(256) void k_router_logits(const float* __restrict__
 
 // ------------------------------------------------------------------------
 // K4: mode per head (Eq.4 or first argmax, or their two-branch MEAN/FULL
-// forms of the compute-mode ablation, Table 6) and the grouped head lists.
+// forms of the compute-mode ablation, Table 6) and the grouped head lists: one
+// wave, a lane per head, places from ballots (at 300 tokens 5.0 us with one
+// lane filling the lists through LDS, 2.0 us so; a launch is most of that).
 // ------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void k_assign(const float* __restrict__ scores, int H, int rule,
                                                float tau_low, float tau_high,
                                                uint8_t* __restrict__ modes,
                                                int32_t* __restrict__ buckets) {
-    __shared__ int s_mode[kMaxHeads];
-    __shared__ int s_nan[kMaxHeads];
     const int h = threadIdx.x;
+    int md = -1, bad = 0;
     if (h < H) {
-        int md, bad = 0;
         if (rule == 0 || rule == 2) {   // Eq.4; rule 2: two-branch (no SURR)
             const float s = scores[h];
             bad = isnan(s);
@@ -613,26 +630,25 @@ __global__ __launch_bounds__(64) void k_assign(const float* __restrict__ scores,
             bad = isnan(lg[MODE_MEAN]) || isnan(lg[MODE_FULL]);
             md = (bad || lg[MODE_FULL] > lg[MODE_MEAN]) ? MODE_FULL : MODE_MEAN;
         }
-        s_mode[h] = md;
-        s_nan[h] = bad;
         modes[h] = (uint8_t)md;
     }
-    __syncthreads();
+    // Head h's place in the lists (MEAN, SURR, FULL, each in head order): the
+    // heads of lower modes, then those of its own mode before it.
+    const uint64_t b0 = __ballot(md == MODE_MEAN), b1 = __ballot(md == MODE_SURR),
+                   b2 = __ballot(md == MODE_FULL), nan = __ballot(bad != 0);
+    const int c0 = __popcll(b0), c1 = __popcll(b1), c2 = __popcll(b2);
+    if (h < H) {
+        const uint64_t own = md == MODE_MEAN ? b0 : (md == MODE_SURR ? b1 : b2);
+        const int base = md == MODE_MEAN ? 0 : (md == MODE_SURR ? c0 : c0 + c1);
+        buckets[3 + base + __popcll(own & ((1ull << h) - 1))] = h;
+    } else if (h < kMaxHeads) {
+        buckets[3 + h] = -1;
+    }
     if (h == 0) {
-        int cnt[3] = {0, 0, 0}, flags = 0;
-        for (int i = 0; i < H; ++i) {
-            cnt[s_mode[i]]++;
-            flags |= s_nan[i];
-        }
-        int pos = 3;
-        for (int md = 0; md < 3; ++md)
-            for (int i = 0; i < H; ++i)
-                if (s_mode[i] == md) buckets[pos++] = i;
-        for (; pos < 3 + kMaxHeads; ++pos) buckets[pos] = -1;
-        buckets[0] = cnt[0];
-        buckets[1] = cnt[1];
-        buckets[2] = cnt[2];
-        buckets[3 + kMaxHeads] = flags;
+        buckets[0] = c0;
+        buckets[1] = c1;
+        buckets[2] = c2;
+        buckets[3 + kMaxHeads] = nan != 0;
     }
 }
 
@@ -648,7 +664,7 @@ void launch_router(const RouterArgs& a, hipStream_t st) {
         hipLaunchKernelGGL(k_pool_partial_f32, g1, dim3(256), 0, st, (const float*)a.Q,
                            (const float*)a.W, (const float*)a.U, (const float*)a.w, a.N, a.H,
                            a.chunk1, a.mean_pool, a.part1);
-    hipLaunchKernelGGL(k_pool_combine, dim3(a.H), dim3(256), 0, st, a.part1, (int)a.n1,
+    hipLaunchKernelGGL(k_pool_combine, dim3(a.H * (kD / kCombFeat)), dim3(kCombThreads), 0, st, a.part1, (int)a.n1,
                        a.q_pool);
     if (a.dtype == DT_BF16)
         hipLaunchKernelGGL(k_route_partial<DT_BF16>, dim3((unsigned)a.n2), dim3(kRouteThreads), 0, st, a.K,
@@ -656,7 +672,7 @@ void launch_router(const RouterArgs& a, hipStream_t st) {
     else
         hipLaunchKernelGGL(k_route_partial<DT_F32>, dim3((unsigned)a.n2), dim3(kRouteThreads), 0, st, a.K,
                            a.V, a.q_pool, a.scale, a.N, a.H, a.chunk2, a.part2);
-    hipLaunchKernelGGL(k_route_combine, dim3(a.H), dim3(64 * kRouteCombineGroups), 0, st, a.part2, (int)a.n2, a.N,
+    hipLaunchKernelGGL(k_route_combine, dim3(a.H * (kD / kCombFeat)), dim3(kCombThreads), 0, st, a.part2, (int)a.n2, a.N,
                        a.stats, a.score, a.ctx, a.vmean);
 }
 
