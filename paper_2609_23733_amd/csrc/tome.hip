@@ -28,11 +28,12 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-// Lanes of the wave holding the same 8-bit digit (for an active lane).
-__device__ __forceinline__ uint64_t wave_match8(uint32_t d, bool active) {
+// Lanes of the wave holding the same digit of BITS bits (for an active lane).
+template <int BITS>
+__device__ __forceinline__ uint64_t wave_match(uint32_t d, bool active) {
     uint64_t m = __builtin_amdgcn_ballot_w64(active);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < BITS; ++b) {
         const bool bit = (d >> b) & 1u;
         const uint64_t bb = __builtin_amdgcn_ballot_w64(active && bit);
         m &= bit ? bb : ~bb;
@@ -299,87 +300,7 @@ __global__ __launch_bounds__(64 * kTmWaves, 1) void k_tome_match(const bf16* __r
     }
 }
 
-// Per source: its destination slot, the cosine similarity and the selection key
-// (similarity, then the lower token).
-__global__ __launch_bounds__(256) void k_tome_match_final(TomeGeom G,
-                                                          const uint64_t* __restrict__ top,
-                                                          const float* __restrict__ invn,
-                                                          int32_t* __restrict__ best,
-                                                          float* __restrict__ score,
-                                                          uint64_t* __restrict__ key) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= G.nA) return;
-    const float v = float_unorder((uint32_t)(top[i] >> 32));
-    const int64_t tok = tome_src_token(G, i);
-    const float sc = v * invn[tok] + 0.f;   // + 0: no -0
-    best[i] = (int32_t)~(uint32_t)top[i];
-    score[i] = sc;
-    key[i] = ((uint64_t)float_order(sc) << 32) | (uint64_t)(~(uint32_t)tok);
-}
-
-// ---------------------------------------------------------------- T3
-// Radix select of the M largest keys, 8 bits per pass from the top.  State:
-// [0] prefix (u64), [1] keys still to take (as u64).
-__global__ __launch_bounds__(256) void k_tome_init(uint64_t* __restrict__ st,
-                                                   uint32_t* __restrict__ ghist, int64_t M,
-                                                   int32_t* __restrict__ cnt, int64_t nD,
-                                                   uint64_t* __restrict__ top, int64_t nA) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < 256) ghist[i] = 0;
-    if (i == 0) {
-        st[0] = 0;
-        st[1] = (uint64_t)M;
-    }
-    if (i < nD) cnt[i] = 0;    // merged sources per destination
-    if (i < nA) top[i] = kNoMatch;   // matching: maxima so far
-}
-
-__global__ __launch_bounds__(256) void k_rsel_hist(const uint64_t* __restrict__ key, int64_t n,
-                                                   int shift, const uint64_t* __restrict__ st,
-                                                   uint32_t* __restrict__ ghist) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t prefix = st[0];
-    const uint64_t hmask = shift >= 56 ? 0ull : (~0ull << (shift + 8));
-    const int64_t base = (int64_t)blockIdx.x * 4096;
-#pragma unroll 4
-    for (int k = 0; k < 16; ++k) {
-        const int64_t i = base + k * 256 + threadIdx.x;
-        bool act = false;
-        uint32_t d = 0;
-        if (i < n) {
-            const uint64_t v = key[i];
-            act = (v & hmask) == (prefix & hmask);
-            d = (uint32_t)(v >> shift) & 255u;
-        }
-        const uint64_t mt = wave_match8(d, act);
-        if (act && (mt & lanemask_lt()) == 0) atomicAdd(&h[d], (uint32_t)__popcll(mt));
-    }
-    __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&ghist[threadIdx.x], h[threadIdx.x]);
-}
-
-__global__ void k_rsel_pick(uint64_t* __restrict__ st, uint32_t* __restrict__ ghist, int shift) {
-    if (threadIdx.x == 0) {
-        const uint64_t rem = st[1];
-        uint64_t cum = 0;
-        int d = 255;
-        for (; d > 0; --d) {
-            if (cum + ghist[d] >= rem) break;
-            cum += ghist[d];
-        }
-        st[1] = rem - cum;
-        st[0] |= (uint64_t)d << shift;
-    }
-    __syncthreads();
-    if (threadIdx.x < 256) ghist[threadIdx.x] = 0;
-}
-
-// ---------------------------------------------------------------- scans
-// Exclusive scan of non-negative int32 over n: block sums, a one-workgroup
-// scan of the sums, then per-block scans plus their offsets (in == out
-// allowed).
+// Exclusive prefix sum of one value per thread (256 threads); *total: the sum.
 __device__ __forceinline__ int block_scan_excl(int v, int* total) {
     __shared__ int ws[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -398,26 +319,186 @@ __device__ __forceinline__ int block_scan_excl(int v, int* total) {
     return off + x - v;
 }
 
-__global__ __launch_bounds__(256) void k_scan_sums(const int32_t* __restrict__ in, int64_t n,
-                                                   int32_t* __restrict__ bsum) {
+// ---------------------------------------------------------------- T3
+// Radix select of the M largest keys (similarity, then the lower token): the
+// ordered 32 bits of the score above tb bits of the token's complement, N <=
+// 2^tb, so that a key has only the bits that can differ.  11 bits per pass from
+// the top, one histogram of 2,048 counts per pass.  State before pass p: [2 p]
+// prefix, [2 p + 1] keys still to take.  The digit of pass p - 1 is found by every
+// workgroup of pass p for itself (a scan of 2,048 counts; the first one records
+// it), and the last digit by the workgroups of k_tome_flags; pass 0 counts as
+// k_tome_match_final makes the keys.
+// Bound by launches and the latency of a pass: 108,405 keys in 8 passes of 8
+// bits, each a histogram (27 workgroups of 4,096 keys) and a kernel for the
+// digit, 126 us; in 5 passes of 1,024 keys a workgroup, 25 us.
+constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6;   // 32 + 28 bits at most
+constexpr int kSelBlock = 1024;   // keys per workgroup (256 threads x 4)
+
+__device__ __forceinline__ uint64_t sel_key(float score, int64_t tok, int tb) {
+    return ((uint64_t)float_order(score) << tb) | (((uint64_t)1 << tb) - 1 - (uint64_t)tok);
+}
+
+// The digit of a pass: the largest d with as many keys of digits >= d as are still to
+// take.  256 threads; prefix and rem in and out.
+__device__ __forceinline__ void sel_pick(const uint32_t* __restrict__ ghist, int shift,
+                                         uint64_t& prefix, uint64_t& rem) {
+    constexpr int kPer = kSelBins / 256;
+    __shared__ uint32_t s_d, s_rem;
+    uint32_t c[kPer];   // digits from kSelBins - 1 - kPer t down
+    const u32x4* g = reinterpret_cast<const u32x4*>(ghist + kSelBins - kPer * (threadIdx.x + 1));
+    const u32x4 lo = g[0], hi = g[1];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        c[k] = hi[3 - k];
+        c[4 + k] = lo[3 - k];
+    }
+    int sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) sum += (int)c[k];
+    if (threadIdx.x == 0) {
+        s_d = 0;
+        s_rem = (uint32_t)rem;
+    }
+    int tot;
+    uint32_t above = (uint32_t)block_scan_excl(sum, &tot);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        if (above < rem && above + c[k] >= rem) {
+            s_d = kSelBins - 1 - kPer * threadIdx.x - k;
+            s_rem = (uint32_t)rem - above;
+        }
+        above += c[k];
+    }
+    __syncthreads();
+    prefix |= (uint64_t)s_d << shift;
+    rem = s_rem;
+}
+
+// Count of a workgroup's digits into the histogram h (LDS, zeroed), then ghist.
+__device__ __forceinline__ void sel_count(uint32_t* h, uint32_t d, bool act) {
+    const uint64_t mt = wave_match<kSelBits>(d, act);
+    if (act && (mt & lanemask_lt()) == 0) atomicAdd(&h[d], (uint32_t)__popcll(mt));
+}
+__device__ __forceinline__ void sel_flush(const uint32_t* h, uint32_t* __restrict__ ghist) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSelBins; k += 256)
+        if (h[k + threadIdx.x]) atomicAdd(&ghist[k + threadIdx.x], h[k + threadIdx.x]);
+}
+
+__global__ __launch_bounds__(256) void k_tome_init(uint64_t* __restrict__ st,
+                                                   uint32_t* __restrict__ ghist, int64_t M,
+                                                   int32_t* __restrict__ cnt, int64_t nD,
+                                                   uint64_t* __restrict__ top, int64_t nA) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t k = i; k < kSelPasses * kSelBins; k += (int64_t)gridDim.x * 256) ghist[k] = 0;
+    if (i == 0) {
+        st[0] = 0;
+        st[1] = (uint64_t)M;
+    }
+    if (i < nD) cnt[i] = 0;    // merged sources per destination
+    if (i < nA) top[i] = kNoMatch;   // matching: maxima so far
+}
+
+// Per source: its destination slot, the cosine similarity and the selection key;
+// the histogram of the keys' first digits.
+__global__ __launch_bounds__(256) void k_tome_match_final(TomeGeom G, int tb, int shift,
+                                                          const uint64_t* __restrict__ top,
+                                                          const float* __restrict__ invn,
+                                                          int32_t* __restrict__ best,
+                                                          float* __restrict__ score,
+                                                          uint64_t* __restrict__ key,
+                                                          uint32_t* __restrict__ ghist) {
+    __shared__ uint32_t h[kSelBins];
+#pragma unroll
+    for (int k = 0; k < kSelBins; k += 256) h[k + threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * kSelBlock + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < kSelBlock / 256; ++k) {
+        const int64_t i = base + 256 * k;
+        uint32_t d = 0;
+        if (i < G.nA) {
+            const float v = float_unorder((uint32_t)(top[i] >> 32));
+            const int64_t tok = tome_src_token(G, i);
+            const float sc = v * invn[tok] + 0.f;   // + 0: no -0
+            best[i] = (int32_t)~(uint32_t)top[i];
+            score[i] = sc;
+            const uint64_t ky = sel_key(sc, tok, tb);
+            key[i] = ky;
+            d = (uint32_t)(ky >> shift);
+        }
+        sel_count(h, d, i < G.nA);
+    }
+    sel_flush(h, ghist);
+}
+
+// Pass p > 0 at `shift`: counts of the next digit among the keys with the prefix so far.
+__global__ __launch_bounds__(256) void k_rsel_hist(const uint64_t* __restrict__ key, int64_t n,
+                                                   int p, int shift, uint64_t* __restrict__ st,
+                                                   uint32_t* __restrict__ ghist) {
+    __shared__ uint32_t h[kSelBins];
+#pragma unroll
+    for (int k = 0; k < kSelBins; k += 256) h[k + threadIdx.x] = 0;
+    uint64_t v[kSelBlock / 256];
+    const int64_t base = (int64_t)blockIdx.x * kSelBlock + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < kSelBlock / 256; ++k) {
+        const int64_t i = base + 256 * k;
+        v[k] = i < n ? key[i] : ~0ull;   // (no key: it has at most 60 bits)
+    }
+    uint64_t prefix = st[2 * p - 2], rem = st[2 * p - 1];
+    sel_pick(ghist + (p - 1) * kSelBins, shift + kSelBits, prefix, rem);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st[2 * p] = prefix;
+        st[2 * p + 1] = rem;
+    }
+#pragma unroll
+    for (int k = 0; k < kSelBlock / 256; ++k)
+        sel_count(h, (uint32_t)(v[k] >> shift) & (kSelBins - 1),
+                  ((v[k] ^ prefix) >> (shift + kSelBits)) == 0);
+    sel_flush(h, ghist + p * kSelBins);
+}
+
+// ---------------------------------------------------------------- scans
+// Exclusive scans of non-negative int32, up to two arrays at once (blockIdx.y):
+// block sums, then per-block scans plus the sums before them (in == out
+// allowed).  Up to kScanFew blocks each block adds those up itself; beyond,
+// a one-workgroup scan of the sums comes between.  At 137,400 tokens a kernel
+// of this size takes 4 us, nearly all of it latency: six scans of three kernels
+// 72 us, three (two of them on two arrays) of two kernels 28 us.  The whole plan
+// of 5,496 tokens is 110 us shorter (merged layer 314 -> 204 us), that of 137,400
+// tokens 130 us (2293 -> 2161 us).
+constexpr int kScanFew = 1024;
+struct ScanJob {
+    const int32_t* in;
+    int32_t* out;
+    int64_t n;
+    int32_t* bsum;
+};
+
+__global__ __launch_bounds__(256) void k_scan_sums(ScanJob a, ScanJob b) {
+    const ScanJob j = blockIdx.y ? b : a;
+    if ((int64_t)blockIdx.x * kScanBlock >= j.n) return;
     const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * 4;
     int s = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) s += (i + k < n) ? in[i + k] : 0;
+    for (int k = 0; k < 4; ++k) s += (i + k < j.n) ? j.in[i + k] : 0;
     int tot;
     block_scan_excl(s, &tot);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+    if (threadIdx.x == 0) j.bsum[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(256) void k_scan_top(int32_t* __restrict__ bsum, int64_t nb,
-                                                  int32_t* __restrict__ total) {
+__global__ __launch_bounds__(256) void k_scan_top(ScanJob a, ScanJob b) {
+    const ScanJob j = blockIdx.y ? b : a;
+    const int64_t nb = (j.n + kScanBlock - 1) / kScanBlock;
     int carry = 0;
     for (int64_t c = 0; c < nb; c += kScanBlock) {
         const int64_t i = c + threadIdx.x * 4;
         int v[4], s = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            v[k] = (i + k < nb) ? bsum[i + k] : 0;
+            v[k] = (i + k < nb) ? j.bsum[i + k] : 0;
             s += v[k];
         }
         int tot;
@@ -425,43 +506,54 @@ __global__ __launch_bounds__(256) void k_scan_top(int32_t* __restrict__ bsum, in
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (i + k < nb) {
-                bsum[i + k] = run;
+                j.bsum[i + k] = run;
                 run += v[k];
             }
         carry += tot;
         __syncthreads();
     }
-    if (total && threadIdx.x == 0) *total = carry;
 }
 
-__global__ __launch_bounds__(256) void k_scan_apply(const int32_t* in, int64_t n,
-                                                    const int32_t* __restrict__ bsum,
-                                                    int32_t* out) {
+__global__ __launch_bounds__(256) void k_scan_apply(ScanJob a, ScanJob b, int scanned) {
+    const ScanJob j = blockIdx.y ? b : a;
+    if ((int64_t)blockIdx.x * kScanBlock >= j.n) return;
     const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * 4;
     int v[4], s = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        v[k] = (i + k < n) ? in[i + k] : 0;
+        v[k] = (i + k < j.n) ? j.in[i + k] : 0;
         s += v[k];
     }
+    int before;
+    if (scanned) {
+        before = j.bsum[blockIdx.x];
+    } else {
+        int pre = 0;
+#pragma unroll
+        for (int k = 0; k < kScanFew / 256; ++k) {
+            const unsigned q = threadIdx.x + 256 * k;
+            pre += q < blockIdx.x ? j.bsum[q] : 0;
+        }
+        block_scan_excl(pre, &before);
+    }
     int tot;
-    int run = bsum[blockIdx.x] + block_scan_excl(s, &tot);
+    int run = before + block_scan_excl(s, &tot);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        if (i + k < n) {
-            out[i + k] = run;
+        if (i + k < j.n) {
+            j.out[i + k] = run;
             run += v[k];
         }
 }
 
-void scan_excl(const int32_t* in, int32_t* out, int64_t n, int32_t* bsum, int32_t* total,
-               hipStream_t st) {
+void scan_excl(ScanJob a, ScanJob b, hipStream_t st) {
+    const int64_t n = a.n > b.n ? a.n : b.n;
     if (n <= 0) return;
-    const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-    hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)nb), dim3(256), 0, st, in, n, bsum);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, st, bsum, nb, total);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(256), 0, st, in, n,
-                       (const int32_t*)bsum, out);
+    const dim3 grid((unsigned)((n + kScanBlock - 1) / kScanBlock), b.n > 0 ? 2 : 1);
+    const int scanned = grid.x > kScanFew;
+    hipLaunchKernelGGL(k_scan_sums, grid, dim3(256), 0, st, a, b);
+    if (scanned) hipLaunchKernelGGL(k_scan_top, dim3(1, grid.y), dim3(256), 0, st, a, b);
+    hipLaunchKernelGGL(k_scan_apply, grid, dim3(256), 0, st, a, b, scanned);
 }
 
 // ---------------------------------------------------------------- sort
@@ -475,7 +567,7 @@ __global__ __launch_bounds__(kSortBlock) void k_rs_hist(const uint32_t* __restri
     const int64_t i = (int64_t)blockIdx.x * kSortBlock + threadIdx.x;
     const bool act = i < n;
     const uint32_t d = act ? (key[i] >> shift) & 255u : 0u;
-    const uint64_t mt = wave_match8(d, act);
+    const uint64_t mt = wave_match<8>(d, act);
     if (act && (mt & lanemask_lt()) == 0) atomicAdd(&h[d], (int32_t)__popcll(mt));
     __syncthreads();
     if (threadIdx.x < 256) hist[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
@@ -496,7 +588,7 @@ __global__ __launch_bounds__(kSortBlock) void k_rs_scatter(const uint32_t* __res
     const bool act = i < n;
     const uint32_t k = act ? key[i] : 0u;
     const uint32_t d = (k >> shift) & 255u;
-    const uint64_t mt = wave_match8(d, act);
+    const uint64_t mt = wave_match<8>(d, act);
     const int rank = __popcll(mt & lanemask_lt());
     if (act && rank == 0) wc[wave][d] = __popcll(mt);
     __syncthreads();
@@ -509,26 +601,33 @@ __global__ __launch_bounds__(kSortBlock) void k_rs_scatter(const uint32_t* __res
 }
 
 // ---------------------------------------------------------------- T4
-// Per token: kept flag; per source: merged flag; merged count per
-// destination; the optional best / score outputs.
-__global__ __launch_bounds__(256) void k_tome_flags(TomeGeom G, const uint64_t* __restrict__ key,
+// Per token: kept flag; merged count per destination; the optional best /
+// score outputs.  The threshold of the merged sources' keys is the prefix
+// before the last pass (shift 0) and that pass's digit.
+__global__ __launch_bounds__(256) void k_tome_flags(TomeGeom G, int passes,
+                                                    const uint64_t* __restrict__ key,
                                                     const uint64_t* __restrict__ st,
+                                                    const uint32_t* __restrict__ ghist,
                                                     const int32_t* __restrict__ bslot,
                                                     const float* __restrict__ score,
                                                     int32_t* __restrict__ kept,
-                                                    int32_t* __restrict__ mflag,
                                                     int32_t* __restrict__ cnt,
                                                     int32_t* __restrict__ best_out,
                                                     float* __restrict__ score_out) {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    uint64_t least = 0, rem = 0;
+    if (G.nA > 0) {
+        least = st[2 * passes - 2];
+        rem = st[2 * passes - 1];
+        sel_pick(ghist + (passes - 1) * kSelBins, 0, least, rem);
+    }
     if (t >= G.N) return;
     const int64_t s = tome_slot(G, t);
     int k = 1;
     if (s < 0) {
         const int64_t i = -1 - s;
-        const int merged = key[i] >= st[0] ? 1 : 0;
+        const int merged = key[i] >= least ? 1 : 0;
         k = 1 - merged;
-        mflag[i] = merged;
         if (merged) atomicAdd(&cnt[bslot[i]], 1);
         if (best_out) best_out[t] = (int32_t)tome_dst_token(G, bslot[i]);
         if (score_out) score_out[t] = score[i];
@@ -539,39 +638,35 @@ __global__ __launch_bounds__(256) void k_tome_flags(TomeGeom G, const uint64_t* 
     kept[t] = k;
 }
 
-// Merged sources in token order: (destination slot, token).
-__global__ __launch_bounds__(256) void k_tome_compact(TomeGeom G, const int32_t* __restrict__ mflag,
-                                                      const int32_t* __restrict__ pos,
-                                                      const int32_t* __restrict__ bslot,
-                                                      uint32_t* __restrict__ lkey,
-                                                      int32_t* __restrict__ lval) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= G.nA || !mflag[i]) return;
-    lkey[pos[i]] = (uint32_t)bslot[i];
-    lval[pos[i]] = (int32_t)tome_src_token(G, i);
-}
-
-// Rows of merged sources (their destination's), and row sizes of kept
-// tokens (1 + the sources merged into a destination).
-__global__ __launch_bounds__(256) void k_tome_rows(TomeGeom G, const int32_t* __restrict__ kept,
+// Row sizes of kept tokens (1 + the sources merged into a destination); for
+// merged sources, of which t - row[t] come before token t (row: the scan of
+// the kept flags), their place in the list of (destination slot, token) in
+// token order, and their row, the destination's.
+__global__ __launch_bounds__(256) void k_tome_rows(TomeGeom G, int64_t M,
+                                                   const int32_t* __restrict__ kept,
                                                    const int32_t* __restrict__ bslot,
                                                    const int32_t* __restrict__ cnt,
                                                    int32_t* __restrict__ row,
-                                                   int32_t* __restrict__ size) {
+                                                   int32_t* __restrict__ size,
+                                                   uint32_t* __restrict__ lkey,
+                                                   int32_t* __restrict__ lval,
+                                                   int32_t* __restrict__ row_start) {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t == 0) row_start[G.N - M] = (int32_t)G.N;
     if (t >= G.N) return;
-    const int64_t s = tome_slot(G, t);
+    const int64_t s = tome_slot(G, t), r = row[t];
     if (kept[t]) {
-        const int64_t r = row[t];
         if (r >= 0 && r < G.N) size[r] = 1 + (s >= 0 ? cnt[s] : 0);
     } else {
+        const int32_t j = bslot[-1 - s];
+        const int64_t p = t - r;
+        if (p >= 0 && p < M) {
+            lkey[p] = (uint32_t)j;
+            lval[p] = (int32_t)t;
+        }
         // a kept destination's row is final (it came from the scan)
-        row[t] = row[tome_dst_token(G, bslot[-1 - s])];
+        row[t] = row[tome_dst_token(G, j)];
     }
-}
-
-__global__ void k_tome_last(int32_t* __restrict__ row_start, int64_t nrows, int64_t N) {
-    if (threadIdx.x == 0) row_start[nrows] = (int32_t)N;
 }
 
 // (Every index is checked against its array, so an inconsistent plan cannot
@@ -714,8 +809,8 @@ __global__ __launch_bounds__(256) void k_tome_unmerge(const u32x4* __restrict__ 
 
 // Workspace of the plan for N tokens.
 struct TomeWs {
-    size_t m, invn, bslot, score, key, st, ghist, mflag, pos, kept, cnt, off, size, lk0, lv0,
-        lk1, lv1, bsum, hist, top, total;
+    size_t m, invn, bslot, score, key, st, ghist, kept, cnt, off, size, lk0, lv0, lk1, lv1,
+        bsum0, bsum1, hist, top, total;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -723,7 +818,6 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 TomeWs tome_ws(int64_t N) {
     TomeWs w;
     const size_t n = (size_t)(N > 0 ? N : 1);
-    const size_t nbs = (n + kScanBlock - 1) / kScanBlock + 1;
     const size_t nbr = (n + kSortBlock - 1) / kSortBlock;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -736,10 +830,8 @@ TomeWs tome_ws(int64_t N) {
     w.bslot = take(n * 4);
     w.score = take(n * 4);
     w.key = take(n * 8);
-    w.st = take(16);
-    w.ghist = take(256 * 4);
-    w.mflag = take(n * 4);
-    w.pos = take(n * 4);
+    w.st = take(kSelPasses * 16);
+    w.ghist = take(kSelPasses * kSelBins * 4);
     w.kept = take(n * 4);
     w.cnt = take(n * 4);
     w.off = take(n * 4);
@@ -748,7 +840,8 @@ TomeWs tome_ws(int64_t N) {
     w.lv0 = take(n * 4);
     w.lk1 = take(n * 4);
     w.lv1 = take(n * 4);
-    w.bsum = take(((256 * nbr > n ? 256 * nbr : n) / kScanBlock + 2) * 4 + nbs * 4);
+    w.bsum0 = take(((256 * nbr > n ? 256 * nbr : n) / kScanBlock + 1) * 4);
+    w.bsum1 = take((n / kScanBlock + 1) * 4);
     w.hist = take(256 * nbr * 4);
     w.top = take(n * 8);
     w.total = o;
@@ -772,15 +865,17 @@ void launch_tome_plan(const TomeArgs& a, hipStream_t st) {
     uint64_t* key = (uint64_t*)(ws + w.key);
     uint64_t* sel = (uint64_t*)(ws + w.st);
     uint32_t* ghist = (uint32_t*)(ws + w.ghist);
-    int32_t *mflag = (int32_t*)(ws + w.mflag), *pos = (int32_t*)(ws + w.pos);
     int32_t *kept = (int32_t*)(ws + w.kept), *cnt = (int32_t*)(ws + w.cnt);
     int32_t *off = (int32_t*)(ws + w.off), *size = (int32_t*)(ws + w.size);
     uint32_t *lk0 = (uint32_t*)(ws + w.lk0), *lk1 = (uint32_t*)(ws + w.lk1);
     int32_t *lv0 = (int32_t*)(ws + w.lv0), *lv1 = (int32_t*)(ws + w.lv1);
-    int32_t* bsum = (int32_t*)(ws + w.bsum);
+    int32_t *bsum0 = (int32_t*)(ws + w.bsum0), *bsum1 = (int32_t*)(ws + w.bsum1);
     int32_t* hist = (int32_t*)(ws + w.hist);
     uint64_t* top = (uint64_t*)(ws + w.top);
     const int64_t N = G.N, M = a.M, nrows = N - M;
+    int tb = 1;   // bits of a token
+    while (tb < 28 && ((int64_t)1 << tb) < N) ++tb;
+    const int passes = (32 + tb + kSelBits - 1) / kSelBits;
 
     hipLaunchKernelGGL(k_tome_init, dim3(grid256(N)), dim3(256), 0, st, sel, ghist, M, cnt, G.nD,
                        top, G.nA);
@@ -791,26 +886,27 @@ void launch_tome_plan(const TomeArgs& a, hipStream_t st) {
         hipLaunchKernelGGL(k_tome_match, dim3((unsigned)(steps < kTmWG ? steps : kTmWG)),
                            dim3(64 * kTmWaves), 0, st, (const bf16*)m, (const float*)invn, G,
                            (unsigned long long*)top);
-        hipLaunchKernelGGL(k_tome_match_final, dim3(grid256(G.nA)), dim3(256), 0, st, G,
-                           (const uint64_t*)top, (const float*)invn, bslot, score, key);
+        const unsigned gs = (unsigned)((G.nA + kSelBlock - 1) / kSelBlock);
+        int shift = (passes - 1) * kSelBits;
+        hipLaunchKernelGGL(k_tome_match_final, dim3(gs), dim3(256), 0, st, G, tb, shift,
+                           (const uint64_t*)top, (const float*)invn, bslot, score, key, ghist);
         // (M > 0 here: M = 0 leaves stride 1, hence no sources)
-        const unsigned gh = (unsigned)((G.nA + 4095) / 4096);
-        for (int shift = 56; shift >= 0; shift -= 8) {
-            hipLaunchKernelGGL(k_rsel_hist, dim3(gh), dim3(256), 0, st, (const uint64_t*)key, G.nA,
-                               shift, (const uint64_t*)sel, ghist);
-            hipLaunchKernelGGL(k_rsel_pick, dim3(1), dim3(256), 0, st, sel, ghist, shift);
+        for (int p = 1; p < passes; ++p) {
+            shift -= kSelBits;
+            hipLaunchKernelGGL(k_rsel_hist, dim3(gs), dim3(256), 0, st, (const uint64_t*)key, G.nA,
+                               p, shift, sel, ghist);
         }
     }
-    hipLaunchKernelGGL(k_tome_flags, dim3(grid256(N)), dim3(256), 0, st, G, (const uint64_t*)key,
-                       (const uint64_t*)sel, (const int32_t*)bslot, (const float*)score, kept,
-                       mflag, cnt, a.best, a.score);
-    // rows of kept tokens
-    scan_excl(kept, a.row, N, bsum, nullptr, st);
+    hipLaunchKernelGGL(k_tome_flags, dim3(grid256(N)), dim3(256), 0, st, G, passes,
+                       (const uint64_t*)key, (const uint64_t*)sel, (const uint32_t*)ghist,
+                       (const int32_t*)bslot, (const float*)score, kept, cnt, a.best, a.score);
+    // rows of kept tokens; merged sources before each destination's
+    const ScanJob none = {nullptr, nullptr, 0, nullptr};
+    scan_excl({kept, a.row, N, bsum0}, M > 0 ? ScanJob{cnt, off, G.nD, bsum1} : none, st);
+    hipLaunchKernelGGL(k_tome_rows, dim3(grid256(N)), dim3(256), 0, st, G, M, (const int32_t*)kept,
+                       (const int32_t*)bslot, (const int32_t*)cnt, a.row, size, lk0, lv0,
+                       a.row_start);
     if (M > 0) {
-        scan_excl(mflag, pos, G.nA, bsum, nullptr, st);
-        hipLaunchKernelGGL(k_tome_compact, dim3(grid256(G.nA)), dim3(256), 0, st, G,
-                           (const int32_t*)mflag, (const int32_t*)pos, (const int32_t*)bslot, lk0,
-                           lv0);
         // stable sort of the merged sources by destination slot
         int bits = 1;
         while (bits < 31 && ((int64_t)1 << bits) < G.nD) ++bits;
@@ -820,7 +916,9 @@ void launch_tome_plan(const TomeArgs& a, hipStream_t st) {
         for (int shift = 0; shift < bits; shift += 8) {
             hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nb), dim3(kSortBlock), 0, st,
                                (const uint32_t*)ki, M, shift, nb, hist);
-            scan_excl(hist, hist, 256 * nb, bsum, nullptr, st);
+            // (the rows' starts ride along with the first pass)
+            scan_excl({hist, hist, 256 * nb, bsum0},
+                      shift == 0 ? ScanJob{size, a.row_start, nrows, bsum1} : none, st);
             hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nb), dim3(kSortBlock), 0, st,
                                (const uint32_t*)ki, (const int32_t*)vi, M, shift, nb,
                                (const int32_t*)hist, ko, vo);
@@ -833,12 +931,9 @@ void launch_tome_plan(const TomeArgs& a, hipStream_t st) {
         }
         lk0 = ki;
         lv0 = vi;
-        scan_excl(cnt, off, G.nD, bsum, nullptr, st);
+    } else {
+        scan_excl({size, a.row_start, nrows, bsum0}, none, st);
     }
-    hipLaunchKernelGGL(k_tome_rows, dim3(grid256(N)), dim3(256), 0, st, G, (const int32_t*)kept,
-                       (const int32_t*)bslot, (const int32_t*)cnt, a.row, size);
-    scan_excl(size, a.row_start, nrows, bsum, nullptr, st);
-    hipLaunchKernelGGL(k_tome_last, dim3(1), dim3(64), 0, st, a.row_start, nrows, N);
     hipLaunchKernelGGL(k_tome_members, dim3(grid256(N)), dim3(256), 0, st, G, M, nrows,
                        (const int32_t*)kept, (const int32_t*)a.row, (const int32_t*)a.row_start,
                        (const uint32_t*)lk0, (const int32_t*)lv0, (const int32_t*)off,

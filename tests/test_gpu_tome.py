@@ -169,6 +169,38 @@ def test_plan_edges(S, P, M, nspecial):
         np.testing.assert_array_equal(plan.members.cpu().numpy(), np.arange(S * P))
 
 
+@pytest.mark.parametrize("S,P,frac", [(2, 32, 0.4), (4, 1024, 0.6), (3, 1366, 0.3),
+                                      (16, 65536, 0.5), (16, 65537, 0.55)])
+def test_plan_many_ties(S, P, frac):
+    """Keys of 40 directions and power-of-two lengths: most scores are shared by many
+    sources, so the cut falls inside a tie and the lower tokens win, exactly as a sort of
+    the GPU's own (score, token) has it; rows and members follow exactly.  64, 4,096 and
+    4,098 tokens: keys of 38, 44 and 45 bits (4 and 5 passes of 11); 2^20 tokens and 16
+    more: 1,024 scan blocks (added up in place) and 1,025 (a scan of their sums)."""
+    log("tome ties S=%d P=%d" % (S, P))
+    N, M = S * P, int(frac * S * P)
+    rng = np.random.default_rng(N)
+    base = synth.normal((40, 1, 64), synth.derive_seed(50, S, P), 1.0).to(torch.bfloat16).float()
+    scale = torch.from_numpy(2.0 ** rng.integers(-1, 3, N)).float()[:, None, None]
+    K = (base[torch.from_numpy(rng.integers(0, 40, N))] * scale).to(torch.bfloat16)
+    plan = run_plan(K, S, P, M)
+    is_dst, _ = oracle.tome_split(S, P, M)
+    srcs = np.nonzero(~is_dst)[0]
+    score = plan.score.cpu().numpy()[srcs]
+    best = plan.best.cpu().numpy().astype(np.int64)[srcs]
+    order = np.lexsort((srcs, -score))
+    assert len(srcs) == M or score[order[M - 1]] == score[order[M]]
+    merged = np.zeros(len(srcs), bool)
+    merged[order[:M]] = True
+    row, nrows = oracle.tome_rows(N, srcs, best, merged)
+    np.testing.assert_array_equal(plan.row.cpu().numpy(), row)
+    kept = np.ones(N, bool)
+    kept[srcs[merged]] = False
+    members, starts = expected_csr(row, kept, nrows)
+    np.testing.assert_array_equal(plan.row_start.cpu().numpy(), starts)
+    np.testing.assert_array_equal(plan.members.cpu().numpy(), members)
+
+
 @pytest.mark.parametrize("S,P,M", [(2, 70, 40), (3, 700, 1000), (4, 1374, 3900)])
 def test_match_zero_and_nan_rows(S, P, M):
     """Source counts below and above one block of 1024 and destinations around
