@@ -330,7 +330,13 @@ constexpr int kBQf = 512;
 constexpr int kStreamWG = 256;      // grid: one workgroup per CU
 constexpr int kPartFloats = kBQf * kD + 2 * kBQf;   // partial slot: O[512][64], l[512], m[512]
 
-constexpr int kMinPartTiles = 8;    // fewest key tiles per workgroup in the tail
+// Fewest key tiles per workgroup in the tail: one.  A workgroup's chain of tiles (2-3
+// us each) is what a short layer waits for; a part costs its 131 KB once more in
+// K6c.  Layer, 4 FULL heads, with at least 8, 4, 2 and 1: 300 tokens 79.0, 81.4, 80.5,
+// 73.5 us; 600 84.3, 80.9, 71.7, 70.5; 1,000 78.2, 76.2, 74.2, 72.7; 1,374 91.2, 88.0,
+// 75.5, 77.4; 16 heads of 300 90.8, 79.7, 77.2, 69.5.  From 2,048 steps on all are the
+// same (256 workgroups).
+constexpr int kMinPartTiles = 1;
 constexpr int64_t kRotateTiles = 4096;   // 64 MB of K and V^T tiles (16 KB each)
 
 // Workgroups used for T tail steps (at most G, at least `least` steps each), the first step of workgroup w, and the workgroup holding step x.

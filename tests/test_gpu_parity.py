@@ -609,7 +609,7 @@ def test_combined_parts(P, n_full, few):
     x.K = (x.K.float() * 0.7).to(torch.bfloat16)
     nkt, items = -(-P // 64), -(-P // 512) * n_full
     tail = items % 256
-    parts = min(256, tail * nkt // 8)
+    parts = min(256, tail * nkt)
     assert tail and (parts < 8 * tail) == few
     heads = np.nonzero(modes == 2)[0]
     rows = [np.arange(512), 512 * (P // 1024) + np.arange(512), np.arange(P // 512 * 512, P)]
