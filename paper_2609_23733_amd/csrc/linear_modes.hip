@@ -25,6 +25,35 @@ __device__ __forceinline__ float sigmoid_fast(float x) {
     return rcp_fast(1.f + exp2f_fast(-kLog2e * x));
 }
 
+// Rows t0 .. t0 + rows - 1 of head h: the [d] vector vec[h].  8 lanes per row (8
+// values each), 32 rows per step of a workgroup of 256 threads.  MEAN heads are
+// written so by the kernel that computes the SURR heads (K7, K10c): its
+// workgroups for those heads would exit, and a launch of their own cost 4-9 us: layer of
+// 300 tokens 77.9 -> 74.5 us, of 10,992 314.6 -> 310.5, fp32 of 2,748 169.2 -> 163.6,
+// linear attention of 137,400 tokens 170.7 -> 164.5.
+__device__ __forceinline__ void broadcast_rows(const float* __restrict__ vec, int h, int64_t t0,
+                                               int rows, int64_t N, int H, void* __restrict__ Y,
+                                               int ydt) {
+    const int64_t t1 = (t0 + rows < N) ? t0 + rows : N;
+    const int seg = (threadIdx.x & 7) * 8, rr = threadIdx.x >> 3;
+    float mv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mv[j] = vec[h * kD + seg + j];
+    if (ydt == DT_BF16) {
+        const bf16x8 v = pack_bf16x8(mv[0], mv[1], mv[2], mv[3], mv[4], mv[5], mv[6], mv[7]);
+        for (int64_t row = t0 + rr; row < t1; row += 32)
+            *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(Y) + (row * H + h) * kD + seg) = v;
+    } else {
+        const float4 a = make_float4(mv[0], mv[1], mv[2], mv[3]);
+        const float4 b = make_float4(mv[4], mv[5], mv[6], mv[7]);
+        for (int64_t row = t0 + rr; row < t1; row += 32) {
+            float4* p = reinterpret_cast<float4*>(reinterpret_cast<float*>(Y) + (row * H + h) * kD + seg);
+            p[0] = a;
+            p[1] = b;
+        }
+    }
+}
+
 // Tokens per workgroup: 384 (fewer weight copies per token), down to 128
 // when that would leave fewer than kSurrMinGroups workgroups over all heads.
 constexpr int kSurrRows = 384;
@@ -46,9 +75,13 @@ __global__ __launch_bounds__(256, 4) void k_surrogate_bf16(
     const bf16* __restrict__ V, const uint8_t* __restrict__ modes, const float* __restrict__ ctx,
     const bf16* __restrict__ gw1, const float* __restrict__ gb1, const bf16* __restrict__ gw2,
     const float* __restrict__ gb2, const bf16* __restrict__ dw1, const float* __restrict__ db1,
-    const bf16* __restrict__ dw2, const float* __restrict__ db2, int64_t N, int H,
-    int rows, void* __restrict__ Y, int ydt) {
+    const bf16* __restrict__ dw2, const float* __restrict__ db2, const float* __restrict__ vmean,
+    int64_t N, int H, int rows, void* __restrict__ Y, int ydt) {
     const int h = blockIdx.y;
+    if (modes[h] == MODE_MEAN) {
+        broadcast_rows(vmean, h, (int64_t)blockIdx.x * rows, rows, N, H, Y, ydt);
+        return;
+    }
     if (modes[h] != MODE_SURR) return;
     const int64_t t0 = (int64_t)blockIdx.x * rows;
     const int64_t t1 = (t0 + rows < N) ? t0 + rows : N;
@@ -229,9 +262,13 @@ __global__ __launch_bounds__(256, 2) void k_surrogate_f32(
     const float* __restrict__ V, const uint8_t* __restrict__ modes, const float* __restrict__ ctx,
     const float* __restrict__ gw1, const float* __restrict__ gb1, const float* __restrict__ gw2,
     const float* __restrict__ gb2, const float* __restrict__ dw1, const float* __restrict__ db1,
-    const float* __restrict__ dw2, const float* __restrict__ db2, int add_v, int64_t N, int H,
-    void* __restrict__ Y, int ydt) {
+    const float* __restrict__ dw2, const float* __restrict__ db2, const float* __restrict__ vmean,
+    int add_v, int64_t N, int H, void* __restrict__ Y, int ydt) {
     const int h = blockIdx.y;
+    if (modes[h] == MODE_MEAN) {
+        broadcast_rows(vmean, h, (int64_t)blockIdx.x * kSurr32Rows, kSurr32Rows, N, H, Y, ydt);
+        return;
+    }
     if (modes[h] != MODE_SURR) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, hh = lane >> 5;
     __shared__ float sW1[2 * kL * kW1s];        // [gamma units | delta units][value feature]
@@ -335,37 +372,19 @@ __global__ __launch_bounds__(256, 2) void k_surrogate_f32(
 }
 
 // ------------------------------------------------------------------------
-// K8: a write-only stream of one [d] vector per head into every row: MEAN
-// heads (the value mean) and SURR heads of the no-residual ablation (C_h).
-// 8 lanes per row (8 values each); a workgroup covers 32 rows per step.
+// K8: MEAN heads and SURR heads of the no-residual ablation (C_h), a
+// write-only stream.
 // ------------------------------------------------------------------------
 constexpr int kMeanRows = 1024;
 
 __global__ __launch_bounds__(256) void k_broadcast_heads(const uint8_t* __restrict__ modes,
-                                                         int mode, const float* __restrict__ vmean,
-                                                         int64_t N, int H, void* __restrict__ Y,
-                                                         int ydt) {
+                                                         const float* __restrict__ vmean,
+                                                         const float* __restrict__ ctx, int64_t N,
+                                                         int H, void* __restrict__ Y, int ydt) {
     const int h = blockIdx.y;
-    if (modes[h] != mode) return;
-    const int64_t t0 = (int64_t)blockIdx.x * kMeanRows;
-    const int64_t t1 = (t0 + kMeanRows < N) ? t0 + kMeanRows : N;
-    const int seg = (threadIdx.x & 7) * 8, rr = threadIdx.x >> 3;
-    float mv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) mv[j] = vmean[h * kD + seg + j];
-    if (ydt == DT_BF16) {
-        const bf16x8 v = pack_bf16x8(mv[0], mv[1], mv[2], mv[3], mv[4], mv[5], mv[6], mv[7]);
-        for (int64_t row = t0 + rr; row < t1; row += 32)
-            *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(Y) + (row * H + h) * kD + seg) = v;
-    } else {
-        const float4 a = make_float4(mv[0], mv[1], mv[2], mv[3]);
-        const float4 b = make_float4(mv[4], mv[5], mv[6], mv[7]);
-        for (int64_t row = t0 + rr; row < t1; row += 32) {
-            float4* p = reinterpret_cast<float4*>(reinterpret_cast<float*>(Y) + (row * H + h) * kD + seg);
-            p[0] = a;
-            p[1] = b;
-        }
-    }
+    if (modes[h] != MODE_MEAN && modes[h] != MODE_SURR) return;
+    broadcast_rows(modes[h] == MODE_MEAN ? vmean : ctx, h, (int64_t)blockIdx.x * kMeanRows,
+                   kMeanRows, N, H, Y, ydt);
 }
 
 // ------------------------------------------------------------------------
@@ -659,12 +678,18 @@ __global__ __launch_bounds__(256) void k_linattn_combine(const uint8_t* __restri
 // exchange with lane l ^ 32.  Each wave takes kLinQBlocks blocks of 32
 // queries.
 constexpr int kLinQBlocks = 4;
+constexpr int kLinRows = 32 * 4 * kLinQBlocks;   // queries per workgroup
 
 __global__ __launch_bounds__(256) void k_linattn_apply(const float* __restrict__ Q,
                                                        const uint8_t* __restrict__ modes,
-                                                       const float* __restrict__ sums, int64_t N,
+                                                       const float* __restrict__ sums,
+                                                       const float* __restrict__ vmean, int64_t N,
                                                        int H, void* __restrict__ Y, int ydt) {
     const int h = blockIdx.y;
+    if (modes[h] == MODE_MEAN) {
+        broadcast_rows(vmean, h, (int64_t)blockIdx.x * kLinRows, kLinRows, N, H, Y, ydt);
+        return;
+    }
     if (modes[h] != MODE_SURR) return;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int n = lane & 31, hh = lane >> 5;
@@ -738,9 +763,14 @@ __global__ __launch_bounds__(256) void k_linattn_apply(const float* __restrict__
 // stay on fp32 MFMAs.)
 __global__ __launch_bounds__(256, 4) void k_linattn_apply_bf16(const bf16* __restrict__ Q,
                                                             const uint8_t* __restrict__ modes,
-                                                            const float* __restrict__ sums, int64_t N,
+                                                            const float* __restrict__ sums,
+                                                            const float* __restrict__ vmean, int64_t N,
                                                             int H, void* __restrict__ Y, int ydt) {
     const int h = blockIdx.y;
+    if (modes[h] == MODE_MEAN) {
+        broadcast_rows(vmean, h, (int64_t)blockIdx.x * kLinRows, kLinRows, N, H, Y, ydt);
+        return;
+    }
     if (modes[h] != MODE_SURR) return;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int n = lane & 31, hh = lane >> 5;
@@ -881,7 +911,7 @@ void launch_linear_heads(const AttnArgs& a, hipStream_t st) {
             hipLaunchKernelGGL(kern, dim3(nbs, a.H), dim3(256), 0, st, (const bf16*)a.V, a.modes, C,
                                (const bf16*)a.g_w1, a.g_b1, (const bf16*)a.g_w2, a.g_b2,
                                (const bf16*)a.d_w1, a.d_b1, (const bf16*)a.d_w2, a.d_b2,
-                               a.N, a.H, rows, a.Y, a.ydt);
+                               a.vmean, a.N, a.H, rows, a.Y, a.ydt);
         }
         else {
             const unsigned nb32 = (unsigned)((a.N + kSurr32Rows - 1) / kSurr32Rows);
@@ -889,34 +919,31 @@ void launch_linear_heads(const AttnArgs& a, hipStream_t st) {
             hipLaunchKernelGGL(kern, dim3(nb32, a.H), dim3(256), 0, st, (const float*)a.V,
                                a.modes, C, (const float*)a.g_w1, a.g_b1, (const float*)a.g_w2,
                                a.g_b2, (const float*)a.d_w1, a.d_b1, (const float*)a.d_w2,
-                               a.d_b2, add_v, a.N, a.H, a.Y, a.ydt);
+                               a.d_b2, a.vmean, add_v, a.N, a.H, a.Y, a.ydt);
         }
     } else if (v == SURR_NO_RESIDUAL) {
         const unsigned nb = (unsigned)((a.N + kMeanRows - 1) / kMeanRows);
-        hipLaunchKernelGGL(k_broadcast_heads, dim3(nb, a.H), dim3(256), 0, st, a.modes,
-                           (int)MODE_SURR, a.ctx, a.N, a.H, a.Y, a.ydt);
+        hipLaunchKernelGGL(k_broadcast_heads, dim3(nb, a.H), dim3(256), 0, st, a.modes, a.vmean,
+                           a.ctx, a.N, a.H, a.Y, a.ydt);
     } else {   // SURR_LINEAR_ATTN
         const dim3 gp((unsigned)a.n3, a.H), gc((kLinSums + 63) / 64, a.H),
-            ga((unsigned)((a.N + 32 * 4 * kLinQBlocks - 1) / (32 * 4 * kLinQBlocks)), a.H);
+            ga((unsigned)((a.N + kLinRows - 1) / kLinRows), a.H);
         if (a.dtype == DT_BF16) {
             hipLaunchKernelGGL(k_linattn_partial_bf16, gp, dim3(256), 0, st, (const bf16*)a.K,
                                (const bf16*)a.V, a.modes, a.N, a.H, a.chunk3, a.lpart);
             hipLaunchKernelGGL(k_linattn_combine, gc, dim3(256), 0, st, a.modes, a.lpart,
                                (int)a.n3, a.lsum);
             hipLaunchKernelGGL(k_linattn_apply_bf16, ga, dim3(256), 0, st, (const bf16*)a.Q, a.modes,
-                               a.lsum, a.N, a.H, a.Y, a.ydt);
+                               a.lsum, a.vmean, a.N, a.H, a.Y, a.ydt);
         } else {
             hipLaunchKernelGGL(k_linattn_partial, gp, dim3(256), 0, st, (const float*)a.K,
                                (const float*)a.V, a.modes, a.N, a.H, a.chunk3, a.lpart);
             hipLaunchKernelGGL(k_linattn_combine, gc, dim3(256), 0, st, a.modes, a.lpart,
                                (int)a.n3, a.lsum);
             hipLaunchKernelGGL(k_linattn_apply, ga, dim3(256), 0, st, (const float*)a.Q, a.modes,
-                               a.lsum, a.N, a.H, a.Y, a.ydt);
+                               a.lsum, a.vmean, a.N, a.H, a.Y, a.ydt);
         }
     }
-    const unsigned nbm = (unsigned)((a.N + kMeanRows - 1) / kMeanRows);
-    hipLaunchKernelGGL(k_broadcast_heads, dim3(nbm, a.H), dim3(256), 0, st, a.modes,
-                       (int)MODE_MEAN, a.vmean, a.N, a.H, a.Y, a.ydt);
 }
 
 }  // namespace vp
