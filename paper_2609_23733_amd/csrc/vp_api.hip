@@ -40,12 +40,20 @@ bool make_layout(const vp_shape* s, Layout* L) {
     if (s->dtype != VP_F32 && s->dtype != VP_BF16) return false;
     const int64_t N = s->S * s->P;
     L->N = N;
-    int64_t c1 = cdiv(N, 64);
-    c1 = c1 < 256 ? 256 : cdiv(c1, 128) * 128;
+    // Pooling: whole steps of 4 waves x 32 tokens, at most 64 chunks a head.  One
+    // step at least: short layers wait for a workgroup's chain of steps (bf16
+    // router, us, 256 and 128 tokens at least: 1,374 tokens 21.9 and 20.7, 2,748
+    // 22.9 and 22.7, the same from 16,384 on).
+    const int64_t c1 = cdiv(cdiv(N, 64), 128) * 128;
     L->chunk1 = c1;
     L->n1 = cdiv(N, c1);
-    int64_t c2 = cdiv(N, 512);
-    L->chunk2 = c2 < 64 ? 64 : c2;
+    // Routing: at most 512 chunks of 64 tokens or more; below 16,384 tokens one
+    // chunk per CU, of 16 tokens or more (bf16 router, us, chunks of 64, 32 and
+    // 16 tokens: 300 tokens 23.6, 21.4, 20.3; 1,374 26.2, 23.2, 21.9; 5,496 30.4,
+    // 27.0, 28.1; 10,992 33.9, 33.9, 35.7).
+    int64_t c2 = cdiv(cdiv(N, 256), 8) * 8;
+    c2 = c2 < 16 ? 16 : (c2 > 64 ? 64 : c2);
+    L->chunk2 = cdiv(N, 512) > c2 ? cdiv(N, 512) : c2;
     L->n2 = cdiv(N, L->chunk2);
     L->nkt = cdiv(N, 64);
     // linear-attention chunks: at most 128 per head, whole 64-token tiles

@@ -136,11 +136,11 @@ def test_ragged_token_counts(dtype, P):
     check_y(layer.Y.double().cpu().numpy(), ref["Y"], dtype, False, label="P=%d" % P)
 
 
-@pytest.mark.parametrize("P", [64, 4096, 4097, 16384, 32769])
+@pytest.mark.parametrize("P", [15, 64, 1024, 1025, 4097, 8192, 32705, 32769])
 def test_router_chunk_counts(P):
-    """The combine of the routing and pooling partials: 1, 64, 65, 256 and 505 routing
-    chunks and 1, 16, 17, 64 and 52 pooling chunks (64 groups of threads, up to 8 chunks
-    each)."""
+    """Chunks of the router's reductions and their combine (64 groups of threads, up to 8
+    chunks each): 1, 4, 64, 65, 171, 256, 512 and 505 routing chunks, 1, 1, 8, 9, 33, 64,
+    64 and 52 pooling chunks, with ragged last ones."""
     log("router chunks P=%d" % P)
     x = synth.make_layer(1, P, dtype="bf16", key=(14, P), sharp=True,
                          modes=np.zeros(16, np.uint8), qkv_device="cuda")
