@@ -177,7 +177,10 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # The handle of torch.cuda.current_stream(), without building the Stream
+    # object: 0.3 against 2.9 us, and a layer of 300 tokens asks four times in
+    # the 77 us that enqueueing it takes.
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _need(t: torch.Tensor, name: str, shape=None, dtype=None):
