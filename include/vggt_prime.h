@@ -137,7 +137,8 @@ typedef struct {
 
 /* Bytes of device workspace that vp_router_score, vp_routed_global_attention
  * and its stages need for `shape` (0 if the shape is invalid).  The workspace
- * holds router partial sums, the gathered keys and values of FULL heads, the
+ * holds router partial sums, the gathered keys and values of FULL heads (bf16
+ * layers, and fp32 layers past 1,024 tokens), the
  * FULL kernel's partial results and the linear-attention sums; it must be 256-byte
  * aligned and may be reused across calls on one stream (calls on different
  * streams need separate workspaces). */
@@ -356,7 +357,7 @@ vp_status vp_latent_loss(const vp_shape *shape, const void *D_hat, const void *D
  *             -1 for destinations;
  *   score     [N] (may be null): that cosine similarity (fp32), 0 for
  *             destinations.
- *   Workspace: vp_tome_workspace_bytes(shape) (~190 bytes per token).
+ *   Workspace: vp_tome_workspace_bytes(shape) (~190 bytes per token and 50 KB).
  * vp_tome_merge: Xm[r] = mean of X[t] over the members of row r, fp32 sums
  *   in member order, one rounding; X [N, H * 64] -> Xm [nrows, H * 64] in the
  *   shape's dtype.  Member entries outside [0, N) are skipped.

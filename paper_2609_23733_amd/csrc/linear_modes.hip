@@ -6,7 +6,7 @@
 // value mean as context, no residual correction (y_i = C_h), the identity
 // added (y_i = v_i + Eq.7) and linear attention in place of the surrogate.
 // Each kernel runs over (token block, head) and exits unless modes[h] is its
-// mode.
+// mode; the kernels that write SURR heads write MEAN heads, too.
 //
 // The first MLP layer splits z = [v; C] into W1 = [W1_v | W1_C]: the context
 // half W1_C C_h + b1 is the same for every token of a head and is computed
