@@ -103,9 +103,9 @@ __global__ __launch_bounds__(256) void k_tome_metric(const bf16* __restrict__ K,
 // over the workgroups; the parts of a source meet in an atomic maximum of
 // (ordered v, complement of the slot), so the lower slot wins on equal values
 // whatever the order.  Every 16 tiles a part publishes what it has found and
-// takes the value just below the source's maximum so far as its own lower
-// bound: that leaves out only destinations that are strictly worse than a
-// published one, so the outcome does not depend on when it is read.
+// takes a value below the source's maximum so far (the next one, but past -0)
+// as its own lower bound: that leaves out only destinations that are strictly
+// worse than a published one, so the outcome does not depend on when it is read.
 // 108,405 sources x 28,995 destinations (S = 100, 75 %): 911 -> 475 us, 325 of
 // them without a block past its bound (the products alone would take 160).
 // Screening on rows scaled beforehand (a tighter bound, the products taken
@@ -213,7 +213,10 @@ __global__ __launch_bounds__(64 * kTmWaves, 1) void k_tome_match(const bf16* __r
 #pragma unroll
             for (int kb = 0; kb < kTmKB; ++kb) {
                 const uint32_t u = __shfl((uint32_t)(known[kb] >> 32), n);
-                const float low = u > 0x007fffffu ? float_unorder(u - 1) : -INFINITY;
+                // (-0 is ordered just below +0 but equals it: below a maximum of 0 comes
+                // the largest negative value, here the largest normal one)
+                const float low = u == 0x80000000u ? -0x1p-126f
+                                  : u > 0x007fffffu ? float_unorder(u - 1) : -INFINITY;
                 if (low > acc[kb]) {
                     acc[kb] = low;
                     idx[kb] = -1;

@@ -239,6 +239,29 @@ def test_match_zero_and_nan_rows(S, P, M):
     assert int((plan.row.cpu().numpy()[s] == plan.row.cpu().numpy()[best[s]]).sum()) == M
 
 
+@pytest.mark.parametrize("S,P,frac", [(16, 4096, 0.75), (40, 1374, 0.6)])
+def test_match_best_of_zero(S, P, frac):
+    """Sources whose best similarity is exactly 0: a few destinations with a zero row, all
+    others opposite to every source.  Every source takes the first zero destination in token
+    order, also where a workgroup's part of the destinations (44 and 39 tiles of 64) has
+    others' finds, zeros at later places, as its lower bound before it comes to that one."""
+    log("tome best of zero S=%d P=%d" % (S, P))
+    N, M = S * P, int(frac * S * P)
+    is_dst, _ = oracle.tome_split(S, P, M)
+    d, s = np.nonzero(is_dst)[0], np.nonzero(~is_dst)[0]
+    base = synth.normal((1, 1, 64), synth.derive_seed(51, S, P), 1.0)
+    sign = torch.from_numpy(np.where(is_dst, -1.0, 1.0)).float()[:, None, None]
+    K = (base * sign + 0.1 * synth.normal((N, 16, 64), synth.derive_seed(52, S, P), 1.0)).to(
+        torch.bfloat16)
+    zero = np.arange(64 * 40 + 5, len(d), 64 * 4)
+    K[torch.from_numpy(d[zero])] = 0
+    for rep in range(3):
+        plan = run_plan(K, S, P, M)
+        best = plan.best.cpu().numpy()[s]
+        other, nonzero = int((best != d[zero[0]]).sum()), int((plan.score.cpu().numpy()[s] != 0).sum())
+        assert other == 0 and nonzero == 0, (rep, other, nonzero, len(s))
+
+
 def planted_keys(S, P, seed):
     """Random keys; 40 sources are power-of-two multiples of one destination
     (exact cosine ties on both sides), 100 more are noisy copies of other
