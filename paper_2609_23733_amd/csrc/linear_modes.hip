@@ -428,8 +428,9 @@ __device__ __forceinline__ float elu1(float x) {
     return x > 0.f ? x + 1.f : exp2f_fast(x * kLog2e);
 }
 
-// x = b[0] + b[1] + b[2] exactly (24 significant bits; x finite and not so small
-// that the last part is subnormal), for eight values.
+// x = b[0] + b[1] + b[2] exactly (24 significant bits; |x| below 2^128 - 2^119, which
+// rounds to an infinity in bf16, and not so small that the last part is subnormal),
+// for eight values.
 __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&b)[3]) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -779,8 +780,9 @@ __global__ __launch_bounds__(256) void k_linattn_apply(const float* __restrict__
 
 // K10c for bf16 layers, on 32x32x16 bf16 MFMAs: S^T split once per workgroup into LDS
 // (three 64 x 64 matrices, rows dv), phi(Q) split per block in registers: lane l holds
-// features 16 ks + 8 (l / 32) .. + 7 of query l % 32.  (Sums that are not all finite
-// stay on fp32 MFMAs.)
+// features 16 ks + 8 (l / 32) .. + 7 of query l % 32.  (Heads whose sums do not all
+// split, because one is not finite or rounds to an infinity in bf16, stay on fp32
+// MFMAs.)
 __global__ __launch_bounds__(256, 4) void k_linattn_apply_bf16(const bf16* __restrict__ Q,
                                                             const uint8_t* __restrict__ modes,
                                                             const float* __restrict__ sums,
@@ -807,7 +809,7 @@ __global__ __launch_bounds__(256, 4) void k_linattn_apply_bf16(const bf16* __res
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 x[j] = sh[(dk0 + 8 * c + j) * kD + dv];
-                bad |= !(fabsf(x[j]) < INFINITY);
+                bad |= !(fabsf(x[j]) < 0x1.ffp127f);
             }
             split3(x, b);
 #pragma unroll

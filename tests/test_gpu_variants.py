@@ -250,3 +250,23 @@ def test_linear_attention_split(P, bad):
             assert np.isposinf(g[:, 11]).all()
             g, ref = np.delete(g, 11, 1), np.delete(ref, 11, 1)
         assert np.linalg.norm(g - ref) <= 5e-7 * np.linalg.norm(ref), (P, h)
+
+
+def test_linear_attention_largest_sums():
+    """bf16 linear attention with sums that are finite in fp32 and round to infinity in bf16:
+    S = 2^127 + (2^127 - 2^119) in every row of one feature, phi(k) = 1, so y is half of it."""
+    log("linear attention largest sums")
+    from paper_2609_23733_amd import vp
+    x = synth.make_layer(1, 2, dtype="bf16", key=(72, 0), modes=np.ones(16, np.uint8))
+    x.Q[:] = -8.0
+    x.K[:] = 0.0
+    x.V[0, :, 5] = 2.0 ** 127
+    x.V[1, :, 5] = 2.0 ** 127 - 2.0 ** 119
+    layer = vp.RoutedLayer(x, y_dtype=torch.float32, surr_variant=vp.SURR_LINEAR_ATTN)
+    layer.step()
+    torch.cuda.synchronize()
+    Y = layer.Y.double().cpu().numpy()
+    for h in (0, 15):
+        ref = oracle.linattn_rows(x.Q, x.K, x.V, h)
+        assert np.isfinite(Y[:, h]).all()
+        assert (np.abs(Y[:, h] - ref) <= 1e-6 * np.abs(ref).max(0)).all()
