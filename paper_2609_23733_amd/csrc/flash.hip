@@ -1517,7 +1517,10 @@ __global__ __launch_bounds__(256) void k_flash_f32_combine(const int32_t* __rest
 // K is scaled per head, V per head and feature (undone at the end, so that
 // every feature keeps its own precision), Q per query.  Heads and items with a
 // value that is not finite or whose largest magnitude lies outside [2^-60, 2^60]
-// (zero aside) are flagged and left to K6.
+// (zero aside) are flagged and left to K6, and so are items whose logits may reach 2^24
+// (64 |q| |k| c, the largest magnitudes of the query and of the head's K): a query's
+// reference point is a rounded logit, by up to half an ulp, and its weights, then as
+// large as 2 to the power of that, must stay in fp16's range times 2^14.
 //   k_absmax_f32: per group of token rows, largest |k| and per feature |v|, as
 //   integer bits (a NaN is larger than any number);
 //   k_pack_f32: scales, and per 64-key tile K hi, K lo (rows in swap23 order),
@@ -1528,7 +1531,8 @@ constexpr int kWG32 = 512;       // workgroups: two per CU
 constexpr int kMinTiles32 = 4;   // fewest key tiles per workgroup in the tail
 constexpr uint32_t kTile32 = 32768;    // bytes of a packed key tile
 constexpr int kMax32 = kD + 1;         // |v| per feature, |k|
-constexpr int kScale32 = kD + 4;       // per slot: 2^e_d of V, 2^e of K, exact flag, 2 pad
+constexpr int kScale32 = kD + 4;       // per slot: 2^e_d of V, 2^e of K, exact flag, |k|, 1 pad
+constexpr float kMaxProduct32 = 0x1p18f;   // |q| |k| c of the items that K6e computes
 constexpr int kMaxGroups32 = 64;
 
 __host__ __device__ inline int64_t f32_group_rows(int64_t N) {   // rows per maximum group
@@ -1622,6 +1626,7 @@ __global__ __launch_bounds__(256) void k_pack_f32(const float* __restrict__ K,
         if (t < kD) scales[slot * kScale32 + t] = f32_in_range(smax[t]) ? pow2(f32_exponent(smax[t])) : 1.f;
         if (t == kD) scales[slot * kScale32 + kD] = f32_in_range(smax[kD]) ? pow2(ek) : 1.f;
         if (t == kD + 1) scales[slot * kScale32 + kD + 1] = any ? 1.f : 0.f;
+        if (t == kD + 2) scales[slot * kScale32 + kD + 2] = __uint_as_float(smax[kD]);
     }
     // (out of range: any scale, the tiles are not used)
     const float dk = f32_in_range(smax[kD]) ? pow2(-ek) : 1.f;
@@ -1713,7 +1718,9 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
             for (int j = 0; j < 4; ++j) mq = max(mq, __float_as_uint(q[i][j]) & 0x7fffffffu);
         mq = max(mq, (uint32_t)__shfl_xor(mq, 32));
         // (also the barrier between one segment's LDS reads and the next's writes)
-        const bool exact = __syncthreads_or(!f32_in_range(mq) || sc[kD + 1] != 0.f) != 0;
+        const bool exact = __syncthreads_or(!f32_in_range(mq) || sc[kD + 1] != 0.f ||
+                                            !(__uint_as_float(mq) * sc[kD + 2] * c <
+                                              kMaxProduct32)) != 0;
         if (t0 == 0 && threadIdx.x == 0) left[L] = exact;
         if (exact) return;   // uniform over the workgroup
         const int eq = f32_exponent(mq);

@@ -231,6 +231,32 @@ def test_fp32_split_full_heads(case, P):
         assert (err <= bound).all(), (case, int(h), float((err / bound).max()))
 
 
+@pytest.mark.parametrize("scale", [64.0, 4096.0, 16384.0])
+def test_fp32_large_logits(scale):
+    """fp32 FULL heads past 1,024 tokens with logits up to about 2^15, 2^27 and 2^31 (log2
+    units), where half an ulp of a softmax reference point reaches 64: every row whose two
+    largest logits lie further apart than fp32 dot products can move them (64 roundings of
+    2^-24 of sum |q k| each, both logits) and 40 is that key's value row, to 1e-6."""
+    log("fp32 large logits x%g" % scale)
+    P = 1100
+    x = synth.make_layer(1, P, dtype="f32", n_full=3, n_surr=0, key=(62, P), sharp=True)
+    x.Q *= scale
+    x.K *= scale
+    Y = run_gpu(x, y_dtype=torch.float32).Y.double().cpu().numpy()
+    for h in np.nonzero(x.modes == 2)[0]:
+        q, k, v = (t[:, int(h)].double().numpy() for t in (x.Q, x.K, x.V))
+        t = C_LOG2 * (q @ k.T)
+        moved = C_LOG2 * 2.0 ** -17 * (np.abs(q) @ np.abs(k).T).max(1)
+        top2 = np.sort(t, axis=1)[:, -2:]
+        sure = top2[:, 1] - top2[:, 0] > moved + 40
+        assert sure.mean() > 0.5 if scale == 64 else sure.mean() > 0.9
+        g, ref = Y[sure, h], v[t.argmax(1)[sure]]
+        lost = int((~np.isfinite(Y[:, h])).any(1).sum())
+        assert lost == 0, (scale, int(h), lost)
+        ratio = float((np.abs(g - ref) / (1e-6 * np.abs(ref) + 2.0 ** -30 * np.abs(v).max())).max())
+        assert ratio <= 1, (scale, int(h), ratio)
+
+
 def test_single_token():
     """N = 1: FULL returns v, MEAN returns v, s = 1 (every head FULL under Eq.4)."""
     log("N=1")
