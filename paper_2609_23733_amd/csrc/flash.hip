@@ -1505,22 +1505,26 @@ __global__ __launch_bounds__(256) void k_flash_f32_combine(const int32_t* __rest
 }
 
 // ------------------------------------------------------------------------
-// K6e (fp32, longer layers).  Every operand is a sum of two fp16 values times a power of two, x
-// 2^-e = hi + lo (both rounded to nearest: the remainder is at most 2^-24 |x|,
-// like fp32's own rounding, and 2^-39 of the largest value of its group where lo is
-// subnormal), and a product takes three 32x32x16 fp16 MFMAs, lo hi + hi lo + hi hi
-// (lo lo is at most 2^-24 of it), 96 cycles per 16 values against 512 for the
-// 32x32x2 fp32 MFMA; all sums stay fp32.  Measured against float64 the
-// error is smaller than with fp32 MFMAs, whose 64 products per sum are added
+// K6e (fp32, longer layers).  Every operand is a power of two times hi + 2^-11 lo, two
+// fp16 values (both rounded to nearest: the remainder is at most 2^-23 |x|, and 2^-49 of
+// the largest value of its group where lo is subnormal; lo is held times 2^11, so that
+// it is as far from that as hi), and a product takes three 32x32x16 fp16 MFMAs,
+// 2^-11 (lo hi + hi lo) + hi hi (2^-22 lo lo is at most 2^-22 of it), 96 cycles per 16
+// values against 512 for the 32x32x2 fp32 MFMA; all sums stay fp32.  The bounds are
+// wider than fp32's rounding of a value (2^-24), but on random values the error
+// against float64 is smaller than with fp32 MFMAs, whose 64 products per sum are added
 // one by one (of the output norm, 2,748 tokens: 1.3e-7 against 1.9e-7; sharp
 // heads 2.1e-7 against 3.5e-7, Q x 3 4.2e-7 against 9.4e-7).
 // K is scaled per head, V per head and feature (undone at the end, so that
-// every feature keeps its own precision), Q per query.  Heads and items with a
-// value that is not finite or whose largest magnitude lies outside [2^-60, 2^60]
-// (zero aside) are flagged and left to K6, and so are items whose logits may reach 2^24
-// (64 |q| |k| c, the largest magnitudes of the query and of the head's K): a query's
-// reference point is a rounded logit, by up to half an ulp, and its weights, then as
-// large as 2 to the power of that, must stay in fp16's range times 2^14.
+// every feature keeps its own precision), Q per query.  Left to K6 are:
+//   - heads and items with a value that is not finite or whose largest magnitude lies
+//     outside [2^-60, 2^60] (zero aside);
+//   - heads with a row of V all of whose features lie below 2^-20 of their largest: small
+//     weights (held to 2^-50 of the largest) on the other rows could outweigh it;
+//   - items whose logits may reach 2^24 (64 |q| |k| c, the largest magnitudes of the query
+//     and of the head's K): a query's reference point is a rounded logit, by up to half an
+//     ulp, and its weights, then as large as 2 to the power of that, must stay in fp16's
+//     range times 2^14.
 //   k_absmax_f32: per group of token rows, largest |k| and per feature |v|, as
 //   integer bits (a NaN is larger than any number);
 //   k_pack_f32: scales, and per 64-key tile K hi, K lo (rows in swap23 order),
@@ -1543,13 +1547,15 @@ __host__ __device__ inline int64_t f32_group_rows(int64_t N) {   // rows per max
 __global__ __launch_bounds__(256) void k_absmax_f32(const float* __restrict__ K,
                                                     const float* __restrict__ V,
                                                     const int32_t* __restrict__ buckets, int64_t N,
-                                                    int H, uint32_t* __restrict__ part) {
+                                                    int H, uint32_t* __restrict__ part,
+                                                    float* __restrict__ scales) {
     const int slot = blockIdx.y;
     if (slot >= full_count(buckets, H)) return;
     const int h = full_head(buckets, H, slot);
     if (h < 0) return;
     __shared__ uint32_t s[kMax32];
     if (threadIdx.x < kMax32) s[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) scales[slot * kScale32 + kD + 1] = 0.f;
     __syncthreads();
     const int64_t rows = f32_group_rows(N), r0 = (int64_t)blockIdx.x * rows;
     const int64_t r1 = r0 + rows < N ? r0 + rows : N;
@@ -1584,10 +1590,11 @@ __device__ __forceinline__ bool f32_in_range(uint32_t m) {
 }
 __device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
 
-// x = hi + lo (x already scaled).
+// x = hi + 2^-11 lo (x already scaled, at most 2^15: |lo| is at most 2^14).
+constexpr float kLow32 = 0x1p-11f;
 __device__ __forceinline__ void split16(float x, f16& hi, f16& lo) {
     hi = (f16)x;
-    lo = (f16)(x - (float)hi);
+    lo = (f16)((x - (float)hi) * (1.f / kLow32));
 }
 
 __global__ __launch_bounds__(256) void k_pack_f32(const float* __restrict__ K,
@@ -1620,12 +1627,11 @@ __global__ __launch_bounds__(256) void k_pack_f32(const float* __restrict__ K,
     }
     __syncthreads();
     const int ek = f32_exponent(smax[kD]);
+    bool bad = false;
     if (tile == 0) {
-        const bool bad = t < kMax32 && !f32_in_range(smax[t]);
-        const bool any = __syncthreads_or(bad) != 0;
+        bad = t < kMax32 && !f32_in_range(smax[t]);
         if (t < kD) scales[slot * kScale32 + t] = f32_in_range(smax[t]) ? pow2(f32_exponent(smax[t])) : 1.f;
         if (t == kD) scales[slot * kScale32 + kD] = f32_in_range(smax[kD]) ? pow2(ek) : 1.f;
-        if (t == kD + 1) scales[slot * kScale32 + kD + 1] = any ? 1.f : 0.f;
         if (t == kD + 2) scales[slot * kScale32 + kD + 2] = __uint_as_float(smax[kD]);
     }
     // (out of range: any scale, the tiles are not used)
@@ -1646,16 +1652,24 @@ __global__ __launch_bounds__(256) void k_pack_f32(const float* __restrict__ K,
         *reinterpret_cast<f16x8*>(p) = hi;
         *reinterpret_cast<f16x8*>(p + 8192) = lo;
     }
+    float vmax = 0.f;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         const uint32_t m = smax[dseg + j];
         const float dv = f32_in_range(m) ? pow2(-f32_exponent(m)) : 1.f;
+        const float x = ok ? vv[j >> 2][j & 3] * dv : 0.f;
         f16 a, b;
-        split16(ok ? vv[j >> 2][j & 3] * dv : 0.f, a, b);
+        split16(x, a, b);
+        vmax = fmaxf(vmax, fabsf(x));
         sT[0][(dseg + j) * kLdsRow + key] = a;
         sT[1][(dseg + j) * kLdsRow + key] = b;
     }
-    __syncthreads();
+    // (a feature's largest value is scaled to 2^13 .. 2^14; four lanes hold a row)
+    vmax = fmaxf(vmax, __shfl_xor(vmax, 1));
+    vmax = fmaxf(vmax, __shfl_xor(vmax, 2));
+    bad |= vmax > 0.f && vmax < 0x1p-6f;
+    if (__syncthreads_or(bad) && t == 0)
+        atomicOr((uint32_t*)&scales[slot * kScale32 + kD + 1], 1u);
     const int d = t >> 2;
 #pragma unroll
     for (int p = 0; p < 2; ++p)
@@ -1718,7 +1732,7 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
             for (int j = 0; j < 4; ++j) mq = max(mq, __float_as_uint(q[i][j]) & 0x7fffffffu);
         mq = max(mq, (uint32_t)__shfl_xor(mq, 32));
         // (also the barrier between one segment's LDS reads and the next's writes)
-        const bool exact = __syncthreads_or(!f32_in_range(mq) || sc[kD + 1] != 0.f ||
+        const bool exact = __syncthreads_or(!f32_in_range(mq) || __float_as_uint(sc[kD + 1]) ||
                                             !(__uint_as_float(mq) * sc[kD + 2] * c <
                                               kMaxProduct32)) != 0;
         if (t0 == 0 && threadIdx.x == 0) left[L] = exact;
@@ -1770,6 +1784,10 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
                     S[kb] = mfma_f16(kh[ks][kb], ql[ks], S[kb]);
                 }
 #pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) S[kb][i] *= kLow32;
+#pragma unroll
             for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) S[kb] = mfma_f16(kh[ks][kb], qh[ks], S[kb]);
@@ -1792,10 +1810,9 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
             const float mn = fmaxf(m, mx * cs);
             const float al = exp2f_fast(m - mn);
             m = mn;
-            // The weights are split times 2^14 (the low halves of all but the
-            // smallest are then normal), a factor that O keeps until the
-            // end.  (Added to the exponent it would cost the precision
-            // of an argument near 14.)
+            // The weights are split times 2^14, a factor that O keeps until the end.
+            // (Added to the exponent it would cost the precision of an argument
+            // near 14.)
             float ls = 0.f;
             f16x8 ph[2][2], pl[2][2];
 #pragma unroll
@@ -1811,7 +1828,8 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
                         ls += e[1];
                         const f32x2 es = {e[0] * 16384.f, e[1] * 16384.f};
                         const f16x2 eh = __builtin_convertvector(es, f16x2);
-                        const f32x2 er = {es[0] - (float)eh[0], es[1] - (float)eh[1]};
+                        const f32x2 er = {(es[0] - (float)eh[0]) * (1.f / kLow32),
+                                          (es[1] - (float)eh[1]) * (1.f / kLow32)};
                         h4[j] = __builtin_bit_cast(uint32_t, eh);
                         l4[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(er, f16x2));
                     }
@@ -1836,6 +1854,10 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
                     vh[kc][db] = frag(buf, 2, db, kc);
                     Ot[db] = mfma_f16(vh[kc][db], pl[kc >> 1][kc & 1], Ot[db]);
                 }
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) Ot[db][r] *= kLow32;
 #pragma unroll
             for (int kc = 0; kc < 4; ++kc)
 #pragma unroll
@@ -2071,7 +2093,7 @@ void launch_flash(const AttnArgs& a, hipStream_t st) {
         float* scales = a.fmax + (size_t)a.H * ng * kMax32;
         int32_t* left = (int32_t*)(scales + (size_t)a.H * kScale32);
         hipLaunchKernelGGL(k_absmax_f32, dim3(ng, a.H), dim3(256), 0, st, (const float*)a.K,
-                           (const float*)a.V, a.buckets, a.N, a.H, mx);
+                           (const float*)a.V, a.buckets, a.N, a.H, mx, scales);
         hipLaunchKernelGGL(k_pack_f32, dim3(nkt, a.H), dim3(256), 0, st, (const float*)a.K,
                            (const float*)a.V, a.buckets, a.N, a.H, nkt, (const uint32_t*)mx, ng,
                            scales, (char*)a.ftiles);

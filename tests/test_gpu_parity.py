@@ -257,6 +257,36 @@ def test_fp32_large_logits(scale):
         assert ratio <= 1, (scale, int(h), ratio)
 
 
+@pytest.mark.parametrize("case,b", [("features", 12), ("features", 16), ("features", 20),
+                                    ("features", 24), ("rows", 8), ("rows", 16), ("rows", 24),
+                                    ("cells", 20)])
+def test_fp32_split_unequal_sizes(case, b):
+    """fp32 FULL heads past 1,024 tokens whose operands differ much in size: half of K's
+    features 2^-b and Q's 2^b times the others (the same logits), and value rows, or half of
+    their features, 2^-b of the others that get all the weight (the others' logits are 80
+    below).  Bound as in test_fp32_split_full_heads, with the size of the rows that have the
+    weight."""
+    log("fp32 unequal sizes %s 2^%d" % (case, b))
+    P = 1100
+    x = synth.make_layer(1, P, dtype="f32", n_full=3, n_surr=0, key=(63, P), sharp=True)
+    if case == "features":
+        x.K[:, :, :32] *= 2.0 ** -b
+        x.Q[:, :, :32] *= 2.0 ** b
+    else:
+        x.Q[:, :, 0] = 30.0
+        x.K[0::2, :, 0] = 0.0
+        x.K[1::2, :, 0] = -16.0
+        x.V[0::2, :, :64 if case == "rows" else 32] *= 2.0 ** -b
+    Y = run_gpu(x, y_dtype=torch.float32).Y.double().cpu().numpy()
+    for h in np.nonzero(x.modes == 2)[0]:
+        ref = oracle.full_rows(x.Q, x.K, x.V, int(h))
+        err = np.linalg.norm(Y[:, h] - ref, axis=0)
+        scale = np.abs(x.V[0::2, int(h)].double().numpy()).max(0)
+        ratio = float((err / (1e-6 * np.linalg.norm(ref, axis=0) + 2e-7 * scale)).max())
+        log("  head %d worst err/bound %.3f" % (h, ratio))
+        assert ratio <= 1, (case, b, int(h), ratio)
+
+
 def test_single_token():
     """N = 1: FULL returns v, MEAN returns v, s = 1 (every head FULL under Eq.4)."""
     log("N=1")
