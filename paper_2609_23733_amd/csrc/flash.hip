@@ -1288,47 +1288,28 @@ __global__ __launch_bounds__(256, 2) void k_flash_bf16_wide(const bf16* __restri
 // matching V row from LDS.  Small layers (few work items for the chip) split
 // each item's key tiles into two halves run by separate workgroups; each
 // half writes O (unnormalized, relative to its reference point m), l and m
-// per query, and K6d combines the two halves in order.  With `only`, runs the
-// items flagged there (those that K6e left).
+// per query, and K6d combines the two halves in order.  Longer layers run K6e,
+// and K6's loop there for the segments that K6e does not split.
 // ------------------------------------------------------------------------
 constexpr int kBQ32 = 128;
 constexpr int kKRow32 = 65;   // odd stride: column reads are bank-conflict free
 constexpr int kRec32 = kD + 4;   // part record: O[64], l, m, 2 pad (16-byte aligned)
 
-__global__ __launch_bounds__(256, 2) void k_flash_f32(const float* __restrict__ Q,
-                                                      const float* __restrict__ K,
-                                                      const float* __restrict__ V,
-                                                      const int32_t* __restrict__ buckets,
-                                                      int64_t N, int H, int nqt, int nkt, float c,
-                                                      int splits, const int32_t* __restrict__ only,
-                                                      float* __restrict__ part,
-                                                      void* __restrict__ Y, int ydt) {
-    const int nfull = full_count(buckets, H);
-    const int active = nfull * nqt;
-    if ((int)blockIdx.x >= active * splits) return;
-    const int Lx = xcd_remap(blockIdx.x, active * splits);
-    const int L = Lx / splits, half = Lx - L * splits;
-    if (only && !only[L]) return;
-    const int slot = L / nqt, qt = L - slot * nqt;
-    // key tiles [t0, t1) of the item (all of them unless split)
-    const int t0 = (int)((int64_t)half * nkt / splits);
-    const int t1 = (int)((int64_t)(half + 1) * nkt / splits);
-    const int h = full_head(buckets, H, slot);
-    if (h < 0) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int n = lane & 31, hh = lane >> 5;
-
-    __shared__ float sK[2][kBK * kKRow32];
-    __shared__ __attribute__((aligned(16))) float sV[2][kBK * kD];
-
-    const int64_t qi = (int64_t)qt * kBQ32 + wave * 32 + n;
-    const bool qok = qi < N;
+// Key tiles t0 .. t1 - 1 for the lane's query (row qp of Q; zeros unless qok): O and l
+// relative to m, l this lane half's share.  kLean: fewer LDS reads in flight, for K6e,
+// whose registers would spill otherwise.
+constexpr int kLds32 = 2 * kBK * (kKRow32 + kD);   // floats: two buffers of K and V rows
+template <bool kLean>
+__device__ __forceinline__ void f32_tiles(const float* __restrict__ qp, bool qok,
+                                          const float* __restrict__ K,
+                                          const float* __restrict__ V, int64_t N, int H, int h,
+                                          int t0, int t1, float c, float* __restrict__ sK,
+                                          float* __restrict__ sV, f32x16 (&O)[2], float& m,
+                                          float& l) {
+    const int lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
     float Qf[32];
-    {
-        const float* qp = Q + ((qok ? qi : 0) * H + h) * kD + hh;
 #pragma unroll
-        for (int ks = 0; ks < 32; ++ks) Qf[ks] = qok ? qp[2 * ks] : 0.f;
-    }
+    for (int ks = 0; ks < 32; ++ks) Qf[ks] = qok ? qp[2 * ks + hh] : 0.f;
 
     const int lr = threadIdx.x >> 2, lc = (threadIdx.x & 3) * 16;
     // Keys past N read row 0 (in bounds); their logits are masked to -inf,
@@ -1346,14 +1327,15 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32(const float* __restrict__ 
         d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
     };
     auto lstore = [&](int buf) {
-        float* kd = &sK[buf][lr * kKRow32 + lc];
+        float* kd = sK + buf * kBK * kKRow32 + lr * kKRow32 + lc;
         put4(kd, pk0); put4(kd + 4, pk1); put4(kd + 8, pk2); put4(kd + 12, pk3);
-        float4* vd = reinterpret_cast<float4*>(&sV[buf][lr * kD + lc]);
+        float4* vd = reinterpret_cast<float4*>(sV + buf * kBK * kD + lr * kD + lc);
         vd[0] = pv0; vd[1] = pv1; vd[2] = pv2; vd[3] = pv3;
     };
 
-    f32x16 O[2] = {zero_f32x16(), zero_f32x16()};
-    float m = -INFINITY, l = 0.f;
+    O[0] = O[1] = zero_f32x16();
+    m = -INFINITY;
+    l = 0.f;
     gload(t0);
     lstore(0);
     __syncthreads();
@@ -1366,7 +1348,11 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32(const float* __restrict__ 
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int ks = 0; ks < 32; ++ks)
-                S[kb] = mfma_f32(sK[buf][(kb * 32 + n) * kKRow32 + 2 * ks + hh], Qf[ks], S[kb]);
+            {
+                S[kb] = mfma_f32(sK[buf * kBK * kKRow32 + (kb * 32 + n) * kKRow32 + 2 * ks + hh],
+                                 Qf[ks], S[kb]);
+                if (kLean && ks % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+            }
         if ((int64_t)(t + 1) * kBK > N) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
@@ -1406,7 +1392,8 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32(const float* __restrict__ 
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int key = kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                    Ot[db] = mfma_f32(sV[buf][key * kD + db * 32 + n], S[kb][r], Ot[db]);
+                    Ot[db] = mfma_f32(sV[buf * kBK * kD + key * kD + db * 32 + n], S[kb][r], Ot[db]);
+                    if (kLean && r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
         for (int db = 0; db < 2; ++db)
@@ -1415,6 +1402,37 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32(const float* __restrict__ 
         if (t + 1 < t1) lstore(buf ^ 1);
         __syncthreads();
     }
+}
+
+__global__ __launch_bounds__(256, 2) void k_flash_f32(const float* __restrict__ Q,
+                                                      const float* __restrict__ K,
+                                                      const float* __restrict__ V,
+                                                      const int32_t* __restrict__ buckets,
+                                                      int64_t N, int H, int nqt, int nkt, float c,
+                                                      int splits, float* __restrict__ part,
+                                                      void* __restrict__ Y, int ydt) {
+    const int nfull = full_count(buckets, H);
+    const int active = nfull * nqt;
+    if ((int)blockIdx.x >= active * splits) return;
+    const int Lx = xcd_remap(blockIdx.x, active * splits);
+    const int L = Lx / splits, half = Lx - L * splits;
+    const int slot = L / nqt, qt = L - slot * nqt;
+    // key tiles [t0, t1) of the item (all of them unless split)
+    const int t0 = (int)((int64_t)half * nkt / splits);
+    const int t1 = (int)((int64_t)(half + 1) * nkt / splits);
+    const int h = full_head(buckets, H, slot);
+    if (h < 0) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int n = lane & 31, hh = lane >> 5;
+
+    __shared__ __attribute__((aligned(16))) float smem[kLds32];
+
+    const int64_t qi = (int64_t)qt * kBQ32 + wave * 32 + n;
+    const bool qok = qi < N;
+    f32x16 O[2];
+    float m, l;
+    f32_tiles<false>(Q + ((qok ? qi : 0) * H + h) * kD, qok, K, V, N, H, h, t0, t1, c,
+              smem + 2 * kBK * kD, smem, O, m, l);
 
     const float lt = l + __shfl_xor(l, 32);
     if (splits > 1) {
@@ -1516,7 +1534,11 @@ __global__ __launch_bounds__(256) void k_flash_f32_combine(const int32_t* __rest
 // one by one (of the output norm, 2,748 tokens: 1.3e-7 against 1.9e-7; sharp
 // heads 2.1e-7 against 3.5e-7, Q x 3 4.2e-7 against 9.4e-7).
 // K is scaled per head, V per head and feature (undone at the end, so that
-// every feature keeps its own precision), Q per query.  Left to K6 are:
+// every feature keeps its own precision), Q per query.  The segments of these run K6's
+// loop instead, on the same split of the work (2,748 tokens, 8 such heads: FULL stage
+// 175 us; 229 us with a K6 launch of their own after this one, a workgroup per item; 201 us
+// with K6 alone in two halves.  1,374 tokens 76, 128 and 63 us; 5,496 tokens 539, 761
+// and 724 us):
 //   - heads and items with a value that is not finite or whose largest magnitude lies
 //     outside [2^-60, 2^60] (zero aside);
 //   - heads with a row of V all of whose features lie below 2^-20 of their largest: small
@@ -1686,11 +1708,12 @@ __global__ __launch_bounds__(256) void k_pack_f32(const float* __restrict__ K,
 // steps.  One workgroup = 4 waves x 32 queries; two workgroups per CU, so that one
 // wave's softmax runs beside another's MFMAs.
 __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__ Q,
+                                                       const float* __restrict__ K,
+                                                       const float* __restrict__ V,
                                                        const int32_t* __restrict__ buckets,
                                                        int64_t N, int H, int nqt, int nkt, float c,
                                                        const float* __restrict__ scales,
                                                        const char* __restrict__ tiles,
-                                                       int32_t* __restrict__ left,
                                                        float* __restrict__ part, int G,
                                                        void* __restrict__ Y, int ydt) {
     const int nfull = full_count(buckets, H);
@@ -1700,7 +1723,8 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
     const int full = active / G * G, R = active - full;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 31, hh = lane >> 5;
-    __shared__ __attribute__((aligned(1024))) char smem[2 * kTile32];
+    __shared__ __attribute__((aligned(1024))) char smem[kLds32 * 4];
+    static_assert(kLds32 * 4 >= 2 * kTile32, "both loops' buffers");
     typedef __attribute__((address_space(3))) char lds_char;
     typedef __attribute__((address_space(3))) const f16x8 lds_frag;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
@@ -1712,13 +1736,14 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
         const int64_t qi = (int64_t)qt * kBQ32 + wave * 32 + n;
         const bool qok = qi < N;
         const float* sc = scales + slot * kScale32;
+        const float* qrow = Q + ((qok ? qi : 0) * H + h) * kD;
         f32x16 O[2] = {zero_f32x16(), zero_f32x16()};
         float m = -INFINITY, l = 0.f;
 
         // Q: features 16 ks + 8 hh .. + 7 of the lane's query, and its scale.
         f32x4 q[8];
         {
-            const float* qp = Q + ((qok ? qi : 0) * H + h) * kD + 8 * hh;
+            const float* qp = qrow + 8 * hh;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 q[i] = *reinterpret_cast<const f32x4*>(qp + 16 * (i >> 1) + 4 * (i & 1));
@@ -1735,147 +1760,150 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
         const bool exact = __syncthreads_or(!f32_in_range(mq) || __float_as_uint(sc[kD + 1]) ||
                                             !(__uint_as_float(mq) * sc[kD + 2] * c <
                                               kMaxProduct32)) != 0;
-        if (t0 == 0 && threadIdx.x == 0) left[L] = exact;
-        if (exact) return;   // uniform over the workgroup
-        const int eq = f32_exponent(mq);
-        const float dq = pow2(-eq), cs = c * sc[kD] * pow2(eq);
-        f16x8 qh[4], ql[4];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                f16 a, b;
-                split16(q[2 * ks + (j >> 2)][j & 3] * dq, a, b);
-                qh[ks][j] = a;
-                ql[ks][j] = b;
-            }
-        const char* tb = tiles + (int64_t)slot * nkt * kTile32;
-        auto copy = [&](int t, int buf) {   // 8 KB per wave, as it lies
-            const char* src = tb + (int64_t)t * kTile32 + wave * 8192;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                copy_to_lds(lds0 + buf * kTile32 + wave * 8192 + i * 1024, src + i * 1024,
-                            (uint32_t)lane * 16u);
-        };
-        const uint32_t f0 = lds0 + (uint32_t)n * 128u + (uint32_t)((hh ^ ((n >> 1) & 7)) << 4);
-        // chunk 2 k + hh of row 32 blk + n of matrix `mat` (K hi, K lo, V hi, V lo)
-        auto frag = [&](int buf, int mat, int blk, int k) {
-            return *(lds_frag*)(uintptr_t)((f0 ^ (uint32_t)(k << 5)) + buf * kTile32 +
-                                           8192u * mat + 4096u * blk);
-        };
-        copy(t0, 0);
-        for (int t = t0; t < t1; ++t) {
-            const int buf = (t - t0) & 1;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();   // tile t is there; the other buffer's reads are done
-            if (t + 1 < t1) copy(t + 1, buf ^ 1);
-            f32x16 S[2] = {zero_f32x16(), zero_f32x16()};
+        if (exact) {   // uniform over the workgroup, and the same for every part of an item
+            float* sf = reinterpret_cast<float*>(smem);
+            f32_tiles<true>(qrow, qok, K, V, N, H, h, t0, t1, c, sf + 2 * kBK * kD, sf, O, m, l);
+        } else {
+            const int eq = f32_exponent(mq);
+            const float dq = pow2(-eq), cs = c * sc[kD] * pow2(eq);
+            f16x8 qh[4], ql[4];
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-                    S[kb] = mfma_f16(frag(buf, 1, kb, ks), qh[ks], S[kb]);
-            f16x8 kh[4][2];
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    kh[ks][kb] = frag(buf, 0, kb, ks);
-                    S[kb] = mfma_f16(kh[ks][kb], ql[ks], S[kb]);
+                for (int j = 0; j < 8; ++j) {
+                    f16 a, b;
+                    split16(q[2 * ks + (j >> 2)][j & 3] * dq, a, b);
+                    qh[ks][j] = a;
+                    ql[ks][j] = b;
                 }
+            const char* tb = tiles + (int64_t)slot * nkt * kTile32;
+            auto copy = [&](int t, int buf) {   // 8 KB per wave, as it lies
+                const char* src = tb + (int64_t)t * kTile32 + wave * 8192;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int i = 0; i < 8; ++i)
+                    copy_to_lds(lds0 + buf * kTile32 + wave * 8192 + i * 1024, src + i * 1024,
+                                (uint32_t)lane * 16u);
+            };
+            const uint32_t f0 = lds0 + (uint32_t)n * 128u + (uint32_t)((hh ^ ((n >> 1) & 7)) << 4);
+            // chunk 2 k + hh of row 32 blk + n of matrix `mat` (K hi, K lo, V hi, V lo)
+            auto frag = [&](int buf, int mat, int blk, int k) {
+                return *(lds_frag*)(uintptr_t)((f0 ^ (uint32_t)(k << 5)) + buf * kTile32 +
+                                               8192u * mat + 4096u * blk);
+            };
+            copy(t0, 0);
+            for (int t = t0; t < t1; ++t) {
+                const int buf = (t - t0) & 1;
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();   // tile t is there; the other buffer's reads are done
+                if (t + 1 < t1) copy(t + 1, buf ^ 1);
+                f32x16 S[2] = {zero_f32x16(), zero_f32x16()};
 #pragma unroll
-                for (int i = 0; i < 16; ++i) S[kb][i] *= kLow32;
+                for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
+                    for (int kb = 0; kb < 2; ++kb)
+                        S[kb] = mfma_f16(frag(buf, 1, kb, ks), qh[ks], S[kb]);
+                f16x8 kh[4][2];
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb) S[kb] = mfma_f16(kh[ks][kb], qh[ks], S[kb]);
-            if ((int64_t)(t + 1) * kBK > N) {
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb) {
+                        kh[ks][kb] = frag(buf, 0, kb, ks);
+                        S[kb] = mfma_f16(kh[ks][kb], ql[ks], S[kb]);
+                    }
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int64_t key =
-                            (int64_t)t * kBK + kb * 32 + 16 * (i >> 3) + 8 * hh + (i & 7);
-                        if (key >= N) S[kb][i] = -INFINITY;
+                    for (int i = 0; i < 16; ++i) S[kb][i] *= kLow32;
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb) S[kb] = mfma_f16(kh[ks][kb], qh[ks], S[kb]);
+                if ((int64_t)(t + 1) * kBK > N) {
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            const int64_t key =
+                                (int64_t)t * kBK + kb * 32 + 16 * (i >> 3) + 8 * hh + (i & 7);
+                            if (key >= N) S[kb][i] = -INFINITY;
+                        }
+                }
+                float mx = -INFINITY;
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[kb][i]);
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float mn = fmaxf(m, mx * cs);
+                const float al = exp2f_fast(m - mn);
+                m = mn;
+                // The weights are split times 2^14, a factor that O keeps until the end.
+                // (Added to the exponent it would cost the precision of an argument
+                // near 14.)
+                float ls = 0.f;
+                f16x8 ph[2][2], pl[2][2];
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        u32x4 h4, l4;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const f32x2 e = {exp2f_fast(fmaf(S[kb][8 * b + 2 * j], cs, -mn)),
+                                             exp2f_fast(fmaf(S[kb][8 * b + 2 * j + 1], cs, -mn))};
+                            ls += e[0];
+                            ls += e[1];
+                            const f32x2 es = {e[0] * 16384.f, e[1] * 16384.f};
+                            const f16x2 eh = __builtin_convertvector(es, f16x2);
+                            const f32x2 er = {(es[0] - (float)eh[0]) * (1.f / kLow32),
+                                              (es[1] - (float)eh[1]) * (1.f / kLow32)};
+                            h4[j] = __builtin_bit_cast(uint32_t, eh);
+                            l4[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(er, f16x2));
+                        }
+                        ph[kb][b] = __builtin_bit_cast(f16x8, h4);
+                        pl[kb][b] = __builtin_bit_cast(f16x8, l4);
                     }
+                l = fmaf(l, al, ls);
+                // Two-level sums: the tile's product is summed from zero,
+                // then added to the running O, so that rounding grows with the
+                // tile count rather than the key count.
+                f32x16 Ot[2] = {zero_f32x16(), zero_f32x16()};
+#pragma unroll
+                for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+                    for (int db = 0; db < 2; ++db)
+                        Ot[db] = mfma_f16(frag(buf, 3, db, kc), ph[kc >> 1][kc & 1], Ot[db]);
+                f16x8 vh[4][2];
+#pragma unroll
+                for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+                    for (int db = 0; db < 2; ++db) {
+                        vh[kc][db] = frag(buf, 2, db, kc);
+                        Ot[db] = mfma_f16(vh[kc][db], pl[kc >> 1][kc & 1], Ot[db]);
+                    }
+#pragma unroll
+                for (int db = 0; db < 2; ++db)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) Ot[db][r] *= kLow32;
+#pragma unroll
+                for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+                    for (int db = 0; db < 2; ++db)
+                        Ot[db] = mfma_f16(vh[kc][db], ph[kc >> 1][kc & 1], Ot[db]);
+#pragma unroll
+                for (int db = 0; db < 2; ++db)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) O[db][r] = fmaf(O[db][r], al, Ot[db][r]);
             }
-            float mx = -INFINITY;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[kb][i]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float mn = fmaxf(m, mx * cs);
-            const float al = exp2f_fast(m - mn);
-            m = mn;
-            // The weights are split times 2^14, a factor that O keeps until the end.
-            // (Added to the exponent it would cost the precision of an argument
-            // near 14.)
-            float ls = 0.f;
-            f16x8 ph[2][2], pl[2][2];
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    u32x4 h4, l4;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const f32x2 e = {exp2f_fast(fmaf(S[kb][8 * b + 2 * j], cs, -mn)),
-                                         exp2f_fast(fmaf(S[kb][8 * b + 2 * j + 1], cs, -mn))};
-                        ls += e[0];
-                        ls += e[1];
-                        const f32x2 es = {e[0] * 16384.f, e[1] * 16384.f};
-                        const f16x2 eh = __builtin_convertvector(es, f16x2);
-                        const f32x2 er = {(es[0] - (float)eh[0]) * (1.f / kLow32),
-                                          (es[1] - (float)eh[1]) * (1.f / kLow32)};
-                        h4[j] = __builtin_bit_cast(uint32_t, eh);
-                        l4[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(er, f16x2));
-                    }
-                    ph[kb][b] = __builtin_bit_cast(f16x8, h4);
-                    pl[kb][b] = __builtin_bit_cast(f16x8, l4);
-                }
-            l = fmaf(l, al, ls);
-            // Two-level sums: the tile's product is summed from zero,
-            // then added to the running O, so that rounding grows with the
-            // tile count rather than the key count.
-            f32x16 Ot[2] = {zero_f32x16(), zero_f32x16()};
-#pragma unroll
-            for (int kc = 0; kc < 4; ++kc)
-#pragma unroll
-                for (int db = 0; db < 2; ++db)
-                    Ot[db] = mfma_f16(frag(buf, 3, db, kc), ph[kc >> 1][kc & 1], Ot[db]);
-            f16x8 vh[4][2];
-#pragma unroll
-            for (int kc = 0; kc < 4; ++kc)
-#pragma unroll
-                for (int db = 0; db < 2; ++db) {
-                    vh[kc][db] = frag(buf, 2, db, kc);
-                    Ot[db] = mfma_f16(vh[kc][db], pl[kc >> 1][kc & 1], Ot[db]);
-                }
 #pragma unroll
             for (int db = 0; db < 2; ++db)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) Ot[db][r] *= kLow32;
+                for (int g = 0; g < 4; ++g) {
+                    const f32x4 up = *reinterpret_cast<const f32x4*>(sc + db * 32 + 8 * g + 4 * hh);
 #pragma unroll
-            for (int kc = 0; kc < 4; ++kc)
-#pragma unroll
-                for (int db = 0; db < 2; ++db)
-                    Ot[db] = mfma_f16(vh[kc][db], ph[kc >> 1][kc & 1], Ot[db]);
-#pragma unroll
-            for (int db = 0; db < 2; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) O[db][r] = fmaf(O[db][r], al, Ot[db][r]);
+                    for (int i = 0; i < 4; ++i) O[db][4 * g + i] *= up[i] * 0x1p-14f;
+                }
         }
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 up = *reinterpret_cast<const f32x4*>(sc + db * 32 + 8 * g + 4 * hh);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) O[db][4 * g + i] *= up[i] * 0x1p-14f;
-            }
 
         const float lt = l + __shfl_xor(l, 32);
         if (t0 != 0 || t1 != nkt) {
@@ -1938,7 +1966,6 @@ __global__ __launch_bounds__(256, 2) void k_flash_f32s(const float* __restrict__
 // its values each.
 __global__ __launch_bounds__(256) void k_flash_f32s_combine(const int32_t* __restrict__ buckets,
                                                             int64_t N, int H, int nqt, int nkt,
-                                                            const int32_t* __restrict__ left,
                                                             const float* __restrict__ part, int G,
                                                             void* __restrict__ Y, int ydt) {
     const int nfull = full_count(buckets, H);
@@ -1949,7 +1976,7 @@ __global__ __launch_bounds__(256) void k_flash_f32s_combine(const int32_t* __res
     const int Gt = tail_groups(T, G, kMinTiles32);
     const int wf = tail_owner((int64_t)i * nkt, T, Gt);
     const int wl = tail_owner((int64_t)(i + 1) * nkt - 1, T, Gt);
-    if (wf == wl || left[full + i]) return;
+    if (wf == wl) return;
     const int L = full + i, slot = L / nqt, qt = L - slot * nqt;
     const int h = full_head(buckets, H, slot);
     if (h < 0) return;
@@ -2013,10 +2040,13 @@ size_t flash_part_bytes(int64_t N, int H) {
 
 // fp32 layers.  Up to kSplit32 tokens: K6, with two key halves per work item while
 // the items alone would leave the chip short of waves (at most 2 workgroups
-// per CU of them).  Longer ones: K6e, whose packing and combine launches cost
-// more than it gains on short ones (FULL stage, 8 heads: 768 tokens 38.7 us with K6
-// and 42.0 with K6e; 1,024 tokens 48.9 and 44.8; 1,374 tokens 65 and 50; 2,748
-// tokens 205 and 86; 4,096 tokens 290 and 139).
+// per CU of them).  Longer ones: K6e, whose packing and combine launches cost more than
+// it gains on short ones.  FULL stage, us, K6 and K6e with 1, 2, 4, 8 and 16 of 16 heads:
+//   640 tokens   32.3 32.0   32.4 32.9   32.8 39.9   33.7 42.3   35.7 44.4
+//   896          41.1 33.8   41.4 40.6   41.9 42.5   43.4 45.3   46.1 46.4
+//   1,024        45.7 32.0   46.0 39.8   46.5 41.7   48.3 45.1   51.9 45.0
+// 1,374 tokens, 8 heads 63 and 50; 2,748 201 and 90; 5,496 724 and 242.  With no FULL head
+// the launches alone are 11 us (K6, two) and 19 us (K6e, four).
 constexpr int64_t kSplit32 = 1024;
 static bool f32_split(int64_t N) { return N > kSplit32; }
 static int flash_f32_halves(int64_t N, int H) {
@@ -2024,7 +2054,7 @@ static int flash_f32_halves(int64_t N, int H) {
     return nqt * H <= 2 * kStreamWG && nkt >= 2 ? 2 : 1;
 }
 // Bytes of the partial results (K6's halves, or two part slots per workgroup
-// that K6e's tail can use), of K6e's flags, maxima and scales, and of its tiles.
+// that K6e's tail can use), of K6e's maxima and scales, and of its tiles.
 size_t flash_f32_part_bytes(int64_t N, int H) {
     const int64_t nqt = (N + kBQ32 - 1) / kBQ32, nkt = (N + kBK - 1) / kBK;
     if (!f32_split(N))
@@ -2036,7 +2066,7 @@ size_t flash_f32_part_bytes(int64_t N, int H) {
 static int flash_f32_groups(int64_t N) { return (int)((N + f32_group_rows(N) - 1) / f32_group_rows(N)); }
 size_t flash_f32_max_bytes(int64_t N, int H) {
     if (!f32_split(N)) return 0;
-    return (size_t)H * (flash_f32_groups(N) * kMax32 + kScale32 + (N + kBQ32 - 1) / kBQ32) * 4;
+    return (size_t)H * (flash_f32_groups(N) * kMax32 + kScale32) * 4;
 }
 size_t flash_f32_tile_bytes(int64_t N, int H) {
     if (!f32_split(N)) return 0;
@@ -2082,8 +2112,7 @@ void launch_flash(const AttnArgs& a, hipStream_t st) {
         const int splits = flash_f32_halves(a.N, a.H);
         hipLaunchKernelGGL(k_flash_f32, dim3(nqt * a.H * splits), dim3(256), 0, st,
                            (const float*)a.Q, (const float*)a.K, (const float*)a.V, a.buckets,
-                           a.N, a.H, nqt, nkt, c, splits, (const int32_t*)nullptr, a.part, a.Y,
-                           a.ydt);
+                           a.N, a.H, nqt, nkt, c, splits, a.part, a.Y, a.ydt);
         if (splits > 1)
             hipLaunchKernelGGL(k_flash_f32_combine, dim3(nqt * a.H * 2), dim3(256), 0, st,
                                a.buckets, a.N, a.H, nqt, (const float*)a.part, a.Y, a.ydt);
@@ -2091,21 +2120,17 @@ void launch_flash(const AttnArgs& a, hipStream_t st) {
         const int ng = flash_f32_groups(a.N);
         uint32_t* mx = (uint32_t*)a.fmax;
         float* scales = a.fmax + (size_t)a.H * ng * kMax32;
-        int32_t* left = (int32_t*)(scales + (size_t)a.H * kScale32);
         hipLaunchKernelGGL(k_absmax_f32, dim3(ng, a.H), dim3(256), 0, st, (const float*)a.K,
                            (const float*)a.V, a.buckets, a.N, a.H, mx, scales);
         hipLaunchKernelGGL(k_pack_f32, dim3(nkt, a.H), dim3(256), 0, st, (const float*)a.K,
                            (const float*)a.V, a.buckets, a.N, a.H, nkt, (const uint32_t*)mx, ng,
                            scales, (char*)a.ftiles);
         hipLaunchKernelGGL(k_flash_f32s, dim3(kWG32), dim3(256), 0, st, (const float*)a.Q,
-                           a.buckets, a.N, a.H, nqt, nkt, c, (const float*)scales,
-                           (const char*)a.ftiles, left, a.part, kWG32, a.Y, a.ydt);
-        hipLaunchKernelGGL(k_flash_f32s_combine, dim3(2 * (nqt * a.H < kWG32 ? nqt * a.H : kWG32)),
-                           dim3(256), 0, st, a.buckets, a.N, a.H, nqt, nkt, (const int32_t*)left,
-                           (const float*)a.part, kWG32, a.Y, a.ydt);
-        hipLaunchKernelGGL(k_flash_f32, dim3(nqt * a.H), dim3(256), 0, st, (const float*)a.Q,
                            (const float*)a.K, (const float*)a.V, a.buckets, a.N, a.H, nqt, nkt, c,
-                           1, (const int32_t*)left, (float*)nullptr, a.Y, a.ydt);
+                           (const float*)scales, (const char*)a.ftiles, a.part, kWG32, a.Y, a.ydt);
+        hipLaunchKernelGGL(k_flash_f32s_combine, dim3(2 * (nqt * a.H < kWG32 ? nqt * a.H : kWG32)),
+                           dim3(256), 0, st, a.buckets, a.N, a.H, nqt, nkt,
+                           (const float*)a.part, kWG32, a.Y, a.ydt);
     }
 }
 

@@ -287,6 +287,23 @@ def test_fp32_split_unequal_sizes(case, b):
         assert ratio <= 1, (case, b, int(h), ratio)
 
 
+def test_fp32_mixed_items():
+    """fp32 FULL heads of 4,200 tokens (33 items of 128 queries a head, 528 in all: one whole
+    round of the 512 workgroups and 16 split over them), every other head past the split's
+    range: workgroups go from one loop to the other.  The first, a middle and the last item."""
+    log("fp32 mixed items")
+    P = 4200
+    x = synth.make_layer(1, P, dtype="f32", key=(65, P), sharp=True,
+                         modes=np.full(16, 2, np.uint8))
+    x.K[:, 1::2] *= 2.0 ** 70
+    x.Q[:, 1::2] *= 2.0 ** -70
+    rows = np.concatenate([np.arange(128), 2048 + np.arange(128), np.arange(4096, P)])
+    layer = run_gpu(x, y_dtype=torch.float32)
+    Y = layer.Y[torch.from_numpy(rows).to(layer.Y.device)].double().cpu().numpy()
+    ref = np.stack([oracle.full_rows(x.Q, x.K, x.V, h, rows=rows) for h in range(16)], 1)
+    check_y(Y, ref, "f32", False, label="mixed items")
+
+
 def test_single_token():
     """N = 1: FULL returns v, MEAN returns v, s = 1 (every head FULL under Eq.4)."""
     log("N=1")
