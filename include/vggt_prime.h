@@ -136,10 +136,12 @@ typedef struct {
 } vp_surrogate_weights;
 
 /* Bytes of device workspace that vp_router_score, vp_routed_global_attention
- * and its stages need for `shape` (0 if the shape is invalid).  The workspace
- * holds router partial sums, the gathered keys and values of FULL heads (bf16
- * layers, and fp32 layers past 1,024 tokens), the
- * FULL kernel's partial results and the linear-attention sums; it must be 256-byte
+ * and its stages need for `shape` (0 if the shape is invalid).  It never falls
+ * when S * P grows, so a workspace sized for the largest of several layers
+ * (same H and dtype) serves them all.  The workspace holds router partial
+ * sums, the gathered keys and values of FULL heads (bf16 layers 256 bytes per
+ * token and head, fp32 layers past 1,024 tokens 512), the FULL kernel's
+ * partial results and the linear-attention sums; it must be 256-byte
  * aligned and may be reused across calls on one stream (calls on different
  * streams need separate workspaces). */
 size_t vp_workspace_bytes(const vp_shape *shape);

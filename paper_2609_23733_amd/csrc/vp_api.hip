@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/vggt_prime.h"
@@ -60,11 +61,18 @@ bool make_layout(const vp_shape* s, Layout* L) {
     int64_t c3 = cdiv(cdiv(N, 128), 64) * 64;
     L->chunk3 = c3 < 256 ? 256 : c3;
     L->n3 = cdiv(N, L->chunk3);
+    // The partial sums have room for the most chunks of any layer of up to N tokens (the
+    // counts themselves fall where a chunk grows, for instance n2 from 256 at 4,096 tokens
+    // to 171 at 4,097), so that a workspace for N tokens serves every smaller layer.
+    const int64_t most1 = std::min<int64_t>(cdiv(N, 128), 64);
+    const int64_t most2 = std::max(std::min<int64_t>(cdiv(N, 16), 256),
+                                   std::min<int64_t>(cdiv(N, 64), 512));
+    const int64_t most3 = std::min<int64_t>(cdiv(N, 256), 128);
     size_t off = kAlign;   // first 256 bytes reserved
     L->off_part1 = off;
-    off = align_up(off + (size_t)L->n1 * s->H * (2 + VP_HEAD_DIM) * sizeof(float));
+    off = align_up(off + (size_t)most1 * s->H * (2 + VP_HEAD_DIM) * sizeof(float));
     L->off_part2 = off;
-    off = align_up(off + (size_t)L->n2 * s->H * (2 + 2 * VP_HEAD_DIM) * sizeof(float));
+    off = align_up(off + (size_t)most2 * s->H * (2 + 2 * VP_HEAD_DIM) * sizeof(float));
     L->off_vt = off;
     if (s->dtype == VP_BF16) off = align_up(off + (size_t)s->H * L->nkt * 64 * 64 * 2);
     L->off_kh = off;
@@ -87,7 +95,7 @@ bool make_layout(const vp_shape* s, Layout* L) {
     L->off_ftiles = off;
     if (s->dtype == VP_F32) off = align_up(off + vp::flash_f32_tile_bytes(N, (int)s->H));
     L->off_lpart = off;
-    off = align_up(off + (size_t)L->n3 * s->H * vp::kLinSums * sizeof(float));
+    off = align_up(off + (size_t)most3 * s->H * vp::kLinSums * sizeof(float));
     L->off_lsum = off;
     off = align_up(off + (size_t)s->H * vp::kLinSums * sizeof(float));
     L->total = off;

@@ -57,6 +57,20 @@ def test_workspace_bytes(lib):
     assert f(shape(dt=vp.VP_BF16)) > f(shape(dt=vp.VP_F32))
 
 
+def test_workspace_grows_with_tokens(lib):
+    """A workspace sized for the largest of several layers serves the smaller ones, too."""
+    ns = list(range(1, 4200)) + list(range(4200, 40000, 7)) + \
+        [m * 512 + r for m in range(8, 400) for r in (0, 1)] + [137400, 687000, 1 << 28]
+    for f in (lib.vp_workspace_bytes, lib.vp_teacher_workspace_bytes, lib.vp_tome_workspace_bytes):
+        for dt in (vp.VP_BF16, vp.VP_F32):
+            for H in (1, 3, 16):
+                most, at = 0, 0
+                for n in sorted(ns):
+                    b = f(ctypes.byref(shape(S=1, P=n, H=H, dt=dt)))
+                    assert b >= most, (f.__name__, dt, H, at, most, n, b)
+                    most, at = b, n
+
+
 def rw(L=64, W=FAKE, scale=0.0, pool=vp.POOL_GATED):
     return vp.vp_router_weights(W, FAKE, FAKE, L, scale, pool)
 
