@@ -2118,8 +2118,9 @@ void launch_flash(const AttnArgs& a, hipStream_t st) {
                                a.buckets, a.N, a.H, nqt, (const float*)a.part, a.Y, a.ydt);
     } else {
         const int ng = flash_f32_groups(a.N);
-        uint32_t* mx = (uint32_t*)a.fmax;
-        float* scales = a.fmax + (size_t)a.H * ng * kMax32;
+        float* scales = a.fmax;   // (first: read 16 bytes at a time)
+        uint32_t* mx = (uint32_t*)(scales + (size_t)a.H * kScale32);
+        static_assert(kScale32 % 4 == 0, "16-byte alignment of every slot's scales");
         hipLaunchKernelGGL(k_absmax_f32, dim3(ng, a.H), dim3(256), 0, st, (const float*)a.K,
                            (const float*)a.V, a.buckets, a.N, a.H, mx, scales);
         hipLaunchKernelGGL(k_pack_f32, dim3(nkt, a.H), dim3(256), 0, st, (const float*)a.K,

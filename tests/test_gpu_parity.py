@@ -287,6 +287,18 @@ def test_fp32_split_unequal_sizes(case, b):
         assert ratio <= 1, (case, b, int(h), ratio)
 
 
+@pytest.mark.parametrize("H", [1, 2, 3, 5])
+def test_fp32_split_few_heads(H):
+    """fp32 FULL heads past 1,024 tokens with fewer heads than 16 (other strides and
+    workspace offsets), every row."""
+    log("fp32 split H=%d" % H)
+    x = synth.make_layer(1, 1374, dtype="f32", key=(64, H), H=H, sharp=True,
+                         modes=np.full(H, 2, np.uint8))
+    layer = run_gpu(x, y_dtype=torch.float32)
+    ref = oracle_layer(x)
+    check_y(layer.Y.double().cpu().numpy(), ref["Y"], "f32", False, label="H=%d" % H)
+
+
 def test_fp32_mixed_items():
     """fp32 FULL heads of 4,200 tokens (33 items of 128 queries a head, 528 in all: one whole
     round of the 512 workgroups and 16 split over them), every other head past the split's
