@@ -190,9 +190,11 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4
         }
     };
     {
-        const f32x2 bv = *reinterpret_cast<const f32x2*>(g.bias + fw + 2 * lane);
+        // (the caller's vectors are aligned to 4 bytes)
+        typedef float f32x2_at4 __attribute__((__vector_size__(8), aligned(4)));
+        const f32x2 bv = *reinterpret_cast<const f32x2_at4*>(g.bias + fw + 2 * lane);
         f32x2 lv = {0.f, 0.f};
-        if constexpr (kScale) lv = *reinterpret_cast<const f32x2*>(g.ls + fw + 2 * lane);
+        if constexpr (kScale) lv = *reinterpret_cast<const f32x2_at4*>(g.ls + fw + 2 * lane);
         if constexpr (EPI == EPI_RESID2) load_res(0, 0);
         *(lds_f32x2*)(uintptr_t)(vecs + 8u * lane) = bv;
         if constexpr (kScale) *(lds_f32x2*)(uintptr_t)(vecs + 512u + 8u * lane) = lv;

@@ -145,6 +145,30 @@ def test_block_more_tiles_than_workgroups(N):
     check_update(out[rt.cuda()], X[rt], ref, "N=%d out" % N)
 
 
+def test_block_vectors_at_4_bytes():
+    """Biases, LayerNorm and LayerScale vectors at addresses that are multiples of 4 bytes
+    only (the API asks for no more): the same bits as with aligned ones."""
+    from paper_2609_23733_amd import vp
+    log("block vectors at 4 bytes")
+    N = 300
+    wd = {k: v.cuda() for k, v in synth.make_block_weights((27, 0)).items()}
+    odd = {}
+    for k, v in wd.items():
+        odd[k] = v
+        if v.dtype == torch.float32:
+            odd[k] = torch.empty(v.numel() + 1, device="cuda")[1:].copy_(v)
+            assert odd[k].data_ptr() % 8 == 4
+    X = synth.make_block_input(1, N, key=(27, N)).cuda()
+    pos = torch.from_numpy(synth.token_positions(1, N)).cuda()
+    Y = synth.stored(synth.normal((N, D), synth.derive_seed(27, N, 99), 0.1), "bf16").cuda()
+    ws = torch.empty(vp.block_workspace_bytes(1, N), dtype=torch.uint8, device="cuda")
+    out = [list(vp.block_qkv(X, pos, w, 1, N, ws)) + [vp.block_out(X, Y, w, 1, N, ws)]
+           for w in (wd, odd)]
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
 def test_block_element_offsets_past_2_32():
     """N = 3053 x 1374 = 4,194,822 tokens: the FFN's 4096-wide hidden rows
     pass 2^32 elements from token 2^20 on, the 1024-wide rows of X, Q, K, V
