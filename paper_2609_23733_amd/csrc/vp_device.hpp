@@ -151,7 +151,7 @@ __device__ __forceinline__ void copy_to_lds(uint32_t lds, const char* base, uint
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(lds), "v"(voff), "s"(base)
-                 : "memory");
+                 : "memory", "m0");
 }
 
 // Remap a linear work index so that consecutive work items land on the same
