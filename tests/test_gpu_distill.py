@@ -81,6 +81,32 @@ def test_colmax_split(P, H):
         check_colmax(smax[h:h + 1].cpu().numpy(), ref.max(keepdims=True), "smax")
 
 
+@pytest.mark.parametrize("where", ["query nan", "query inf", "key nan", "key inf"])
+def test_colmax_not_finite(where):
+    """NaN and infinite values of Q or K: a query whose softmax is NaN (a NaN logit, or +inf)
+    never wins a column's maximum, the others' maxima are what they are without it, and a key
+    that no query can weigh has 0.  Keys and queries in two blocks and two tiles."""
+    from paper_2609_23733_amd import vp
+    log("column maxima %s" % where)
+    P, H = 1100, 2
+    x = synth.make_layer(1, P, dtype="bf16", key=(36, 0), H=H, n_full=1, sharp=True)
+    for at in (70, 1050):
+        if where.startswith("query"):
+            x.Q[at, 1, 9] = float(where[6:])
+        else:
+            x.K[at, 1, 9] = float(where[4:])
+    colmax, smax, _ = vp.teacher_targets(x.Q.cuda(), x.K.cuda(), x.V.cuda(), 1, P)
+    torch.cuda.synchronize()
+    for h in range(H):
+        t = x.Q[:, h].double().numpy() @ x.K[:, h].double().numpy().T / 8
+        with np.errstate(invalid="ignore"):
+            p = np.exp(t - t.max(1, keepdims=True))
+            p /= p.sum(1, keepdims=True)
+        ref = np.nan_to_num(p, nan=0.0).max(0)
+        check_colmax(colmax[h].cpu().numpy(), ref, "%s h=%d" % (where, h))
+        check_colmax(smax[h:h + 1].cpu().numpy(), ref.max(keepdims=True), "smax")
+
+
 def test_teacher_targets_few_heads():
     """H = 3 heads (the teacher takes any head count up to 16)."""
     from paper_2609_23733_amd import vp

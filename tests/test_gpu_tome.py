@@ -172,9 +172,10 @@ def test_plan_edges(S, P, M, nspecial):
 @pytest.mark.parametrize("S,P,frac", [(2, 32, 0.4), (4, 1024, 0.6), (3, 1366, 0.3),
                                       (16, 65536, 0.5), (16, 65537, 0.55)])
 def test_plan_many_ties(S, P, frac):
-    """Keys of 40 directions and power-of-two lengths: most scores are shared by many
-    sources, so the cut falls inside a tie and the lower tokens win, exactly as a sort of
-    the GPU's own (score, token) has it; rows and members follow exactly.  64, 4,096 and
+    """Keys of 40 directions and power-of-two lengths: a source's own direction is its best,
+    shared by many destinations, of which the first in token order is taken; most scores are
+    shared by many sources, so the cut falls inside a tie and the lower tokens win, exactly
+    as a sort of the GPU's own (score, token) has it; rows and members follow exactly.  64, 4,096 and
     4,098 tokens: keys of 38, 44 and 45 bits (4 and 5 passes of 11); 2^20 tokens and 16
     more: 1,024 scan blocks (added up in place) and 1,025 (a scan of their sums)."""
     log("tome ties S=%d P=%d" % (S, P))
@@ -182,12 +183,18 @@ def test_plan_many_ties(S, P, frac):
     rng = np.random.default_rng(N)
     base = synth.normal((40, 1, 64), synth.derive_seed(50, S, P), 1.0).to(torch.bfloat16).float()
     scale = torch.from_numpy(2.0 ** rng.integers(-1, 3, N)).float()[:, None, None]
-    K = (base[torch.from_numpy(rng.integers(0, 40, N))] * scale).to(torch.bfloat16)
+    way = rng.integers(0, 40, N)
+    K = (base[torch.from_numpy(way)] * scale).to(torch.bfloat16)
     plan = run_plan(K, S, P, M)
     is_dst, _ = oracle.tome_split(S, P, M)
-    srcs = np.nonzero(~is_dst)[0]
+    srcs, dsts = np.nonzero(~is_dst)[0], np.nonzero(is_dst)[0]
     score = plan.score.cpu().numpy()[srcs]
     best = plan.best.cpu().numpy().astype(np.int64)[srcs]
+    first = np.full(40, -1)
+    first[way[dsts][::-1]] = dsts[::-1]   # a direction's first destination
+    same = first[way[srcs]] >= 0
+    assert same.mean() > (0.3 if N < 100 else 0.99)
+    np.testing.assert_array_equal(best[same], first[way[srcs]][same])
     order = np.lexsort((srcs, -score))
     assert len(srcs) == M or score[order[M - 1]] == score[order[M]]
     merged = np.zeros(len(srcs), bool)
