@@ -23,7 +23,11 @@ sys.path.insert(0, ROOT)
 
 METRIC = "routed global-attn layer latency (ms) + TFLOP/s & % bf16 MFMA peak vs S"
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
-PEAK_FP32_TFLOPS = 157.3       # MI355X fp32 vector
+PEAK_FP32_TFLOPS = 157.3       # MI355X fp32 matrix
+# fp32 FULL heads past 1,024 tokens: three fp16 MFMA products per fp32 product.
+PEAK_FP32_SPLIT_TFLOPS = round(PEAK_BF16_TFLOPS / 3, 1)
+# bf16 linear attention: three bf16 products for phi(k) v^T, six for phi(q) S.
+PEAK_LINATTN_TFLOPS = round(PEAK_BF16_TFLOPS / 4.5, 1)
 PEAK_HBM_GBS = 8000.0
 P_TOKENS = 1374
 HEADS, D, L = 16, 64, 64
@@ -35,7 +39,7 @@ HEADS, D, L = 16, 64, 64
 # = 524305 KiB for 1 GiB read (x2.0) and WRITE_SIZE = 1048576 KiB for 1 GiB
 # written (x1.0).  Valid only for the kernel source it was measured on.
 FLASH_TRAFFIC = {
-    "source_sha256": "db65ba87194a9f4d13c39db495d988406524db9b3f8fca46b07fb951c1525bb3",
+    "source_sha256": "4735039265ad4662138553391a48dce13f4fc99d02ec1cd9dddbb916acae4d56",
     "S": 100, "n_full": 4,
     "fetch_kib": 1544533, "write_kib": 122449,
     "copy_fetch_kib": 524305, "copy_write_kib": 1048576, "copy_bytes": 1 << 30,
@@ -147,7 +151,8 @@ def run_workload(S, n_full, steps, warmup, seed_key, dtype="bf16", sharp=False, 
     N = S * P_TOKENS
     fl = layer_flops(N, counts[2], counts[1], counts[0])
     ff = flops_full(N, counts[2])
-    peak = PEAK_BF16_TFLOPS if dtype == "bf16" else PEAK_FP32_TFLOPS
+    peak = (PEAK_BF16_TFLOPS if dtype == "bf16" else
+            PEAK_FP32_SPLIT_TFLOPS if N > 1024 else PEAK_FP32_TFLOPS)
     b_in = 2 if dtype == "bf16" else 4
     b_out = 2 if ydt == torch.bfloat16 else 4
     byt = stage_bytes(N, counts[2], counts[1], counts[0], b_in, b_out)
@@ -220,11 +225,11 @@ def run_variants(x, steps, warmup):
         if sv == 4 and counts[1]:
             fl = linattn_flops(x.N, counts[1])
             ach = fl / lin_ms / 1e9
-            rec["roofline"] = {"kernel": "k_linattn_partial + k_linattn_combine + "
-                                         "k_linattn_apply (+ MEAN broadcast)",
+            rec["roofline"] = {"kernel": "k_linattn_partial_bf16 + k_linattn_combine + "
+                                         "k_linattn_apply_bf16 (with the MEAN heads)",
                                "bound": "alu", "achieved": round(ach, 2),
-                               "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                               "frac": round(ach / PEAK_FP32_TFLOPS, 4),
+                               "peak": PEAK_LINATTN_TFLOPS, "unit": "TFLOP/s",
+                               "frac": round(ach / PEAK_LINATTN_TFLOPS, 4),
                                "algorithmic_flop_per_launch": fl}
         out.append(rec)
         del layer

@@ -1531,8 +1531,8 @@ __global__ __launch_bounds__(256) void k_flash_f32_combine(const int32_t* __rest
 // values against 512 for the 32x32x2 fp32 MFMA; all sums stay fp32.  The bounds are
 // wider than fp32's rounding of a value (2^-24), but on random values the error
 // against float64 is smaller than with fp32 MFMAs, whose 64 products per sum are added
-// one by one (of the output norm, 2,748 tokens: 1.3e-7 against 1.9e-7; sharp
-// heads 2.1e-7 against 3.5e-7, Q x 3 4.2e-7 against 9.4e-7).
+// one by one (of the output norm, 2,748 tokens: 1.4e-7 against 1.9e-7; sharp
+// heads 2.2e-7 against 3.5e-7, Q x 3 4.3e-7 against 9.6e-7).
 // K is scaled per head, V per head and feature (undone at the end, so that
 // every feature keeps its own precision), Q per query.  The segments of these run K6's
 // loop instead, on the same split of the work (2,748 tokens, 8 such heads: FULL stage

@@ -125,9 +125,8 @@ def test_teacher_targets_few_heads():
 
 
 def test_teacher_targets_large_keys():
-    """K scaled by 2^7 and Q by 2^-7 (exact in bf16): the logits are those of
-    a mild layer, but the key norms leave the fp16 residual's error bound, so
-    the exact-logit kernel computes the offsets."""
+    """K scaled by 2^7 and Q by 2^-7 (exact in bf16): the logits of a mild layer
+    from large keys and small queries."""
     from paper_2609_23733_amd import vp
     log("teacher targets large keys")
     x = synth.make_layer(1, 700, dtype="bf16", key=(33, 0))
