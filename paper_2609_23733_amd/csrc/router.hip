@@ -8,6 +8,8 @@
 // so results are bitwise reproducible run to run.
 #include <type_traits>
 
+#include <float.h>
+
 #include "vp_device.hpp"
 #include "vp_internal.hpp"
 
@@ -475,7 +477,9 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_partial(const void* __r
     const float cs = scale * kLog2e;
 #pragma unroll
     for (int j = 0; j < 8; ++j) qp[j] = active ? q_pool[h * kD + seg * 8 + j] * cs : 0.f;
-    float m = -INFINITY, l = 0.f, C[8], sv[8];
+    // (m starts at the least finite value, not at -inf: a logit of -inf, from an infinite
+    // key, then has weight 0 as a thread's first token, too, instead of 2^(-inf + inf))
+    float m = -FLT_MAX, l = 0.f, C[8], sv[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) C[j] = sv[j] = 0.f;
 
@@ -530,7 +534,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_partial(const void* __r
     }
     __syncthreads();
     if (rr == 0) {
-        float M = -INFINITY;
+        float M = -FLT_MAX;
         for (int q = 0; q < rpi; ++q) M = fmaxf(M, s_m[q * tpr + hs]);
         float L = 0.f, CC[8], SS[8];
 #pragma unroll
@@ -538,7 +542,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_route_partial(const void* __r
         for (int q = 0; q < rpi; ++q) {
             const int src = q * tpr + hs;
             const float mq = s_m[src];
-            const float sc = (mq == -INFINITY) ? 0.f : exp2f_fast(mq - M);
+            const float sc = exp2f_fast(mq - M);
             L += s_l[src] * sc;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -570,8 +574,11 @@ __global__ __launch_bounds__(kCombThreads) void k_route_combine(const float* __r
     const int h = blockIdx.x / (kD / kCombFeat), d0 = blockIdx.x % (kD / kCombFeat) * kCombFeat;
     const int t = threadIdx.x;
     float acc[2];
-    const Combined r = combine_chunks<2, 8>(part + (int64_t)h * nchunks * (2 + 2 * kD), nchunks,
-                                            d0, acc);
+    Combined r = combine_chunks<2, 8>(part + (int64_t)h * nchunks * (2 + 2 * kD), nchunks, d0, acc);
+    if (!(r.L > 0.f)) {   // every logit is -inf or NaN: no weights
+        r.L = NAN;
+        if (r.M == -FLT_MAX) r.M = -INFINITY;
+    }
     if (t < kCombFeat) {
         ctx[h * kD + d0 + t] = acc[0] / r.L;
         vmean[h * kD + d0 + t] = acc[1] / (float)N;

@@ -151,6 +151,32 @@ def test_router_chunk_counts(P):
     check_y(layer.Y[:4].double().cpu().numpy(), ref["Y"], "bf16", False, label="P=%d" % P)
 
 
+@pytest.mark.parametrize("dtype,P", [("bf16", 300), ("f32", 300), ("bf16", 5000)])
+def test_router_key_of_minus_infinity(dtype, P):
+    """An infinite key whose logit is -inf has weight 0 wherever it stands (the first tokens
+    of a chunk's threads, others, the last one; one position per head), and a head of such
+    keys alone has no weights: NaN, which Eq.4 sends to FULL with the flag set."""
+    from paper_2609_23733_amd import vp
+    log("router minus infinity %s P=%d" % (dtype, P))
+    x = synth.make_layer(1, P, dtype=dtype, key=(66, P), sharp=True)
+    qp = oracle.router_pool(x.Q, x.W, x.U, x.w)
+    at = [0, 1, 2, 3, 4, 7, 8, 15, 16, 17, 31, 32, P // 2, P - 2, P - 1]
+    for h, i in enumerate(at):
+        x.K[i, h, 5] = -float("inf") * float(np.sign(qp[h, 5]))
+    x.K[:, 15, 5] = -float("inf") * float(np.sign(qp[15, 5]))
+    layer = run_gpu(x, rule=oracle.RULE_THRESHOLD)
+    st = layer.state
+    for h in range(15):
+        t = x.K[:, h].double().numpy() @ qp[h] / 8
+        p = np.exp(t - t.max())
+        ctx = p @ x.V[:, h].double().numpy() / p.sum()
+        assert abs(float(st.score[h]) * p.sum() - 1) <= 1e-4, (h, float(st.score[h]))
+        err = np.abs(st.ctx[h].double().cpu().numpy() - ctx).max()
+        assert err <= 1e-4 * rms(ctx), (h, err)
+    assert np.isnan(float(st.score[15])) and int(layer.modes[15]) == 2
+    assert int(layer.buckets[19]) & 1
+
+
 @pytest.mark.parametrize("H", [1, 3, 5, 8])
 def test_fewer_heads(H):
     log("H=%d" % H)
